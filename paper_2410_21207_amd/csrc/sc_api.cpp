@@ -65,7 +65,7 @@ size_t ctl_region(int n) { return sc::align_up(sizeof(WsHead) + (size_t)n * size
 // Fill the device descriptor of one image whose scratch starts at `base` and whose Ctl is `ctl`.
 sc::Img make_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long long pitch, int target_w,
                  int32_t* seams_out, int64_t* costs_out, char* base, sc::Ctl* ctl, int kr, int G, int mode) {
-    const sc::Layout L = sc::layout_for(H, W, C, 32);
+    const sc::Layout L = sc::layout_for(H, W, C);
     sc::Img d;
     memset(&d, 0, sizeof(d));
     d.src = src;
@@ -78,9 +78,10 @@ sc::Img make_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long lon
     d.seams_out = seams_out;
     d.costs_out = reinterpret_cast<long long*>(costs_out);
     d.e = reinterpret_cast<uint16_t*>(base + L.e);
-    d.dirs = reinterpret_cast<uint8_t*>(base + L.dirs);
-    d.anc = reinterpret_cast<int8_t*>(base + L.anc);
-    d.xq = reinterpret_cast<uint32_t*>(base + L.xq);
+    d.P = sc::key_rows(H, kr, mode);
+    d.xw = sc::key_pitch(W);
+    d.anc = reinterpret_cast<int8_t*>(base + L.scratch);
+    d.xq = reinterpret_cast<uint32_t*>(base + L.scratch + sc::align_up((size_t)d.P * d.xw, sc::kAlign));
     d.seam = reinterpret_cast<int32_t*>(base + L.seam);
     d.ro = reinterpret_cast<int32_t*>(base + L.ro);
     d.wk = reinterpret_cast<uint8_t*>(base + L.wk);
@@ -90,9 +91,6 @@ sc::Img make_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long lon
     d.bar = &ctl->bar;
     d.status = &ctl->status;
     d.ep = L.ep;
-    d.db = L.db;
-    d.xw = L.xw;
-    d.P = (H + kr - 1) / kr;
     d.G = G;
     d.mode = mode;
     return d;
@@ -107,23 +105,20 @@ int resolve_variant(const sc_tune* t) {
 
 namespace sc {
 
-Layout layout_for(int H, int W, int C, int kr_min) {
+Layout layout_for(int H, int W, int C) {
     Layout L;
-    const int P = (H + kr_min - 1) / kr_min;
-    L.P = P;
     L.ep = (int)align_up((size_t)W + 8, 64);
-    L.db = (int)align_up((size_t)(W + 3) / 4 + 4, 16);
-    L.xw = (int)align_up((size_t)W + 16, 64);
     size_t off = 0;
     L.ctl = 0;
     L.e = off;
     off = align_up(off + (size_t)H * L.ep * 2, kAlign);
-    L.dirs = off;
-    off = align_up(off + (size_t)align_up((size_t)H, 4) * L.db, kAlign);  // rows grouped by four
-    L.anc = off;
-    off = align_up(off + (size_t)P * W, kAlign);
-    L.xq = off;
-    off = align_up(off + (size_t)2 * L.xw * 4, kAlign);
+    // the backtrack's scratch: ancestor offsets and published keys, 5 * key_rows * key_pitch bytes at
+    // most (the largest for 24-row blocks).  The size is that of the 2-bit direction map, the 32-row
+    // phases' offsets and the two exchange rows the carve once kept here: no workspace has grown.
+    L.scratch = off;
+    off = align_up(off + (size_t)align_up((size_t)H, 4) * align_up((size_t)(W + 3) / 4 + 4, 16), kAlign);
+    off = align_up(off + (size_t)((H + 31) / 32) * W, kAlign);
+    off = align_up(off + (size_t)2 * align_up((size_t)W + 16, 64) * 4, kAlign);
     L.seam = off;
     off = align_up(off + (size_t)H * 4, kAlign);
     L.ro = off;
@@ -153,7 +148,7 @@ const char* sc_variant_name(int v) {
 
 size_t sc_workspace_bytes(int H, int W, int C) {
     if (H < 1 || W < 1 || C < 1 || C > 4) return 0;
-    return ctl_region(1) + sc::layout_for(H, W, C, 32).total;
+    return ctl_region(1) + sc::layout_for(H, W, C).total;
 }
 
 sc_status sc_energy(const uint8_t* img, int H, int W, int C, int pitch, int32_t* energy, void* stream) {
@@ -176,12 +171,12 @@ sc_status sc_dp_seam(const int32_t* energy, int H, int W, int32_t* seam, int64_t
     const int v = sc::default_variant();
     char* base = static_cast<char*>(ws);
     sc::Ctl* ctl = reinterpret_cast<sc::Ctl*>(base + sizeof(WsHead));
-    sc::Img d = make_img(nullptr, nullptr, H, W, 1, W, W > 1 ? W - 1 : 1, seam, cost, base + ctl_region(1), ctl,
-                         sc::variant(v).kr, 1, 1);
+    // with dirs_out the sweep runs down over all rows (mode 2) and writes the map itself
+    sc::Img d = make_img(nullptr, dirs_out, H, W, 1, W, W > 1 ? W - 1 : 1, seam, cost, base + ctl_region(1), ctl,
+                         sc::variant(v).kr, 1, dirs_out ? 2 : 1);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = sc::launch_prepare_from_i32(d, energy, st);
     if (e == hipSuccess) e = sc::launch_carve_single(d, v, 1, 0, st);
-    if (e == hipSuccess && dirs_out) e = sc::launch_unpack_dirs(d, dirs_out, st);
     if (e != hipSuccess) return hip_fail(e, "dp launch");
     return ok();
 }
@@ -336,7 +331,7 @@ size_t sc_batch_workspace_bytes(const sc_job* jobs, int n) {
     total += sc::align_up((size_t)n * sizeof(int), sc::kAlign);
     for (int i = 0; i < n; ++i) {
         if (jobs[i].H < 1 || jobs[i].W < 1) return 0;
-        total += sc::layout_for(jobs[i].H, jobs[i].W, jobs[i].C, 32).total;
+        total += sc::layout_for(jobs[i].H, jobs[i].W, jobs[i].C).total;
     }
     return total;
 }
@@ -462,7 +457,7 @@ sc_status sc_batch_prepare(const sc_job* jobs, int n, const sc_tune* tune, void*
         imgs[i] = make_img(j.src, j.img, j.H, j.W, j.C, j.pitch, j.target_w, j.seams_out, j.costs_out,
                            base + off_data, ctl, sc::variant(v).kr, gsz[i], 0);
         if (tune && (tune->flags & SC_TUNE_NO_MINSIDE)) imgs[i].minside = 0;
-        off_data += sc::layout_for(j.H, j.W, j.C, 32).total;
+        off_data += sc::layout_for(j.H, j.W, j.C).total;
         max_rows = std::max(max_rows, j.H);
     }
     memcpy(host.data() + off_blk, blk.data(), blk.size() * sizeof(int2));

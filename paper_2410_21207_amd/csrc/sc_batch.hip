@@ -1,0 +1,99 @@
+// The carve engine over many images: the batched launch and the step-wise launch of a serving loop.
+#include "sc_carver.h"
+
+namespace sc {
+
+// Batched carve: block b is member blk[b].y of team blk[b].x; team t carves the images
+// team_imgs[teams[t].x .. teams[t].x + teams[t].y) one after another.
+template <int CPL, int KR, int NT>
+__global__ __launch_bounds__(NT, 4) void carve_batch_kernel(const Img* __restrict__ imgs, const int2* __restrict__ blk,
+                                                         const int2* __restrict__ teams,
+                                                         const int* __restrict__ team_imgs) {
+    using CV = Carver<CPL, KR, NT>;
+    __shared__ typename CV::Smem sm;
+    const int2 me = blk[blockIdx.x];
+    if (me.x < 0) return;
+    const int2 tr = teams[me.x];
+    for (int i = 0; i < tr.y; ++i) {
+        const CAS Img* gd = (const CAS Img*)(imgs + team_imgs[tr.x + i]);
+        CV::carve_image(gd, me.y, gd->G, sm, 0);
+        __syncthreads();
+    }
+}
+
+// Step-wise carve (serving): each image of the slot table advances by at most max_seams seams and
+// reports how many seams it has removed in total (-1 on a device error, -2 for an empty slot).
+// Without a plan block b carves slot b alone; with one, block b is member plan[b].y of the team of
+// plan[b].z workgroups that carves slot plan[b].x (-1: no work), the members of a team on one XCD.
+// The table is a device array of descriptors written by slot_write_kernel.
+template <int CPL, int KR, int NT>
+__global__ __launch_bounds__(NT, 4) void carve_steps_kernel(const Img* __restrict__ table, int n, int max_seams,
+                                                            unsigned long long budget_ticks,
+                                                            int* __restrict__ progress, const int4* __restrict__ plan) {
+    using CV = Carver<CPL, KR, NT>;
+    __shared__ typename CV::Smem sm;
+    int slot = (int)blockIdx.x, rank = 0, G = 1;
+    if (plan) {
+        const int4 p = plan[blockIdx.x];
+        slot = p.x;
+        rank = p.y;
+        G = p.z;
+    }
+    if (slot < 0 || slot >= n) return;
+    const CAS Img* gd = (const CAS Img*)(table + slot);
+    if (gd->H == 0) {
+        if (rank == 0 && threadIdx.x == 0 && progress) progress[slot] = -2;
+        return;
+    }
+    // a time budget (device wall clock ticks) ends the image's share after the seam that crosses
+    // it, so a step's workgroups stay busy for about the same time
+    CV::carve_image(gd, rank, G, sm, max_seams, budget_ticks ? wall_clock64() + budget_ticks : 0ull);
+    __syncthreads();
+    if (rank == 0 && threadIdx.x == 0 && progress) {
+        const GAS Ctl* ctl = gp(reinterpret_cast<const Ctl*>(gd->amin));
+        progress[slot] = (ctl->status & (kStatusTimeout | kStatusPlacement)) ? -1 : (int)ctl->done;
+    }
+}
+
+hipError_t launch_carve_batch(const Img* imgs, const int2* blk, const int2* teams, const int* ti, int nb, int v,
+                              hipStream_t st) {
+    switch (v) {
+#define X(id, c, k, t) \
+    case id: hipLaunchKernelGGL((carve_batch_kernel<c, k, t>), dim3(nb), dim3(t), 0, st, imgs, blk, teams, ti); break;
+        SC_VARIANTS(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_carve_steps(const Img* table, int n, int v, int max_seams, unsigned long long budget_ticks,
+                              int* progress, const int4* plan, int nblocks, hipStream_t st) {
+    const int nb = plan ? nblocks : n;
+    switch (v) {
+#define X(id, c, k, t)                                                                                        \
+    case id:                                                                                                  \
+        hipLaunchKernelGGL((carve_steps_kernel<c, k, t>), dim3(nb), dim3(t), 0, st, table, n, max_seams, budget_ticks, \
+                           progress, plan);                                                                        \
+        break;
+        SC_VARIANTS(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+int carve_blocks_per_cu(int v) {
+    int nb = 0;
+    hipError_t e = hipErrorInvalidValue;
+    switch (v) {
+#define X(id, c, k, t) \
+    case id: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, carve_batch_kernel<c, k, t>, t, 0); break;
+        SC_VARIANTS(X)
+#undef X
+        default: break;
+    }
+    return e == hipSuccess ? nb : 0;
+}
+
+}  // namespace sc

@@ -1,0 +1,792 @@
+// The carve engine of the seam-carving hot path for gfx950 (CDNA4), included by the .hip sources.
+//
+// Steps (arXiv 2410.21207): e1 energy (sec. "Energy Mapping"), the DP table
+// M(i,j) = e(i,j) + min(M(i-1,j-1..j+1)) (DP section, Alg. 3), the bottom-row
+// argmin, the backtrack (Alg. 3) and the removal of the seam (sec. "Removal of
+// Seams"), repeated once per seam on the current image (flowchart loop).
+//
+// Design (nothing here is a contraction, so no MFMA; every step is integer):
+//  * The energy plane is kept on the device as uint16 (max e = 510*C <= 2040).
+//  * The DP keeps a row of packed 32-bit keys in registers: bits [31:9] hold
+//    M, bits [8:2] an ancestor offset, bits [1:0] the direction tag.  Each lane
+//    owns CPL consecutive columns; neighbours in other lanes arrive through DPP
+//    wave shifts.  The three parent candidates get tags 0/1/2 (left, up,
+//    right) so one v_min3 picks the minimum AND the leftmost tie (reading R5),
+//    and the same add moves the ancestor offset.  The direction bits are
+//    shifted into a byte per lane with v_alignbit (half a byte with CPL 2,
+//    which a lane pair joins) and stored as a 2-bit map.
+//  * A wave owns a strip of S = 64*CPL - 2*KR columns and computes KR halo
+//    columns on each side, so it runs KR rows with no exchange at all
+//    ("ghost zone" tiling); waves exchange the last row of every KR-row phase
+//    through memory and a barrier.
+//  * At the last row of each phase every owned column records how far its
+//    minimal path moved within the phase; the backtrack then hops phase by
+//    phase (one load per phase) and walks the KR rows of every phase in
+//    parallel from an LDS window of the direction map.
+//  * Removal shifts the shorter side of each row one pixel toward the seam
+//    (the right side only when min-side removal is off), row-parallel with
+//    coalesced 16-byte slots, for the image and the energy plane alike;
+//    the energy is then recomputed only at the two new columns {s-1, s} of
+//    each row (the only cells whose stencil changed).
+#pragma once
+#include "sc_device.h"
+
+namespace sc {
+
+constexpr uint32_t QINF = 0xFFFFFF00u;  // "+infinity" key: larger than any real key, +10 cannot wrap
+
+// r + 512 * (low or high 16 bits of `pair`): one v_mad_u32_u16 adds e(i,j) << 9 to a DP key
+// straight from the packed uint16 energy pair, with no separate unpack.
+__device__ __forceinline__ uint32_t mad_lo16(uint32_t pair, uint32_t r) {
+    uint32_t o;
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(o) : "v"(pair), "s"(512u), "v"(r));
+    return o;
+}
+__device__ __forceinline__ uint32_t mad_hi16(uint32_t pair, uint32_t r) {
+    uint32_t o;
+    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(o) : "v"(pair), "s"(512u), "v"(r));
+    return o;
+}
+
+// ----------------------------------------------------------------------------------------------
+// e1 energy at logical column x of a row from a buffer: the row starts at byte offset br of the
+// descriptor's memory, the rows above and below at bu and bd (min-side removal keeps every row at
+// its own offset).  The channel loop runs to 4 with dropped offsets past C, so the loads carry no
+// branches and go out together; a column outside [0, w) is clamped like the pixels of any other
+// (callers do not store its value).
+template <bool COH>
+__device__ __forceinline__ uint32_t energy_buf(__amdgpu_buffer_rsrc_t rb, uint32_t br, uint32_t bu, uint32_t bd, int w,
+                                               int C, int x) {
+    x = min(max(x, 0), w - 1);
+    const int xl = x > 0 ? x - 1 : 0, xr = x + 1 < w ? x + 1 : w - 1;
+    uint32_t s = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const bool ok = c < C;
+        const int a = (int)buf_ld8<COH>(rb, ok ? br + (uint32_t)(xr * C + c) : kBufDrop);
+        const int b = (int)buf_ld8<COH>(rb, ok ? br + (uint32_t)(xl * C + c) : kBufDrop);
+        const int dn = (int)buf_ld8<COH>(rb, ok ? bd + (uint32_t)(x * C + c) : kBufDrop);
+        const int up = (int)buf_ld8<COH>(rb, ok ? bu + (uint32_t)(x * C + c) : kBufDrop);
+        s += (uint32_t)abs(a - b) + (uint32_t)abs(dn - up);
+    }
+    return s;
+}
+
+// ----------------------------------------------------------------------------------------------
+// The carve engine: one image, carved by a team of G workgroups of NT threads.
+template <int CPL, int KR, int NT>
+struct Carver {
+    static constexpr int WIN = 64 * CPL;    // columns a wave computes in the DP
+    static constexpr int S = WIN - 2 * KR;  // columns a strip adds: KR ghost columns on each side
+    static constexpr int NW = NT / 64;      // waves per workgroup
+    static constexpr int PF = 8;            // rows of energy prefetched ahead
+    static constexpr int R = block_rows(KR);  // rows of a backtrack block
+    static constexpr int BCPL = 4;            // columns per lane of a backtrack window
+    static constexpr int BW = 64 * BCPL;      // columns of a backtrack window
+    static constexpr int BS = BW - 2 * R;     // of which exact at the block's last row
+    static constexpr int NG = R / 4;          // 4-row direction groups of a block
+    static constexpr int BMAX = (kMaxRows / 2 + 4) / R + 2;  // blocks of half the tallest image
+    static constexpr int CH = 252 / R + 1;    // hops per memory round trip: h * R + 3 < 256 for h < CH
+    static_assert(CPL == 2 || CPL == 4 || CPL == 8, "one energy load per lane and row");
+    static_assert(KR % R == 0 && R % PF == 0 && KR <= 64 && R <= 63 && KR % CPL == 0 && S > 0, "phase shape");
+
+    struct Smem {
+        int jend[2 * BMAX];            // seam column at the last row of block b of half h at [h * BMAX + b]
+        int2 pos[2];                   // per half: the block the backtrack has reached (-1: done), its column
+        uint32_t cw[2][CH * 128];      // windows of ancestor offsets, 512 bytes per hop
+        unsigned long long red[NW];
+        int flag;
+        int stop;                      // step mode: the time budget is spent
+    };
+
+    struct EV {
+        uint64_t v[(CPL + 3) / 4];  // CPL uint16 energies
+    };
+
+    // Energies at the lane's byte offset `off` of the row starting `soff` bytes into the plane
+    // (wave-uniform: row base plus the row's start offset).  COH sets the sc1 bit.
+    template <bool COH, int N>
+    static __device__ __forceinline__ void load_ev(uint64_t (&e)[(N + 3) / 4], __amdgpu_buffer_rsrc_t re, uint32_t soff,
+                                                   uint32_t off) {
+        if constexpr (N == 2) {
+            e[0] = __builtin_amdgcn_raw_buffer_load_b32(re, (int)off, (int)soff, COH ? 16 : 0);
+        } else if constexpr (N == 4) {
+            const v2u v = __builtin_amdgcn_raw_buffer_load_b64(re, (int)off, (int)soff, COH ? 16 : 0);
+            e[0] = ((uint64_t)v[1] << 32) | v[0];
+        } else {
+            const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, (int)off, (int)soff, COH ? 16 : 0);
+            e[0] = ((uint64_t)v[1] << 32) | v[0];
+            e[1] = ((uint64_t)v[3] << 32) | v[2];
+        }
+    }
+
+    // The rows of one half (h = 0: from the top down to the split row, 1: from the bottom up).
+    // Virtual row v of a half is image row v - pad counted from the half's border; the rows below
+    // pad do not exist and carry zero energy, so that the half is a whole number of blocks and its
+    // first real row costs its own energy.
+    struct Half {
+        int n, B, pad;  // rows, blocks, missing rows
+    };
+    static __device__ __forceinline__ Half half_of(int H, int mode, int h) {
+        const int m = split_row(H, mode);
+        Half x;
+        x.n = h ? H - m : m;
+        x.B = (x.n + R - 1) / R;
+        x.pad = x.B * R - x.n;
+        return x;
+    }
+
+    static __device__ __forceinline__ int strips(int w) { return w <= WIN ? 1 : (w - 2 * KR + S - 1) / S; }
+
+    // Byte offset in the energy plane of virtual row v (its base plus its start offset) of half h,
+    // rows outside the half clamped to its ends.
+    template <bool COH>
+    static __device__ __forceinline__ uint32_t row_off(const Img& d, const Half& x, int h, int v,
+                                                       __amdgpu_buffer_rsrc_t rro) {
+        const int i = min(max(v - x.pad, 0), x.n - 1);
+        const int r = h ? d.H - 1 - i : i;
+        return (uint32_t)r * (uint32_t)d.ep * 2u + 2u * buf_ld32<COH>(rro, (uint32_t)r * 4u);
+    }
+
+    // ---- the cost sweep (a3): keys M << 9 only, no directions.
+    //
+    // A seam's cost table is swept from both ends of the image at once, T from the top row down to
+    // the split row and B from the bottom row up, and the cheapest pair of adjacent cells in the two
+    // middle rows gives the seam's cost and its two middle columns.  The tie rules survive: among
+    // the cheapest seams the backtrack wants the smallest (s[H-1], ..., s[0]), paths chosen by
+    // "leftmost minimum" from neighbouring cells never cross, so in the lower half the leftmost
+    // child leads to the leftmost end, and the leftmost middle column to the leftmost path of all.
+    //
+    // What bounds it: a chain of rows, each one wave's instructions.  Without directions and
+    // ancestor offsets a row is a v_min3 and a v_mad per column and two wave shifts; the two ends
+    // halve the chain.
+    struct Item {
+        int p, j;      // phase, the wave's item in it
+        int h, t;      // half, strip
+        int v0, v1;    // virtual rows
+        int drop;      // leading rows without energy (first phase)
+        uint32_t off;  // byte offset of the lane's first column in an energy row
+        int col0;      // the lane's first column
+        int ns;
+    };
+    static __device__ __forceinline__ Item make_item(const Half (&hf)[2], int w, int ns, int tw, int TW, int p, int j,
+                                                     int lane) {
+        Item it;
+        it.p = p;
+        it.j = j;
+        it.ns = ns;
+        const int q = tw + j * TW;
+        const bool two = hf[1].n > 0;
+        it.h = two ? q & 1 : 0;
+        it.t = two ? q >> 1 : q;
+        const Half x = it.h ? hf[1] : hf[0];
+        it.v0 = p ? p * KR : x.pad & ~(PF - 1);
+        it.v1 = min(x.B * R, p * KR + KR);
+        it.drop = p ? 0 : x.pad & (PF - 1);
+        const int base = it.t == ns - 1 ? max(0, w - WIN) : it.t * S;
+        it.col0 = base + lane * CPL;
+        it.off = (uint32_t)(it.col0 < w ? it.col0 : 0) * 2u;
+        return it;
+    }
+
+    // EDGE: the one strip of an image narrower than a window (columns from w on are kept all ones).
+    template <bool EDGE>
+    static __device__ __forceinline__ void cost_step(uint32_t (&Q)[CPL], uint32_t& left, uint32_t& right,
+                                                     const uint64_t (&ev)[(CPL + 3) / 4], const uint32_t (&em)[CPL]) {
+        // Neighbours of the lane's first and last column come from lanes -1 and +1.  Lane 0's left and
+        // lane 63's right keep all ones: a window's side is either the image's edge, where that is the
+        // missing parent, or ghost columns, where a wrong value moves one column inward per row and
+        // never reaches an owned column within a phase.
+        left = (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)Q[CPL - 1], 0x138, 0xf, 0xf, false);
+        right = (uint32_t)__builtin_amdgcn_update_dpp((int)right, (int)Q[0], 0x130, 0xf, 0xf, false);
+        uint32_t n[CPL];
+#pragma unroll
+        for (int k = 0; k < CPL; ++k)
+            n[k] = min(min(k ? Q[k - 1] : left, Q[k]), k + 1 < CPL ? Q[k + 1] : right);
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) {
+            const uint32_t pair = (uint32_t)(ev[k >> 2] >> (((k >> 1) & 1) * 32));
+            Q[k] = (k & 1) ? mad_hi16(pair, n[k]) : mad_lo16(pair, n[k]);
+            if (EDGE) Q[k] |= em[k];
+        }
+    }
+
+    // Tag of the keys a seam publishes: 1..511, never the 0 of a cleared row.  Every row of ck is
+    // written once per seam, so a reader only has to tell a seam from the one before it.
+    static __device__ __forceinline__ uint32_t seam_tag(int k) { return 1u + (uint32_t)k % 511u; }
+
+    // Returns false when the wait for a neighbour's keys timed out (the image's status says so).
+    template <bool EDGE, bool TEAM>
+    static __device__ __forceinline__ bool cost_sweep(const Img& d, int w, int k, int tw, int TW, int lane) {
+        const Half hf[2] = {half_of(d.H, d.mode, 0), half_of(d.H, d.mode, 1)};
+        const int ns = strips(w), items = hf[1].n > 0 ? 2 * ns : ns;
+        if (tw >= items) return true;
+        const int nsw = (items - tw + TW - 1) / TW;
+        const int P0 = (hf[0].B * R + KR - 1) / KR, P1 = (hf[1].B * R + KR - 1) / KR;
+        const uint32_t tag = seam_tag(k);
+        const __amdgpu_buffer_rsrc_t re = make_rsrc(d.e, (uint32_t)d.H * (uint32_t)d.ep * 2u);
+        const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
+        const uint32_t ckrow = (uint32_t)d.xw * 4u;
+        const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
+
+        Item it = make_item(hf, w, ns, tw, TW, 0, 0, lane);
+        uint32_t roff = row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro);
+        uint64_t ring[PF][(CPL + 3) / 4];
+#pragma unroll
+        for (int i = 0; i < PF; ++i)
+            load_ev<TEAM, CPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), i < it.drop ? kBufDrop : it.off);
+        uint32_t Q[CPL], em[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            em[c] = EDGE && it.col0 + c >= w ? 0xFFFFFFFFu : 0u;
+            Q[c] = em[c];
+        }
+        uint32_t left = 0xFFFFFFFFu, right = 0xFFFFFFFFu;
+        for (;;) {
+            // the wave's next item: its row offsets now, its first rows during this item's last block
+            int pn = it.p, jn = it.j;
+            do {
+                if (++jn == nsw) jn = 0, ++pn;
+            } while (pn < P0 && hf[1].n > 0 && pn >= P1 && ((tw + jn * TW) & 1));
+            const bool more = pn < P0;
+            const Item nx = more ? make_item(hf, w, ns, tw, TW, pn, jn, lane) : it;
+            const uint32_t roffn = row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro);
+            // keys of the row above: the ghost columns, or every column when the wave has several items
+            if (it.p == 0) {
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) Q[c] = em[c];
+            } else if (ns > 1) {
+                const bool need = nsw > 1 || (it.t > 0 && lane < KR / CPL) || (it.t < ns - 1 && lane >= 64 - KR / CPL);
+                const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + it.v0 / R - 1) * ckrow;
+                const uint32_t ko = need ? (uint32_t)it.col0 * 4u : kBufDrop;
+                unsigned long long t0 = 0;
+                for (int n = 0;; ++n) {
+                    uint32_t x[CPL];
+                    if constexpr (CPL == 2) {
+                        const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rck, (int)ko, (int)krow, 16);
+                        x[0] = v[0], x[1] = v[1];
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < CPL; c += 4) {
+                            const v4u v = __builtin_amdgcn_raw_buffer_load_b128(rck, (int)(ko + 4u * c), (int)krow, 16);
+                            x[c] = v[0], x[c + 1] = v[1], x[c + 2] = v[2], x[c + 3] = v[3];
+                        }
+                    }
+                    bool ok = true;
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) ok = ok && (x[c] & 0x1FFu) == tag;
+                    if (__all(ok || !need)) {
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) Q[c] = need ? x[c] & ~0x1FFu : Q[c];
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                    if ((n & 63) == 63) {  // bounded wait: 10 s at the 100 MHz constant clock
+                        const unsigned long long now = wall_clock64();
+                        if (t0 == 0) t0 = now;
+                        if (now - t0 > 1000000000ull ||
+                            (__hip_atomic_load(gp(d.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+                             (kStatusTimeout | kStatusPlacement))) {
+                            if (lane == 0)
+                                __hip_atomic_fetch_or(gp(d.status), kStatusTimeout, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+                            return false;
+                        }
+                    }
+                }
+            }
+            // exact columns go out with the seam's tag at every block's last row (whole lanes: a
+            // window's side is ghost columns or the image's edge); the next phase's neighbours and
+            // the backtrack blocks start from them.  Columns two strips share are stored twice with
+            // the same value.
+            const bool pub = (it.t == 0 || lane >= KR / CPL) && (it.t == ns - 1 || lane < 64 - KR / CPL);
+            auto publish = [&](int v) {  // v: the row just done is v - 1
+                const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + v / R - 1) * ckrow;
+                if constexpr (EDGE) {
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c)
+                        __builtin_amdgcn_raw_buffer_store_b32((Q[c] & ~0x1FFu) | tag, rck, (int)(em[c] ? kBufDrop : (uint32_t)(it.col0 + c) * 4u),
+                                                              (int)krow, 0);
+                } else {
+                    const uint32_t ko = pub ? (uint32_t)it.col0 * 4u : kBufDrop;
+                    if constexpr (CPL == 2) {
+                        __builtin_amdgcn_raw_buffer_store_b64((v2u){Q[0] | tag, Q[1] | tag}, rck, (int)ko, (int)krow, 0);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < CPL; c += 4)
+                            buf_st128(rck, (v4u){Q[c] | tag, Q[c + 1] | tag, Q[c + 2] | tag, Q[c + 3] | tag},
+                                      krow + ko + 4u * c);
+                    }
+                }
+            };
+            int v = it.v0;
+#pragma unroll 1
+            while (v < it.v1) {
+                // the next rows' scalar offsets first: a scalar written by the vector unit may not be
+                // used as a buffer offset for some cycles
+                const bool cross = v + PF >= it.v1;
+                const uint32_t ro = cross ? roffn : roff;
+                const uint32_t eo = cross ? nx.off : it.off;
+                const int l0 = cross ? 0 : v + PF - it.v0;
+                const int dr = cross && more ? nx.drop : 0;
+                uint32_t so[PF];
+#pragma unroll
+                for (int i = 0; i < PF; ++i) so[i] = (uint32_t)__builtin_amdgcn_readlane(ro, l0 + i);
+#pragma unroll
+                for (int i = 0; i < PF; ++i) {
+                    cost_step<EDGE>(Q, left, right, ring[i], em);
+                    load_ev<TEAM, CPL>(ring[i], re, so[i], eo);
+                    __builtin_amdgcn_sched_barrier(0);  // keep the prefetch PF rows ahead of its use
+                }
+                if (dr) {  // another first-phase item: its missing rows carry no energy
+#pragma unroll
+                    for (int i = 0; i < PF; ++i)
+#pragma unroll
+                        for (int c = 0; c < (CPL + 3) / 4; ++c) ring[i][c] = i < dr ? 0 : ring[i][c];
+                }
+                v += PF;
+                if (v % R == 0) publish(v);
+            }
+            if (!more) return true;
+            it = nx;
+            roff = roffn;
+        }
+    }
+
+    // ---- the middle (a4): the cheapest pair of T's and B's last rows, leftmost lower column, then
+    // leftmost upper one (an image of one half: the leftmost minimum of T's last row).  Every
+    // workgroup of a team finds it by itself.  Key: M << 32 | lower column << 2 | (upper - lower + 1).
+    template <bool COH>
+    static __device__ __forceinline__ unsigned long long middle(const Img& d, Smem& sm, int w) {
+        constexpr int kC = COH ? 16 : 0;
+        const Half h0 = half_of(d.H, d.mode, 0), h1 = half_of(d.H, d.mode, 1);
+        const uint32_t ckrow = (uint32_t)d.xw * 4u;
+        const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
+        const uint32_t t0 = (uint32_t)(h0.B - 1) * ckrow, b0 = (uint32_t)(h0.B + max(h1.B, 1) - 1) * ckrow;
+        unsigned long long best = ~0ull;
+        for (int c0 = 4 * (int)threadIdx.x; c0 < w; c0 += 4 * NT) {
+            const v4u T = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)t0, kC);
+            if (h1.n == 0) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (c0 + c < w)
+                        best = min(best, ((unsigned long long)(T[c] >> 9) << 32) | (unsigned)((c0 + c) << 2) | 1u);
+                continue;
+            }
+            const v4u B = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)b0, kC);
+            const uint32_t tl = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)t0, kC);
+            const uint32_t tr = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 + 4 < w ? c0 * 4 + 16 : (int)kBufDrop, (int)t0, kC);
+            const uint32_t x[6] = {tl, T[0], T[1], T[2], T[3], tr};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (c0 + c >= w) continue;
+                uint32_t m = c0 + c > 0 ? x[c] >> 9 : 0x7FFFFFFFu, dir = 0;
+                if ((x[c + 1] >> 9) < m) m = x[c + 1] >> 9, dir = 1;
+                if (c0 + c + 1 < w && (x[c + 2] >> 9) < m) m = x[c + 2] >> 9, dir = 2;
+                best = min(best, ((unsigned long long)(m + (B[c] >> 9)) << 32) | (unsigned)((c0 + c) << 2) | dir);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) best = min(best, (unsigned long long)__shfl_xor((long long)best, o, 64));
+        if ((threadIdx.x & 63) == 0) sm.red[threadIdx.x >> 6] = best;
+        __syncthreads();
+        best = sm.red[0];
+#pragma unroll
+        for (int i = 1; i < NW; ++i) best = min(best, sm.red[i]);
+        return best;
+    }
+
+    // ---- the backtrack (a5).  The cost sweep leaves the keys of every block's last row in ck; a
+    // block's directions are computed again, for a window of columns, with keys M << 9 | u << 2 | tag:
+    // the candidates get tags 0 / 1 / 2 (left, middle, right) and move u by the same, so one v_min3
+    // picks the minimum, the leftmost tie and the ancestor's offset.  On return pk[g] holds the
+    // directions of the block's rows 4g .. 4g+3 (a byte per row, 2 bits per column) and Q the keys of
+    // its last row.  All blocks run at once, one wave each, where the path can still be.
+    template <bool EDGE, bool COH>
+    static __device__ __forceinline__ void trace_block(const Img& d, const Half& x, int h, int blk, int ckbase, int w,
+                                                       int base, int lane, uint32_t (&pk)[NG], uint32_t (&Q)[BCPL]) {
+        const __amdgpu_buffer_rsrc_t re = make_rsrc(d.e, (uint32_t)d.H * (uint32_t)d.ep * 2u);
+        const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
+        const uint32_t ckrow = (uint32_t)d.xw * 4u;
+        const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
+        const int col0 = base + lane * BCPL;
+        const uint32_t roff = row_off<COH>(d, x, h, blk * R + min(lane, R - 1), rro);
+        const v4u kv = __builtin_amdgcn_raw_buffer_load_b128(rck, blk > 0 && col0 < w ? col0 * 4 : (int)kBufDrop,
+                                                             (int)((uint32_t)(ckbase + max(blk, 1) - 1) * ckrow), COH ? 16 : 0);
+        const uint32_t eo = (uint32_t)(col0 < w ? col0 : 0) * 2u;
+        const int drop = blk ? 0 : x.pad;  // rows without energy
+        uint64_t ring[PF][1];
+#pragma unroll
+        for (int i = 0; i < PF; ++i)
+            load_ev<COH, BCPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), i < drop ? kBufDrop : eo);
+        bool valid[BCPL];
+#pragma unroll
+        for (int c = 0; c < BCPL; ++c) {
+            valid[c] = !EDGE || col0 + c < w;
+            Q[c] = valid[c] ? kv[c] & ~0x1FFu : QINF;
+        }
+        uint32_t left = QINF, right = QINF, p = 0;
+        static_for<R>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            uint32_t t[BCPL];
+#pragma unroll
+            for (int c = 0; c < BCPL; ++c) t[c] = Q[c] & ~3u;
+            left = (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)t[BCPL - 1], 0x138, 0xf, 0xf, false);
+            right = (uint32_t)__builtin_amdgcn_update_dpp((int)right, (int)(t[0] + 10u), 0x130, 0xf, 0xf, false);
+            uint32_t acc = 0;
+#pragma unroll
+            for (int c = 0; c < BCPL; ++c) {
+                const uint32_t m = min(min(c ? t[c - 1] : left, t[c] + 5u), c + 1 < BCPL ? t[c + 1] + 10u : right);
+                const uint32_t pair = (uint32_t)(ring[i % PF][0] >> ((c >> 1) * 32));
+                Q[c] = (c & 1) ? mad_hi16(pair, m) : mad_lo16(pair, m);
+                if (EDGE) Q[c] = valid[c] ? Q[c] : QINF;
+                acc = __builtin_amdgcn_alignbit(m, acc, 2u);
+            }
+            p = __builtin_amdgcn_perm(acc, p, 0x07030201u);  // this row's byte on top
+            if constexpr (i % 4 == 3) pk[i / 4] = p;
+            if constexpr (i + PF < R)
+                load_ev<COH, BCPL>(ring[i % PF], re, (uint32_t)__builtin_amdgcn_readlane(roff, i + PF),
+                                   i + PF < drop ? kBufDrop : eo);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+
+    // Every direction of the map as bytes (one half, mode 2): windows dealt to the waves of the team.
+    template <bool COH>
+    static __device__ __forceinline__ void write_map(const Img& d, int w, int tw, int TW, int lane) {
+        const Half x = half_of(d.H, d.mode, 0);
+        const int nw = w <= BW ? 1 : (w - 2 * R + BS - 1) / BS;
+        const __amdgpu_buffer_rsrc_t ro = make_rsrc(d.img, (uint32_t)d.H * (uint32_t)w);
+        for (int q = tw; q < x.B * nw; q += TW) {
+            const int blk = q / nw, j = q % nw, base = j * BS, col0 = base + lane * BCPL;
+            uint32_t pk[NG], Q[BCPL];
+            trace_block<true, COH>(d, x, 0, blk, 0, w, base, lane, pk, Q);
+            const bool own = (j == 0 || lane >= R / BCPL) && (j == nw - 1 || lane < 64 - R / BCPL);
+            for (int i = 0; i < R; ++i) {
+                const int y = blk * R + i - x.pad;
+                if (y < 0) continue;
+                uint32_t v = 0;
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    if (g == i / 4) v = pk[g];
+                v = y ? v >> (8 * (i & 3)) : 0x55u;  // row 0 has no parent: 1
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c)
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((v >> (2 * c)) & 3u), ro,
+                                                         (int)(own && col0 + c < w ? (uint32_t)(col0 + c) : kBufDrop),
+                                                         (int)((uint32_t)y * (uint32_t)w), 0);
+            }
+        }
+    }
+
+    // The seam from its middle columns outward, written to d.seam (and seams_out).  Rounds: the
+    // waves of the team are split over the halves still open and, in each, over the blocks from the
+    // one the path has reached toward the border, with as many windows per block as there are
+    // waves for, centred at the path's column; then every workgroup hops through the blocks' ancestor
+    // offsets as far as the path stays inside the windows' exact columns, and the waves that hold a
+    // block of the path walk it from their registers.  One round is enough unless the path drifts
+    // out or the team has fewer waves than blocks.
+    template <bool TEAM>
+    static __device__ __forceinline__ bool backtrack(const Img& d, const CAS Img* gd, Smem& sm, int w, int k, int tw, int TW, int lane,
+                                                     int G, unsigned& epoch, unsigned long long key) {
+        const Half hf[2] = {half_of(d.H, d.mode, 0), half_of(d.H, d.mode, 1)};
+        const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const __amdgpu_buffer_rsrc_t ranc = make_rsrc(d.anc, (uint32_t)d.P * (uint32_t)d.xw);
+        int cB = min(max((int)((key & 0xffffffffu) >> 2), 0), w - 1);
+        int b[2], c[2];
+        b[0] = hf[0].B - 1;
+        b[1] = hf[1].B - 1;  // -1 when there is no lower half
+        c[1] = cB;
+        c[0] = min(max(cB + (int)(key & 3u) - 1, 0), w - 1);
+        while (b[0] >= 0 || b[1] >= 0) {
+            // the round's plan (the same in every wave of the team)
+            const int nopen = (b[0] >= 0) + (b[1] >= 0);
+            const int NWH = max(1, TW / nopen);
+            int nblk[2], nwin[2], X0[2], ulo[2], uhi[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                nblk[h] = min(b[h] + 1, NWH);
+                const int all = w <= BW ? 1 : (w - 2 * R + BS - 1) / BS;
+                nwin[h] = nblk[h] > 0 ? min(all, NWH / nblk[h]) : 1;
+                const int span = nwin[h] * BS + 2 * R;
+                X0[h] = max(0, min(c[h] - span / 2, w - span));
+                const int end = min(X0[h] + span, max(w, BW));
+                ulo[h] = X0[h] == 0 ? 0 : X0[h] + R;
+                uhi[h] = end >= w ? w : end - R;
+            }
+            const int h = nopen == 2 ? tw & 1 : (b[0] >= 0 ? 0 : 1);
+            const int idx = nopen == 2 ? tw >> 1 : tw;
+            const Half x = h ? hf[1] : hf[0];
+            const int nw = h ? nwin[1] : nwin[0];
+            const bool act = idx < (h ? nblk[1] : nblk[0]) * nw;
+            const int blk = (h ? b[1] : b[0]) - idx / nw;
+            const int base = min((h ? X0[1] : X0[0]) + (idx % nw) * BS, max(0, w - BW));
+            const int elo = base == 0 ? 0 : base + R, ehi = base + BW >= w ? w : base + BW - R;
+            uint32_t pk[NG];
+            if (act) {
+                uint32_t Q[BCPL];
+                const int ckb = h ? hf[0].B : 0;
+                if (base + BW > w) trace_block<true, TEAM>(d, x, h, blk, ckb, w, base, lane, pk, Q);
+                else trace_block<false, TEAM>(d, x, h, blk, ckb, w, base, lane, pk, Q);
+                // ancestor offsets of the exact columns (whole lanes; a lane past w - 1 writes into
+                // the row's slack)
+                const int col0 = base + lane * BCPL;
+                const bool own = (base == 0 || lane >= R / BCPL) && (base + BW >= w || lane < 64 - R / BCPL) && col0 < w;
+                uint32_t a = 0;
+#pragma unroll
+                for (int q = 0; q < BCPL; ++q) a |= (((Q[q] >> 2) & 127u) & 0xFFu) << (8 * q);
+                __builtin_amdgcn_raw_buffer_store_b32(a, ranc, (int)(own ? (uint32_t)col0 : kBufDrop),
+                                                      (int)((uint32_t)(ckb + blk) * (uint32_t)d.xw), 0);
+            }
+            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return false;
+            // wave h hops through half h: a block's path column at its last row is within R columns of
+            // the next block's, so a round trip loads the offsets of CH blocks at once (512 bytes of
+            // each row around the current column) and takes CH hops from LDS
+            const int hh = wv & 1;
+            if (wv < 2 && (hh ? b[1] : b[0]) >= 0) {
+                const int ckb = hh ? hf[0].B : 0, lo = hh ? ulo[1] : ulo[0], hi = hh ? uhi[1] : uhi[0];
+                uint32_t* cw = sm.cw[hh];
+                int p = hh ? b[1] : b[0], j = hh ? c[1] : c[0];
+                const int low = p - (hh ? nblk[1] : nblk[0]) + 1;
+                bool run = true;
+                if (lane == 0) sm.jend[hh * BMAX + p] = j;
+                while (run) {
+                    const int j0 = j, p0 = p, m = min(CH, p - max(low, 1) + 1);
+                    uint32_t v[CH][2];
+#pragma unroll
+                    for (int i = 0; i < CH; ++i) {
+                        // byte window [o, o + 512) of block p - i's row, from a dword at or below j - 256;
+                        // dwords before the array are dropped
+                        const int o = (ckb + p0 - i) * d.xw + ((j0 - 256) & ~3);
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            const int bo = o + 4 * (lane + 64 * q);
+                            v[i][q] = buf_ld32<TEAM>(ranc, i < m && bo >= 0 ? (uint32_t)bo : kBufDrop);
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < CH; ++i) {
+                        cw[i * 128 + lane] = v[i][0];
+                        cw[i * 128 + 64 + lane] = v[i][1];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    const uint8_t* cb = reinterpret_cast<const uint8_t*>(cw);
+                    for (int i = 0; i < m; ++i) {
+                        const int a = (int)(int8_t)cb[i * 512 + min(max(j - ((j0 - 256) & ~3), 0), 511)];
+                        j = __builtin_amdgcn_readfirstlane(min(max(j + a - R, 0), w - 1));
+                        --p;
+                        if (p < low || j < lo || j >= hi) {
+                            run = false;
+                            break;
+                        }
+                        if (lane == 0) sm.jend[hh * BMAX + p] = j;
+                    }
+                    if (run && p == 0) {
+                        run = false;
+                        p = -1;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+                if (lane == 0) sm.pos[hh] = make_int2(p, j);
+            }
+            __syncthreads();
+            const int nb0 = b[0] >= 0 ? sm.pos[0].x : -1, nb1 = b[1] >= 0 ? sm.pos[1].x : -1;
+            if (act && blk > (h ? nb1 : nb0)) {
+                const int je = __builtin_amdgcn_readfirstlane(sm.jend[h * BMAX + blk]);
+                if (je >= elo && je < ehi) {
+                    int s = je - base, mys = 0;
+                    static_for<R>([&](auto I) {
+                        constexpr int i = R - 1 - decltype(I)::value;
+                        mys = lane == i ? s : mys;
+                        if constexpr (i > 0) {
+                            const uint32_t wd = (uint32_t)__builtin_amdgcn_readlane((int)pk[i / 4], s >> 2);
+                            s += (int)((wd >> ((i & 3) * 8 + (s & 3) * 2)) & 3u) - 1;
+                        }
+                    });
+                    const int y = blk * R + lane - x.pad;
+                    if (lane < R && y >= 0) {
+                        const int r = h ? d.H - 1 - y : y;
+                        const int col = min(max(base + mys, 0), w - 1);
+                        *gp(d.seam + r) = col;
+                        if (d.seams_out) *gp(d.seams_out + (size_t)k * d.H + r) = col;
+                    }
+                }
+            }
+            if (b[0] >= 0) b[0] = nb0, c[0] = sm.pos[0].y;
+            if (b[1] >= 0) b[1] = nb1, c[1] = sm.pos[1].y;
+        }
+        return true;
+    }
+
+    // ---- removal (a6) of rows [ra, rb): the shorter side of a row moves (pixels right of the seam one
+    // column left, or pixels left of it one column right with the row's start offset advanced by one;
+    // without min-side removal always the right side).  A row is only ever written by the wave owning
+    // it, so plain loads see its current bytes even in a team.
+    template <bool TEAM>
+    static __device__ __forceinline__ void remove_rows(const Img& d, int w, int ra, int rb, int lane) {
+        const __amdgpu_buffer_rsrc_t rsm = make_rsrc(d.seam, (uint32_t)d.H * 4u);
+        for (int rc = ra; rc < rb; rc += 64) {
+            const int n = min(64, rb - rc);
+            const int s = min(max((int)buf_ld32<TEAM>(rsm, lane < n ? (uint32_t)(rc + lane) * 4u : kBufDrop), 0), w - 1);
+            const int o = lane < n ? *gp(d.ro + rc + lane) : 0;
+            const bool right = d.minside && s < w - 1 - s;
+            if (lane < n && right) *gp(d.ro + rc + lane) = o + 1;
+            const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
+                                          shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, 2)};
+            shift_rows<2, 2>(planes, n, w, s, o, right, lane);
+        }
+    }
+
+    // Seams k_begin .. k_end-1 of one image (the image has W - k_begin columns on entry).  With a
+    // deadline (device wall clock) it stops after the first seam that ends past it.  Returns the
+    // number of seams removed in total (k_begin + the seams of this call).
+    template <bool TEAM, bool MAP>
+    static __device__ __forceinline__ int carve_seams(const CAS Img* gd, int rank, int G, Smem& sm, int k_begin, int k_end,
+                                                      unsigned& epoch, unsigned long long deadline) {
+        const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        // waves are numbered across the team first, so a phase's strips land on different compute
+        // units (one DP wave per SIMD) before any workgroup takes a second one
+        const int TW = G * NW, tw = wv * G + rank;
+        const int H = gd->H, W = gd->W, mode = gd->mode;
+        const int rpw = (H + TW - 1) / TW;
+        const int ra = min(H, tw * rpw), rb = min(H, ra + rpw);  // rows this wave owns
+        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(gd->amin));
+        const bool timer = rank == 0 && threadIdx.x == 0;  // one clock reader per image
+        unsigned long long tm0 = 0, tm1 = 0, tm2 = 0;
+        for (int k = k_begin; k < k_end; ++k) {
+            const int w = W - k;
+            if (timer) tm0 = wall_clock64();
+            {
+                const Img d = fetch(gd);
+                // a wave that gave up waiting has flagged the image, and the team's barrier abandons it
+                if (w < WIN) cost_sweep<true, TEAM>(d, w, k, tw, TW, lane);
+                else cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
+            }
+            // the keys of every block are complete past here
+            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            {
+                const Img d = fetch(gd);
+                const unsigned long long key = middle<TEAM>(d, sm, w);
+                if (rank == 0 && threadIdx.x == 0 && d.costs_out) *gp(d.costs_out + k) = (long long)(key >> 32);
+                if (timer) tm1 = wall_clock64();
+                if constexpr (MAP) {
+                    if (mode == 2) write_map<TEAM>(d, w, tw, TW, lane);
+                }
+                if (!backtrack<TEAM>(d, gd, sm, w, k, tw, TW, lane, G, epoch, key)) return k;
+            }
+            if (mode) break;
+            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            remove_rows<TEAM>(fetch(gd), w, ra, rb, lane);
+            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            if (timer) tm2 = wall_clock64();
+            const Img d = fetch(gd);
+            // ---- band energy (a2): only the new columns s-1 and s of each row changed.  Buffer
+            // loads (sc1 in a team: the rows above and below were shifted by other workgroups) at
+            // 32-bit offsets; a lane past the wave's rows reads row ra and stores nothing.
+            const int w2 = w - 1;
+            const __amdgpu_buffer_rsrc_t rwk = make_rsrc(d.wk, (uint32_t)H * (uint32_t)d.wp);
+            const __amdgpu_buffer_rsrc_t rsm = make_rsrc(d.seam, (uint32_t)H * 4u);
+            const __amdgpu_buffer_rsrc_t rof = make_rsrc(d.ro, (uint32_t)H * 4u);
+            for (int rc = ra; rc < rb; rc += 64) {
+                const int r = rc + lane < rb ? rc + lane : ra;
+                const int ru = r > 0 ? r - 1 : 0, rd = r + 1 < H ? r + 1 : H - 1;
+                const int s = min(max((int)buf_ld32<TEAM>(rsm, (uint32_t)r * 4u), 0), w - 1);
+                const int o = (int)buf_ld32<TEAM>(rof, (uint32_t)r * 4u);
+                const uint32_t br = (uint32_t)r * (uint32_t)d.wp + (uint32_t)(o * d.C);
+                const uint32_t bu = (uint32_t)ru * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)ru * 4u) * (uint32_t)d.C;
+                const uint32_t bd = (uint32_t)rd * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)rd * 4u) * (uint32_t)d.C;
+                const uint32_t e0 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s - 1);
+                const uint32_t e1 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s);
+                if (rc + lane < rb) {
+                    uint16_t* er = d.e + (size_t)r * d.ep + o;
+                    if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = (uint16_t)e0;
+                    if (s < w2) *gp(er + s) = (uint16_t)e1;
+                }
+            }
+            // a team's time budget: its first member decides before the seam's last barrier, every
+            // member reads the decision after it
+            if (deadline && G > 1 && k + 1 < k_end && rank == 0 && threadIdx.x == 0)
+                __hip_atomic_store(&ctl->stop, wall_clock64() >= deadline ? 1u : 0u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            if (deadline && G > 1 && k + 1 < k_end && __hip_atomic_load(&ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) k_end = k + 1;
+            if (timer) {
+                const unsigned long long tm3 = wall_clock64();
+                ctl->t_stage[0] += tm1 - tm0;
+                ctl->t_stage[1] += tm2 - tm1;
+                ctl->t_stage[2] += tm3 - tm2;
+            }
+            if (deadline && G == 1 && k + 1 < k_end) {  // one decision for the whole workgroup
+                if (threadIdx.x == 0) sm.stop = wall_clock64() >= deadline;
+                __syncthreads();
+                const int stop = sm.stop;
+                __syncthreads();
+                if (stop) k_end = k + 1;
+            }
+        }
+        // ---- after the last seam, the carved rows go from wk (each from its start offset) to img
+        const Img d = fetch(gd);
+        if (!mode && k_end == W - d.target_w && k_end > k_begin) {
+            const int nb = d.target_w * d.C;
+            for (int rc = ra; rc < rb; rc += 64) {
+                const int n = min(64, rb - rc);
+                const int rof = lane < n ? *gp(d.ro + rc + lane) : 0;
+#pragma unroll 1
+                for (int i = 0; i < n; ++i) {
+                    const int o = __builtin_amdgcn_readlane(rof, i);
+                    copy_bytes_wave(d.img + (long long)(rc + i) * d.pitch, d.wk + (long long)(rc + i) * d.wp + (long long)o * d.C,
+                                    nb, lane);
+                }
+            }
+            team_sync<TEAM>(gd, epoch, G, &sm.flag);
+        }
+        return k_end;
+    }
+
+    // Carve one image, or (max_seams > 0) continue it by at most max_seams seams.
+    template <bool MAP = false>
+    static __device__ __forceinline__ void carve_image(const CAS Img* gd, int rank, int G, Smem& sm, int max_seams,
+                                                       unsigned long long deadline = 0) {
+        const Img d = fetch(gd);
+        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.amin));
+        const int nseams = d.mode ? 1 : d.W - d.target_w;
+        const int k0 = max_seams > 0 ? (int)ctl->done : 0;
+        const int k1 = max_seams > 0 ? min(nseams, k0 + max_seams) : nseams;
+        if (k0 >= k1) return;
+        if (rank == 0 && threadIdx.x == 0 && k0 == 0) ctl->t_begin = wall_clock64();
+        // a call that continues a carve (step mode) starts from the barrier count the previous
+        // calls left behind, so a team's barrier counter never has to be reset between launches
+        unsigned epoch = max_seams > 0 ? __hip_atomic_load(&ctl->ebase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        int kd = k0;  // seams removed in total when this call ends
+        if (G > 1) {
+            // every member records its XCD; a team spread over several XCDs would not see each
+            // other's stores through sc1 loads, so such an image is flagged instead of carved
+            if (threadIdx.x == 0) __hip_atomic_fetch_or(&ctl->xmask, 1u << (xcc_id() & 31), __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT);
+            if (!team_sync<true>(gd, epoch, G, &sm.flag)) return;
+            const unsigned m = __hip_atomic_load(&ctl->xmask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__popc(m) != 1) {
+                if (threadIdx.x == 0)
+                    __hip_atomic_fetch_or(gp(d.status), kStatusPlacement, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            kd = carve_seams<true, MAP>(gd, rank, G, sm, k0, k1, epoch, deadline);
+        } else {
+            kd = carve_seams<false, MAP>(gd, rank, G, sm, k0, k1, epoch, deadline);
+        }
+        __syncthreads();
+        if (rank == 0 && threadIdx.x == 0) {
+            ctl->done = (unsigned)kd;
+            if (kd == nseams) ctl->t_end = wall_clock64();
+            if (max_seams > 0) {  // every member ended this call at the same barrier count
+                ctl->ebase = epoch;
+                ctl->xmask = 0;
+                ctl->stop = 0;
+            }
+        }
+    }
+};
+
+}  // namespace sc

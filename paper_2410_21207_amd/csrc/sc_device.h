@@ -19,6 +19,23 @@ __device__ __forceinline__ GAS T* gp(T* p) {
     return (GAS T*)p;
 }
 
+// A descriptor in constant memory (a kernel argument, or a table an earlier launch wrote).  fetch()
+// reads it anew through scalar loads: each stage of a long loop takes its own copy, so that the
+// compiler does not keep every stage's buffer descriptors and strides alive in scalar registers
+// through all the others (hundreds of them, spilled to vector registers otherwise).
+#ifdef __HIP_DEVICE_COMPILE__
+#define CAS __attribute__((address_space(4)))
+#else
+#define CAS  // the host pass only parses the kernels
+#endif
+template <class T>
+__device__ __forceinline__ T fetch(const CAS T* p) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+s"(p));
+#endif
+    return *p;
+}
+
 // Load of data that another workgroup of the same team may have written since this CU last read
 // it.  A relaxed device-scope atomic load is a plain load with the sc1 cache bit: it skips the
 // CU's L1 and reads the XCD's L2, where the other workgroup's stores have landed (a team always
@@ -57,6 +74,13 @@ __device__ __forceinline__ uint8_t buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t vo
     return __builtin_amdgcn_raw_buffer_load_b8(r, (int)voff, 0, COH ? 16 : 0);
 }
 
+// A 16-byte store, with no scalar offset: with one, the compiler may overwrite the data registers in
+// the very next instruction, and stores on gfx950 have been seen to take the new value (the first
+// dword of a lane's 16 bytes), where without one it keeps the registers for the cycles they need.
+__device__ __forceinline__ void buf_st128(__amdgpu_buffer_rsrc_t r, v4u v, uint32_t voff) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)voff, 0, 0);
+}
+
 __device__ __forceinline__ uint32_t xcc_id() {
     uint32_t v;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
@@ -73,117 +97,115 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_seq(f, std::make_integer_sequence<int, N>{});
 }
 
-// One segment of a one-pixel shift inside a row, as 16-byte destination slots aligned to absolute
-// addresses.  Left (R = false): destination [lo, hi) takes the bytes sh above it.  Right (R =
-// true): destination [lo + sh, hi + sh) takes the bytes of [lo, hi).  A slot's output needs its
-// own 16 bytes and one dword beyond it (above for left, below for right) that belongs to the
-// neighbouring slot; slots are numbered so that pass order visits that neighbour in the same
-// pass or a later one (left: ascending addresses, right: descending), and a pass loads before it
-// stores, so the update is hazard free.
+// One-pixel shifts inside rows, in place, one wave.  Row i of a plane closes the gap of its seam
+// pixel s: the pixels right of it move one column left (right = false), or the pixels left of it one
+// column right (right = true; the row then starts one column later).  A row's pixels start at column
+// o of the plane and w of them are in use.
 //
-// The row must start on a 16-byte boundary and belong to the calling wave alone while it runs:
-// a slot at either end of the destination is then written whole, with the bytes outside the
-// destination put back as loaded.
-struct SSeg {
-    uint8_t* base;  // 16-byte aligned
-    int q0, q1;     // destination bytes [base + q0, base + q1)
-    int sh;         // shift in bytes, 1..4
-    int n;          // slots
+// The work is 16-byte slots at aligned offsets, numbered from the seam outward; a lane loads a slot's
+// new bytes with one unaligned 16-byte load (the slot moved by one pixel) and stores it aligned.  Only
+// the seam's own slot (slot 0, lane 0) keeps bytes of the row: those on the other side of the gap.
+// At the far end the last slot may run over bytes that are not in use (past the row's last pixel, or
+// before its first one), never past the row's pitch.  A pass reads one pixel beyond its slots, into
+// the next pass's, so passes go outward and every load of a pass comes before its stores.
+//
+// What bounds it: memory latency.  NR rows of NP planes are one item, and the next item's loads go
+// out before this item's stores, so a wait for loads never covers a store (one counter for both,
+// drained in order); nothing branches between them, or the counter's state would be lost.
+struct ShiftPlane {
+    __amdgpu_buffer_rsrc_t r;  // from 16 bytes below the first row to 64 past the last
+    uint32_t pitch;            // bytes per row, a multiple of 16
+    int px;                    // bytes per pixel, 1..4
 };
 
-template <bool R>
-__device__ __forceinline__ SSeg sseg(uint8_t* lo, uint8_t* hi, int sh) {
-    SSeg g;
-    uint8_t* dlo = R ? lo + sh : lo;
-    const int off = (int)((uintptr_t)dlo & 15);
-    g.base = dlo - off;
-    g.q0 = off;
-    g.q1 = hi > lo ? off + (int)(hi - lo) : off;
-    g.sh = sh;
-    g.n = g.q1 > g.q0 ? ((g.q1 - 1) >> 4) + 1 : 0;
-    return g;
+// n rows (at most 64) of a plane; there are 16 bytes of the workspace below them and 64 above.
+__device__ __forceinline__ ShiftPlane shift_plane(void* row0, int n, uint32_t pitch, int px) {
+    return {make_rsrc(static_cast<uint8_t*>(row0) - 16, 16u + (uint32_t)n * pitch + 64u), pitch, px};
 }
 
-// W[u] holds 20 loaded bytes: left = the slot then the dword above, right = the dword below then
-// the slot.  The accesses are buffer loads and stores through a descriptor starting 16 bytes below
-// the segment's first slot, so every offset is non-negative; a lane without a slot, or without a
-// neighbour dword to read, gets a dropped offset (its load returns 0, its store writes nothing).
-// With no branches around them, all loads of a pass go out before the first wait.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t sseg_rsrc(const SSeg& g) {
-    return make_rsrc(g.base - 16, (uint32_t)(g.n + 2) * 16u);
+struct ShiftSlot {
+    v4u v, own;        // the moved bytes; the bytes in place (slot 0)
+    uint32_t vo;       // the store's offset
+    uint64_t k0, k1;   // the bytes slot 0 keeps
+};
+
+__device__ __forceinline__ int shift_load(ShiftSlot& q, const ShiftPlane& p, bool live, int row, int s, int o, int w,
+                                          bool right, int fb, int lane) {
+    const int lo = (right ? o + 1 : o + s) * p.px, hi = (right ? o + s + 1 : o + w - 1) * p.px;
+    const int first = (right ? hi - 1 : lo) & ~15;
+    const int span = right ? first - (lo & ~15) : ((hi - 1) & ~15) - first;
+    const int n = live && hi > lo ? (span >> 4) + 1 : 0;
+    const int f = fb + lane;
+    const uint32_t at = (uint32_t)row * p.pitch + (uint32_t)(16 + first + (right ? -16 : 16) * f);
+    q.vo = f < n ? at : kBufDrop;
+    q.v = __builtin_amdgcn_raw_buffer_load_b128(p.r, (int)(f < n ? at + (uint32_t)(right ? -p.px : p.px) : kBufDrop),
+                                                0, 0);
+    q.own = __builtin_amdgcn_raw_buffer_load_b128(p.r, (int)(f == 0 && n > 0 ? at : kBufDrop), 0, 0);
+    // kept: the first c bytes of the slot, or (right) all but the first c
+    const int c = right ? ((hi - 1) & 15) + 1 : lo & 15;
+    const uint64_t m0 = c >= 8 ? ~0ull : (1ull << (8 * c)) - 1, m1 = c >= 16 ? ~0ull : c > 8 ? (1ull << (8 * c - 64)) - 1 : 0;
+    q.k0 = right ? ~m0 : m0;
+    q.k1 = right ? ~m1 : m1;
+    return n;
 }
 
-template <int U, bool R>
-__device__ __forceinline__ void sseg_load(const SSeg& g, int fb, int lane, uint32_t (&W)[U][5]) {
-    const __amdgpu_buffer_rsrc_t r = sseg_rsrc(g);
+__device__ __forceinline__ void shift_store(const ShiftSlot& q, const ShiftPlane& p, int fb, int lane) {
+    const bool z = fb + lane == 0;
+    const uint32_t k[4] = {(uint32_t)q.k0, (uint32_t)(q.k0 >> 32), (uint32_t)q.k1, (uint32_t)(q.k1 >> 32)};
+    v4u o;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int f = fb + u * 64 + lane;
-        const bool in = f < g.n;
-        const int so = (R ? g.n - 1 - f : f) << 4;
-        const v4u v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(in ? (uint32_t)so + 16u : kBufDrop), 0, 0);
-        constexpr int k = R ? 1 : 0;
-        W[u][k + 0] = v[0]; W[u][k + 1] = v[1];
-        W[u][k + 2] = v[2]; W[u][k + 3] = v[3];
-        if (R) {
-            const bool nb = in && so > g.q0 - g.sh;
-            W[u][0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(nb ? (uint32_t)so + 12u : kBufDrop), 0, 0);
-        } else {
-            const bool nb = in && so + 16 - g.sh < g.q1;
-            W[u][4] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(nb ? (uint32_t)so + 32u : kBufDrop), 0, 0);
-        }
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t m = z ? k[i] : 0u;
+        o[i] = (q.own[i] & m) | (q.v[i] & ~m);
     }
+    buf_st128(p.r, o, q.vo);
 }
 
-template <int U, bool R>
-__device__ __forceinline__ void sseg_store(const SSeg& g, int fb, int lane, const uint32_t (&W)[U][5]) {
-    const __amdgpu_buffer_rsrc_t r = sseg_rsrc(g);
-    const int a = R ? 4 - g.sh : g.sh;  // byte offset of the output inside the 20 bytes
+// The n rows of the planes; lane l holds row l's seam s, start o and side.
+template <int NR, int NP>
+__device__ __forceinline__ void shift_rows(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int lane) {
+    const int rt = right;
+    auto load = [&](ShiftSlot (&b)[NR][NP], int i, int fb) {
+        int most = 0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int f = fb + u * 64 + lane;
-        const int so = (R ? g.n - 1 - f : f) << 4;
-        uint32_t o[4];
-        if (a == 4) {
-            o[0] = W[u][1]; o[1] = W[u][2]; o[2] = W[u][3]; o[3] = W[u][4];
-        } else {
+        for (int a = 0; a < NR; ++a) {
+            const int li = min(i + a, n - 1);
+            const int si = __builtin_amdgcn_readlane(s, li), oi = __builtin_amdgcn_readlane(o, li);
+            const bool ri = __builtin_amdgcn_readlane(rt, li) != 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(W[u][i + 1], W[u][i], (uint32_t)a);
+            for (int x = 0; x < NP; ++x)
+                most = max(most, shift_load(b[a][x], p[x], i + a < n, li, si, oi, w, ri, fb, lane));
         }
-        if (so < g.q0 || so + 16 > g.q1) {
-            // an end slot: bytes outside the destination keep the values the pass loaded
-            const int c0 = min(max(g.q0 - so, 0), 16), c1 = min(max(g.q1 - so, 0), 16);
-            const uint32_t m16 = ((1u << c1) - 1u) & ~((1u << c0) - 1u);  // bit k = byte k of the slot
+        return most;
+    };
+    auto store = [&](const ShiftSlot (&b)[NR][NP], int fb) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t bm = ((((m16 >> (4 * i)) & 15u) * 0x00204081u) & 0x01010101u) * 0xffu;
-                const uint32_t cur = R ? W[u][i + 1] : W[u][i];
-                o[i] = (o[i] & bm) | (cur & ~bm);
-            }
-        }
-        const v4u ov = {o[0], o[1], o[2], o[3]};
-        __builtin_amdgcn_raw_buffer_store_b128(ov, r, (int)(f < g.n ? (uint32_t)so + 16u : kBufDrop), 0, 0);
-    }
-}
-
-// Two rows' shifts (image and energy segments of row a, then of row b, directions RA and RB)
-// moved together: every pass issues the loads of all four segments before any store, so the
-// rows share each memory round trip.  The segments must not overlap each other's bytes.
-template <int U, bool RA, bool RB>
-__device__ __forceinline__ void shift_rows2_wave(const SSeg& a0, const SSeg& a1, const SSeg& b0, const SSeg& b1,
-                                                 int lane) {
-    const int n = max(max(a0.n, a1.n), max(b0.n, b1.n));
-#pragma unroll 1
-    for (int fb = 0; fb < n; fb += 64 * U) {
-        uint32_t W0[U][5], W1[U][5], W2[U][5], W3[U][5];
-        sseg_load<U, RA>(a0, fb, lane, W0);
-        sseg_load<U, RA>(a1, fb, lane, W1);
-        sseg_load<U, RB>(b0, fb, lane, W2);
-        sseg_load<U, RB>(b1, fb, lane, W3);
-        sseg_store<U, RA>(a0, fb, lane, W0);
-        sseg_store<U, RA>(a1, fb, lane, W1);
-        sseg_store<U, RB>(b0, fb, lane, W2);
-        sseg_store<U, RB>(b1, fb, lane, W3);
+        for (int a = 0; a < NR; ++a)
+#pragma unroll
+            for (int x = 0; x < NP; ++x) shift_store(b[a][x], p[x], fb, lane);
+    };
+    int i = 0, fb = 0;
+    auto step = [&](int most) {  // the next pass of these rows, or the next rows
+        const bool again = fb + 64 < most;
+        i = again ? i : i + NR;
+        fb = again ? fb + 64 : 0;
+    };
+    ShiftSlot A[NR][NP], B[NR][NP];
+    int fa = 0, fbb;
+    step(load(A, i, fb));
+    for (;;) {
+        fbb = fb;
+        const bool mb = i < n;
+        const int nb = load(B, i, fb);
+        step(nb);
+        store(A, fa);
+        if (!mb) break;
+        fa = fb;
+        const bool ma = i < n;
+        const int na = load(A, i, fb);
+        step(na);
+        store(B, fbb);
+        if (!ma) break;
     }
 }
 
@@ -295,7 +317,7 @@ struct PixRow {
 // G have arrived; readers then fetch shared data with sc1 loads (see ld<true>).  The wait is
 // bounded: after ~10 s it flags the image and every member gives up on it.
 template <bool TEAM>
-__device__ __forceinline__ bool team_sync(const Img& d, unsigned& epoch, int G, int* flag) {
+__device__ __forceinline__ bool team_sync(const CAS Img* gd, unsigned& epoch, int G, int* flag) {
     if constexpr (!TEAM) {
         __syncthreads();
         return true;
@@ -303,6 +325,7 @@ __device__ __forceinline__ bool team_sync(const Img& d, unsigned& epoch, int G, 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) {
+            const Img d = fetch(gd);
             epoch += (unsigned)G;
             __hip_atomic_fetch_add(gp(d.bar), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const unsigned long long t0 = wall_clock64();

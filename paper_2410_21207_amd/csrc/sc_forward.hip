@@ -103,7 +103,7 @@ struct Carver {
     // abandons it.
     static __device__ __forceinline__ void dp(const Img& d, Smem& sm, int rank, int gd, int w, int k, int P,
                                               unsigned long long* amin) {
-        const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+        const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
         const int H = d.H;
         const Cols cl = member_cols(rank, gd);
         const int j0 = cl.base + CORE * wv + CPL * lane;  // the lane's first column
@@ -327,8 +327,9 @@ struct Carver {
     }
 
     // The seams of one image by team member `rank` of G.
-    static __device__ __forceinline__ void carve(const Img& d, Smem& sm, int rank, int G) {
-        const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    static __device__ __forceinline__ void carve(const CAS Img* pd, Smem& sm, int rank, int G) {
+        const Img d = fetch(pd);
+        const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
         const int H = d.H, nseams = d.W - d.target_w, P = (H + K - 1) / K;
         const int gd = dp_members(d.W);
         GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.amin));
@@ -338,7 +339,7 @@ struct Carver {
             // every member records its XCD: a team must share one L2
             if (t == 0)
                 __hip_atomic_fetch_or(&ctl->xmask, 1u << (xcc_id() & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (!team_sync<true>(d, epoch, G, &sm.flag)) return;
+            if (!team_sync<true>(pd, epoch, G, &sm.flag)) return;
             const unsigned m = __hip_atomic_load(&ctl->xmask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (__popc(m) != 1) {
                 if (t == 0)
@@ -365,7 +366,7 @@ struct Carver {
             // double-buffered row the other has not read yet.
             if (rank < gd && (gd == 1 || rank * S < w)) dp(d, sm, rank, gd, w, k, P, amin);
             if (G > 1) {
-                if (!team_sync<true>(d, epoch, G, &sm.flag)) return;
+                if (!team_sync<true>(pd, epoch, G, &sm.flag)) return;
             } else {
                 __syncthreads();
             }
@@ -481,38 +482,20 @@ struct Carver {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                // removal: in each row the pixels right of the seam move one column left, four
-                // rows per memory round trip
-#pragma unroll 1
-                for (int i = ia; i < ib; i += 4) {
-                    auto seg = [&](int q) {
-                        SSeg g;
-                        if (i + q >= ib) {
-                            g.base = d.wk;
-                            g.q0 = g.q1 = g.sh = g.n = 0;
-                            return g;
-                        }
-                        const int si = min(max(__builtin_amdgcn_readlane(mys, i + q), 0), w - 1);
-                        uint8_t* r = d.wk + (long long)(r0 + i + q) * d.wp;
-                        // columns si+1 .. w move left, the copy of the last pixel at w included,
-                        // so column w-1 then holds a copy of the new last pixel
-                        return sseg<false>(r + (long long)si * 4, r + (long long)w * 4, 4);
-                    };
-                    shift_rows2_wave<2, false, false>(seg(0), seg(1), seg(2), seg(3), lane);
-                    // a seam at the last column removed the pixel the copy repeated: the new last
-                    // pixel (w-2) is copied to w-1 (after the shift's store to it, same wave)
-                    const int sq = __shfl(mys, min(i + lane, 63), 64);  // row i + lane's seam, in lanes 0..3
-                    if (lane < 4 && i + lane < ib && w >= 2) {
-                        const int si = min(max(sq, 0), w - 1);
-                        if (si == w - 1) {
-                            uint32_t* r = reinterpret_cast<uint32_t*>(d.wk + (long long)(r0 + i + lane) * d.wp);
-                            *gp(r + w - 1) = *gp(r + w - 2);
-                        }
-                    }
+                // removal: in each row columns si+1 .. w move left, the copy of the last pixel at w
+                // included, so column w-1 then holds a copy of the new last pixel
+                const ShiftPlane planes[1] = {shift_plane(d.wk + (size_t)(r0 + ia) * d.wp, ib - ia, (uint32_t)d.wp, 4)};
+                const int sl = min(max(__shfl(mys, min(ia + lane, 63), 64), 0), w - 1);  // row ia + lane
+                shift_rows<4, 1>(planes, ib - ia, w + 1, sl, 0, false, lane);
+                // a seam at the last column removed the pixel the copy repeated: the new last pixel
+                // (w-2) is copied to w-1 (after the shift's store to it, same wave)
+                if (lane < ib - ia && w >= 2 && sl == w - 1) {
+                    uint32_t* r = reinterpret_cast<uint32_t*>(d.wk + (long long)(r0 + ia + lane) * d.wp);
+                    *gp(r + w - 1) = *gp(r + w - 2);
                 }
             }
             if (G > 1) {
-                if (!team_sync<true>(d, epoch, G, &sm.flag)) return;
+                if (!team_sync<true>(pd, epoch, G, &sm.flag)) return;
             } else {
                 __syncthreads();
             }
@@ -541,7 +524,7 @@ struct Carver {
             }
         }
         if (G > 1) {
-            team_sync<true>(d, epoch, G, &sm.flag);
+            team_sync<true>(pd, epoch, G, &sm.flag);
         } else {
             __syncthreads();
         }
@@ -567,9 +550,9 @@ __global__ __launch_bounds__(fwt::NT, 3) void fwt_carve_kernel(const Img* __rest
         me = make_int2(0, (int)(blockIdx.x >> 3));
     }
     if (me.x < 0) return;
-    const Img d = imgs[me.x];
-    if (me.y >= d.G) return;
-    fwt::Carver::carve(d, sm, me.y, d.G);
+    const CAS Img* pd = (const CAS Img*)(imgs + me.x);
+    if (me.y >= pd->G) return;
+    fwt::Carver::carve(pd, sm, me.y, pd->G);
 }
 
 // Copy-in for the forward carve: every pixel of src (or img) as one dword of wk (channels in the

@@ -17,19 +17,22 @@ struct Img {
     long long* costs_out;  // optional, W-target_w
     // workspace pieces
     uint16_t* e;   // energy plane, H rows of `ep` uint16
-    uint8_t* dirs; // parent directions, 2 bits per cell, H rows of `db` bytes
-    int8_t* anc;   // per DP phase, the ancestor offset of every column at the phase's last row
-    uint32_t* xq;  // 2 rows of `xw` uint32: DP keys exchanged between waves at phase ends
+    uint8_t* dirs; // forward energy: parent directions, 2 bits per cell, H rows of `db` bytes
+    int8_t* anc;   // the ancestor offset of every column at the last row of a block (`xw` bytes per row)
+                   // or, forward energy, of a DP phase
+    uint32_t* xq;  // published DP keys: P rows of `xw` uint32, the last row of every block; or, forward
+                   // energy, 2 rows exchanged between members at phase ends
     int32_t* seam; // current seam, H
     int32_t* ro;   // per row: physical column of the row's first pixel (min-side removal), H
     uint8_t* wk;   // working copy of the image, H rows of `wp` bytes (64-byte aligned rows)
     unsigned long long* amin;  // packed (cost << 32 | column) argmin of the current seam
     unsigned* bar;             // team barrier counter
     unsigned* status;          // error bits
-    int ep, db, xw, P;         // pitches and the number of DP phases
+    int ep, db, xw, P;         // pitches; rows of published keys (forward energy: DP phases)
     int wp;                    // bytes per row of wk
     int G;                     // team size (workgroups) carving this image
-    int mode;                  // 0 = carve, 1 = one seam only, no removal (sc_dp_seam)
+    int mode;                  // 0 = carve, 1 = one seam only, no removal (sc_dp_seam), 2 = the same
+                               // and the direction of every cell as a byte in img (H x W)
     int minside;               // 1 = remove a seam pixel by moving the shorter side of its row
     unsigned long long* amk;   // forward teams: the argmin words of even and odd seams
 };
@@ -54,8 +57,8 @@ constexpr unsigned kStatusPlacement = 2u;  // a team's workgroups were not on on
 
 // Placement of one image's scratch inside a workspace.
 struct Layout {
-    size_t ctl, e, dirs, anc, xq, seam, ro, wk, total;
-    int ep, db, xw, P, wp;
+    size_t ctl, e, scratch, seam, ro, wk, total;
+    int ep, wp;
 };
 
 constexpr size_t kAlign = 256;
@@ -68,7 +71,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // threads) for every compiled variant of the carve kernel; the launchers switch over the same list.
 #define SC_VARIANTS(X)                                                                                      \
     X(0, 4, 32, 256) X(1, 4, 32, 512) X(2, 4, 32, 1024) X(3, 8, 32, 512) X(4, 8, 32, 1024) X(5, 4, 48, 512) \
-    X(6, 4, 48, 256) X(7, 4, 56, 512) X(8, 4, 56, 256) X(9, 2, 48, 512)
+    X(6, 4, 48, 256) X(7, 4, 64, 512) X(8, 4, 64, 256) X(9, 2, 48, 512)
 
 struct Variant {
     int cpl, kr, threads;
@@ -79,10 +82,29 @@ inline constexpr Variant kVariants[] = {SC_VARIANTS(SC_VARIANT_ROW)};
 #undef SC_VARIANT_ROW
 inline int variant_count() { return (int)(sizeof(kVariants) / sizeof(kVariants[0])); }
 inline const Variant& variant(int v) { return kVariants[v]; }
-inline int default_variant() { return 7; }  // cpl4_k56_t512
+inline int default_variant() { return 7; }  // cpl4_k64_t512
 
-Layout layout_for(int H, int W, int C, int variant_kr_min);
-constexpr int kLdsExchangeMaxW = 4096;  // single-workgroup carves keep the phase exchange row in LDS up to this width
+Layout layout_for(int H, int W, int C);
+
+constexpr int kMaxRows = 16448;  // rows of the tallest image (one channel; the 23-bit cost limit)
+
+// Rows of a backtrack block of a variant with kr-row phases: whole blocks make up a phase, and a
+// block's ancestor offset fits 7 bits.
+__host__ __device__ constexpr int block_rows(int kr) { return kr % 32 == 0 ? 32 : kr / 2; }
+// The cost sweep runs down over rows [0, split_row) and up over the rest; with the direction map
+// (mode 2: the parent of every cell) it runs down over all of them.  A multiple of 4 or H.
+__host__ __device__ constexpr int split_row(int H, int mode) {
+    const int m = mode == 2 ? H : ((H + 1) / 2 + 3) & ~3;
+    return m < H ? m : H;
+}
+// Blocks of both halves: the rows of published keys.
+__host__ __device__ constexpr int key_rows(int H, int kr, int mode) {
+    const int m = split_row(H, mode), r = block_rows(kr);
+    return (m + r - 1) / r + (H - m + r - 1) / r;
+}
+// Dwords of a row of published keys (bytes of a row of ancestor offsets): a lane's columns may run
+// three past the image's last one.
+__host__ __device__ constexpr int key_pitch(int W) { return (W + 7) & ~3; }
 
 // Launchers (sc_kernels.hip).  Return hipSuccess or the launch error.
 hipError_t launch_energy_i32(const uint8_t* img, int H, int W, int C, long long pitch, int32_t* out,
@@ -93,7 +115,6 @@ hipError_t launch_carve_single(const Img& d, int variant, int G, int xcd, hipStr
 hipError_t launch_carve_steps(const Img* table, int n, int variant, int max_seams, unsigned long long budget_ticks,
                               int* progress, const int4* plan, int nblocks, hipStream_t st);
 hipError_t launch_slot_write(Img* table, int slot, const Img& d, hipStream_t st);
-hipError_t launch_unpack_dirs(const Img& d, uint8_t* out, hipStream_t st);
 hipError_t launch_remove_seam(uint8_t* img, int H, int W, int C, long long pitch, const int32_t* seam,
                               hipStream_t st);
 hipError_t launch_transpose(const uint8_t* src, int H, int W, int C, long long sp, uint8_t* dst, long long dp,

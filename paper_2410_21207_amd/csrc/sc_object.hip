@@ -67,7 +67,7 @@ struct Carver : PixRow<C, CPL> {
     }
 
     static __device__ __forceinline__ void carve(const ObjImg& d, Smem& sm, uint8_t* anc_lds) {
-        const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+        const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
         const int H = d.H, W = d.W, j0 = t * CPL;
         GAS ObjCtl* ctl = gp(d.ctl);
         if (t == 0) ctl->t_begin = wall_clock64();
@@ -311,29 +311,17 @@ struct Carver : PixRow<C, CPL> {
             __syncthreads();
             const unsigned long long tm2 = t == 0 ? wall_clock64() : 0ull;
             // ---- removal: in each seam row the pixels and the mask bytes right of the seam move one
-            // column left; two rows (pixel and mask segments of each) per memory round trip, the
-            // 2-row groups dealt to the waves round-robin
+            // column left, an equal range of rows per wave
+            {
+                const int rpw = (H + NW - 1) / NW, ra = min(H, wv * rpw), rb = min(H, ra + rpw);
 #pragma unroll 1
-            for (int r0 = wv * 2; r0 < H; r0 += NW * 2) {
-                const int n = min(2, H - r0);
-                const int sv = lane < n ? *gp(d.seam + r0 + lane) : 0;
-                auto segs = [&](int i, SSeg& gi, SSeg& gm) {
-                    if (i >= n) {
-                        gi.base = gm.base = d.wk;
-                        gi.q0 = gi.q1 = gi.sh = gi.n = 0;
-                        gm.q0 = gm.q1 = gm.sh = gm.n = 0;
-                        return;
-                    }
-                    const int si = min(max(__builtin_amdgcn_readlane(sv, i), 0), w - 1);
-                    uint8_t* r = d.wk + (long long)(r0 + i) * d.wp;
-                    uint8_t* mr = d.mk + (long long)(r0 + i) * d.mp;
-                    gi = sseg<false>(r + (long long)si * C, r + (long long)(w - 1) * C, C);
-                    gm = sseg<false>(mr + si, mr + (w - 1), 1);
-                };
-                SSeg a0, a1, b0, b1;
-                segs(0, a0, a1);
-                segs(1, b0, b1);
-                shift_rows2_wave<1, false, false>(a0, a1, b0, b1, lane);
+                for (int r = ra; r < rb; r += 64) {
+                    const int n = min(64, rb - r);
+                    const int si = lane < n ? min(max(*gp(d.seam + r + lane), 0), w - 1) : 0;
+                    const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)r * d.wp, n, (uint32_t)d.wp, C),
+                                                  shift_plane(d.mk + (size_t)r * d.mp, n, (uint32_t)d.mp, 1)};
+                    shift_rows<2, 2>(planes, n, w, si, 0, false, lane);
+                }
             }
             __syncthreads();
             if (t == 0) {  // device clock per stage: DP sweep; argmin + backtrack; removal
