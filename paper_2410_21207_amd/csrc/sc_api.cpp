@@ -108,24 +108,24 @@ namespace sc {
 Layout layout_for(int H, int W, int C) {
     Layout L;
     L.ep = (int)align_up((size_t)W + 8, 64);
-    size_t off = 0;
+    size_t off = 64;  // the row shifter may write up to 16 bytes below a plane
     L.ctl = 0;
     L.e = off;
-    off = align_up(off + (size_t)H * L.ep * 2, kAlign);
-    // the backtrack's scratch: ancestor offsets and published keys, 5 * key_rows * key_pitch bytes at
-    // most (the largest for 24-row blocks).  The size is that of the 2-bit direction map, the 32-row
-    // phases' offsets and the two exchange rows the carve once kept here: no workspace has grown.
+    off = align_up(off + (size_t)(H + 1) * L.ep * 2, kAlign);  // and a row of zeros
+    // the backtrack's scratch: ancestor offsets and published keys, 5 * key_rows * key_pitch bytes
     L.scratch = off;
-    off = align_up(off + (size_t)align_up((size_t)H, 4) * align_up((size_t)(W + 3) / 4 + 4, 16), kAlign);
-    off = align_up(off + (size_t)((H + 31) / 32) * W, kAlign);
-    off = align_up(off + (size_t)2 * align_up((size_t)W + 16, 64) * 4, kAlign);
+    const size_t rows = std::max(key_rows(H, 48, 0), key_rows(H, 48, 2));  // of 24, the smallest blocks
+    off = align_up(off + rows * key_pitch(W), kAlign);
+    off = align_up(off + rows * key_pitch(W) * 4, kAlign);
     L.seam = off;
     off = align_up(off + (size_t)H * 4, kAlign);
     L.ro = off;
     off = align_up(off + (size_t)H * 4, kAlign);
-    // working image: 64-byte aligned rows, so a 16-byte slot never spans two rows
-    L.wp = (int)align_up((size_t)W * C, 64);
-    L.wk = off;
+    // working image: 16 bytes between rows and below the first one (the row shifter's last slot may
+    // run over a row's end)
+    L.wp = (int)align_up((size_t)W * C + 16, 16);
+    L.wk = off + 64;
+    off += 64;
     off = align_up(off + (size_t)H * L.wp, kAlign);
     L.total = off + kAlign;  // slack: row copies read a few bytes past the last row
     return L;
@@ -735,7 +735,7 @@ FwdLayout fwd_layout(int H, int W, int C) {
     FwdLayout L;
     L.P = (H + sc::kFwtPhaseRows - 1) / sc::kFwtPhaseRows;
     L.db = (int)sc::align_up((size_t)(W + 3) / 4, 16);  // direction bytes (4 columns each) per row
-    L.wp = (int)sc::align_up((size_t)(W + 1) * 4, 64);   // one dword per pixel, and a copy of the last
+    L.wp = (int)sc::align_up((size_t)(W + 1) * 4 + 16, 16);  // one dword per pixel, a copy of the last, a gap
     L.xw = (int)sc::align_up((size_t)W + 8, 64);
     size_t off = 0;
     L.dirs = off;
@@ -997,8 +997,8 @@ struct ObjLayout {
 ObjLayout obj_layout(int h, int w0, int C, bool restore) {
     ObjLayout L;
     const int P = (h + sc::kFwdPhaseRows - 1) / sc::kFwdPhaseRows;
-    L.wp = (int)sc::align_up((size_t)w0 * C, 64);
-    L.mp = (int)sc::align_up((size_t)w0, 64);
+    L.wp = (int)sc::align_up((size_t)w0 * C + 16, 64);  // 16 bytes between rows: the row shifter's last slot
+    L.mp = (int)sc::align_up((size_t)w0 + 16, 64);
     L.db = (int)sc::align_up((size_t)(w0 + 3) / 4, 16);
     size_t off = 0;
     L.ctl = off;

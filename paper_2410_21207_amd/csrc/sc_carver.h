@@ -35,7 +35,7 @@ namespace sc {
 
 constexpr uint32_t QINF = 0xFFFFFF00u;  // "+infinity" key: larger than any real key, +10 cannot wrap
 
-// r + 512 * (low or high 16 bits of `pair`): one v_mad_u32_u16 adds e(i,j) << 9 to a DP key
+// r + 512 * (low or high 16 bits of `pair`): one v_mad_u32_u16 adds e(i,j) << 9 to a backtrack key
 // straight from the packed uint16 energy pair, with no separate unpack.
 __device__ __forceinline__ uint32_t mad_lo16(uint32_t pair, uint32_t r) {
     uint32_t o;
@@ -73,57 +73,61 @@ __device__ __forceinline__ uint32_t energy_buf(__amdgpu_buffer_rsrc_t rb, uint32
 }
 
 // ----------------------------------------------------------------------------------------------
-// The carve engine: one image, carved by a team of G workgroups of NT threads.
-template <int CPL, int KR, int NT>
-struct Carver {
-    static constexpr int WIN = 64 * CPL;    // columns a wave computes in the DP
-    static constexpr int S = WIN - 2 * KR;  // columns a strip adds: KR ghost columns on each side
-    static constexpr int NW = NT / 64;      // waves per workgroup
-    static constexpr int PF = 8;            // rows of energy prefetched ahead
-    static constexpr int R = block_rows(KR);  // rows of a backtrack block
-    static constexpr int BCPL = 4;            // columns per lane of a backtrack window
-    static constexpr int BW = 64 * BCPL;      // columns of a backtrack window
-    static constexpr int BS = BW - 2 * R;     // of which exact at the block's last row
-    static constexpr int NG = R / 4;          // 4-row direction groups of a block
-    static constexpr int BMAX = (kMaxRows / 2 + 4) / R + 2;  // blocks of half the tallest image
-    static constexpr int CH = 252 / R + 1;    // hops per memory round trip: h * R + 3 < 256 for h < CH
-    static_assert(CPL == 2 || CPL == 4 || CPL == 8, "one energy load per lane and row");
-    static_assert(KR % R == 0 && R % PF == 0 && KR <= 64 && R <= 63 && KR % CPL == 0 && S > 0, "phase shape");
-
-    struct Smem {
-        int jend[2 * BMAX];            // seam column at the last row of block b of half h at [h * BMAX + b]
-        int2 pos[2];                   // per half: the block the backtrack has reached (-1: done), its column
-        uint32_t cw[2][CH * 128];      // windows of ancestor offsets, 512 bytes per hop
-        unsigned long long red[NW];
-        int flag;
-        int stop;                      // step mode: the time budget is spent
-    };
-
-    struct EV {
-        uint64_t v[(CPL + 3) / 4];  // CPL uint16 energies
-    };
-
-    // Energies at the lane's byte offset `off` of the row starting `soff` bytes into the plane
-    // (wave-uniform: row base plus the row's start offset).  COH sets the sc1 bit.
-    template <bool COH, int N>
-    static __device__ __forceinline__ void load_ev(uint64_t (&e)[(N + 3) / 4], __amdgpu_buffer_rsrc_t re, uint32_t soff,
-                                                   uint32_t off) {
-        if constexpr (N == 2) {
-            e[0] = __builtin_amdgcn_raw_buffer_load_b32(re, (int)off, (int)soff, COH ? 16 : 0);
-        } else if constexpr (N == 4) {
-            const v2u v = __builtin_amdgcn_raw_buffer_load_b64(re, (int)off, (int)soff, COH ? 16 : 0);
-            e[0] = ((uint64_t)v[1] << 32) | v[0];
-        } else {
-            const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, (int)off, (int)soff, COH ? 16 : 0);
-            e[0] = ((uint64_t)v[1] << 32) | v[0];
-            e[1] = ((uint64_t)v[3] << 32) | v[2];
-        }
+// Energies at the lane's byte offset `off` of the row starting `soff` bytes into the plane
+// (wave-uniform: row base plus the row's start offset).  COH sets the sc1 bit.
+template <bool COH, int N>
+__device__ __forceinline__ void load_ev(uint64_t (&e)[(N + 3) / 4], __amdgpu_buffer_rsrc_t re, uint32_t soff,
+                                               uint32_t off) {
+    if constexpr (N == 2) {
+        e[0] = __builtin_amdgcn_raw_buffer_load_b32(re, (int)off, (int)soff, COH ? 16 : 0);
+    } else if constexpr (N == 4) {
+        const v2u v = __builtin_amdgcn_raw_buffer_load_b64(re, (int)off, (int)soff, COH ? 16 : 0);
+        e[0] = ((uint64_t)v[1] << 32) | v[0];
+    } else {
+        const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, (int)off, (int)soff, COH ? 16 : 0);
+        e[0] = ((uint64_t)v[1] << 32) | v[0];
+        e[1] = ((uint64_t)v[3] << 32) | v[2];
     }
+}
 
+// One wait for the loads up to this one, in place of one at the first use of each.
+template <int N>
+__device__ __forceinline__ void arrived(const uint64_t (&e)[N]) {
+    asm volatile("" ::"v"(e[N - 1]));
+}
+
+// A team's waves wait for each other's data, not for each other: what a seam publishes carries its
+// tag, and a reader loads again until it shows.  Bounded: `late` says when to give up (10 s at the
+// 100 MHz constant clock, or at once when the image has failed) and flags the image.
+struct Wait {
+    unsigned long long t0 = 0;
+    int n = 0;
+    __device__ __forceinline__ bool late(const Img& d) {
+        __builtin_amdgcn_s_sleep(1);
+        if ((n++ & 63) != 63) return false;
+        const unsigned long long now = wall_clock64();
+        if (t0 == 0) t0 = now;
+        if (now - t0 <= 1000000000ull &&
+            !(__hip_atomic_load(gp(d.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+              (kStatusTimeout | kStatusPlacement)))
+            return false;
+        __hip_atomic_fetch_or(gp(d.status), kStatusTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+};
+
+// Tag of the keys a seam publishes: 1..511, never the 0 of a cleared row.  Every row of ck is
+// written once per seam, so a reader only has to tell a seam from the one before it.
+__device__ __forceinline__ uint32_t seam_tag(int k) { return 1u + (uint32_t)k % 511u; }
+// The same of a row's seam column (16 bits, columns below 65535), in the upper half of its word.
+__device__ __forceinline__ uint32_t seam_word(int k) { return ((uint32_t)k + 1u) << 16; }
+
+template <int R>
+struct Rows {
     // The rows of one half (h = 0: from the top down to the split row, 1: from the bottom up).
     // Virtual row v of a half is image row v - pad counted from the half's border; the rows below
-    // pad do not exist and carry zero energy, so that the half is a whole number of blocks and its
-    // first real row costs its own energy.
+    // pad do not exist and read the plane's row of zeros (row H), so that the half is a whole number
+    // of blocks and its first real row costs its own energy.
     struct Half {
         int n, B, pad;  // rows, blocks, missing rows
     };
@@ -136,37 +140,62 @@ struct Carver {
         return x;
     }
 
-    static __device__ __forceinline__ int strips(int w) { return w <= WIN ? 1 : (w - 2 * KR + S - 1) / S; }
-
     // Byte offset in the energy plane of virtual row v (its base plus its start offset) of half h,
-    // rows outside the half clamped to its ends.
+    // rows past the half clamped to its last one.
     template <bool COH>
     static __device__ __forceinline__ uint32_t row_off(const Img& d, const Half& x, int h, int v,
                                                        __amdgpu_buffer_rsrc_t rro) {
-        const int i = min(max(v - x.pad, 0), x.n - 1);
-        const int r = h ? d.H - 1 - i : i;
-        return (uint32_t)r * (uint32_t)d.ep * 2u + 2u * buf_ld32<COH>(rro, (uint32_t)r * 4u);
+        const int i = min(v - x.pad, x.n - 1);
+        const int r = i < 0 ? d.H : h ? d.H - 1 - i : i;
+        return (uint32_t)r * (uint32_t)d.ep * 2u + 2u * buf_ld32<COH>(rro, i < 0 ? kBufDrop : (uint32_t)r * 4u);
+    }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t energy_rsrc(const Img& d) {
+        return make_rsrc(d.e, (uint32_t)(d.H + 1) * (uint32_t)d.ep * 2u);
     }
 
-    // ---- the cost sweep (a3): keys M << 9 only, no directions.
-    //
-    // A seam's cost table is swept from both ends of the image at once, T from the top row down to
-    // the split row and B from the bottom row up, and the cheapest pair of adjacent cells in the two
-    // middle rows gives the seam's cost and its two middle columns.  The tie rules survive: among
-    // the cheapest seams the backtrack wants the smallest (s[H-1], ..., s[0]), paths chosen by
-    // "leftmost minimum" from neighbouring cells never cross, so in the lower half the leftmost
-    // child leads to the leftmost end, and the leftmost middle column to the leftmost path of all.
-    //
-    // What bounds it: a chain of rows, each one wave's instructions.  Without directions and
-    // ancestor offsets a row is a v_min3 and a v_mad per column and two wave shifts; the two ends
-    // halve the chain.
+};
+
+// ---- the cost sweep (a3): costs only, no directions; published as M << 9 | tag.
+//
+// A seam's cost table is swept from both ends of the image at once, T from the top row down to
+// the split row and B from the bottom row up, and the cheapest pair of adjacent cells in the two
+// middle rows gives the seam's cost and its two middle columns.  The tie rules survive: among
+// the cheapest seams the backtrack wants the smallest (s[H-1], ..., s[0]), paths chosen by
+// "leftmost minimum" from neighbouring cells never cross, so in the lower half the leftmost
+// child leads to the leftmost end, and the leftmost middle column to the leftmost path of all.
+//
+// What bounds it: a chain of rows, each one wave's instructions.  Without directions and
+// ancestor offsets a row is a v_min3 and an add per column and two wave shifts (15 instructions for
+// 256 columns), and the two ends halve the chain.  Rows are loaded a block ahead, one wait per eight
+// rows.  1920 x 1080 by 32 workgroups: 27 us per seam where the one-ended sweep with directions took 106.
+template <int CPL, int KR, int R>
+struct Sweep : Rows<R> {
+    using Half = typename Rows<R>::Half;
+    using Rows<R>::half_of;
+    using Rows<R>::energy_rsrc;
+    static constexpr int WIN = 64 * CPL;    // columns a wave computes
+    static constexpr int S = WIN - 2 * KR;  // columns a strip adds: KR ghost columns on each side
+    static constexpr int PF = R == 32 ? (CPL == 8 ? 16 : 32) : R;  // rows of energy prefetched ahead
+    static_assert(CPL == 2 || CPL == 4 || CPL == 8, "one energy load per lane and row");
+    static_assert(KR % R == 0 && R % PF == 0 && PF % 8 == 0 && KR <= 64 && R <= 63 && KR % CPL == 0 && S > 0, "phase shape");
+
+    // Eight columns per lane: rows are loaded from the dword at or below the lane's first energy and
+    // moved by half a dword where the row starts at an odd column (an access off the dword grid costs
+    // four times as much, and strips this wide run several to a compute unit).  A lane takes the dword
+    // after its own from the next lane; lane 63 has none, so it is ghost columns, or past the image:
+    // the last strip's window runs eight columns past w, and the first of them stays all ones.
+    static constexpr bool GRID = CPL == 8;
+    static constexpr int WINR = GRID ? WIN - CPL : WIN;  // columns of the last strip's window in the image
+
+    static __device__ __forceinline__ int strips(int w) { return w <= WINR ? 1 : (w - WINR + S - 1) / S + 1; }
+
     struct Item {
         int p, j;      // phase, the wave's item in it
         int h, t;      // half, strip
         int v0, v1;    // virtual rows
-        int drop;      // leading rows without energy (first phase)
         uint32_t off;  // byte offset of the lane's first column in an energy row
         int col0;      // the lane's first column
+        int base;      // the strip's first column
         int ns;
     };
     static __device__ __forceinline__ Item make_item(const Half (&hf)[2], int w, int ns, int tw, int TW, int p, int j,
@@ -175,45 +204,56 @@ struct Carver {
         it.p = p;
         it.j = j;
         it.ns = ns;
-        const int q = tw + j * TW;
+        const int q = __builtin_amdgcn_readfirstlane(tw + j * TW);
         const bool two = hf[1].n > 0;
         it.h = two ? q & 1 : 0;
         it.t = two ? q >> 1 : q;
         const Half x = it.h ? hf[1] : hf[0];
-        it.v0 = p ? p * KR : x.pad & ~(PF - 1);
+        it.v0 = p ? p * KR : x.pad - x.pad % PF;
         it.v1 = min(x.B * R, p * KR + KR);
-        it.drop = p ? 0 : x.pad & (PF - 1);
-        const int base = it.t == ns - 1 ? max(0, w - WIN) : it.t * S;
+        const int base = it.t == ns - 1 ? max(0, w - WINR) : it.t * S;
+        it.base = __builtin_amdgcn_readfirstlane(base);
+        it.v0 = __builtin_amdgcn_readfirstlane(it.v0);
+        it.v1 = __builtin_amdgcn_readfirstlane(it.v1);
         it.col0 = base + lane * CPL;
-        it.off = (uint32_t)(it.col0 < w ? it.col0 : 0) * 2u;
+        it.off = GRID ? (uint32_t)lane * (2u * CPL) : (uint32_t)(it.col0 < w ? it.col0 : 0) * 2u;
         return it;
     }
 
     // EDGE: the one strip of an image narrower than a window (columns from w on are kept all ones).
     template <bool EDGE>
     static __device__ __forceinline__ void cost_step(uint32_t (&Q)[CPL], uint32_t& left, uint32_t& right,
-                                                     const uint64_t (&ev)[(CPL + 3) / 4], const uint32_t (&em)[CPL]) {
+                                                     const uint64_t (&raw)[(CPL + 3) / 4], uint32_t odd, const uint32_t (&em)[CPL]) {
         // Neighbours of the lane's first and last column come from lanes -1 and +1.  Lane 0's left and
         // lane 63's right keep all ones: a window's side is either the image's edge, where that is the
         // missing parent, or ghost columns, where a wrong value moves one column inward per row and
         // never reaches an owned column within a phase.
         left = (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)Q[CPL - 1], 0x138, 0xf, 0xf, false);
         right = (uint32_t)__builtin_amdgcn_update_dpp((int)right, (int)Q[0], 0x130, 0xf, 0xf, false);
+        // (three-operand minima by hand: the compiler would share two-operand ones between columns,
+        // one instruction more per pair) first and last column first, for the next row's wave shifts
+        uint32_t pair[CPL / 2];  // energies of columns 2j, 2j + 1
+#pragma unroll
+        for (int j = 0; j < CPL / 2; ++j) pair[j] = (uint32_t)(raw[j >> 1] >> ((j & 1) * 32));
+        if constexpr (GRID) {  // odd: 0 or 16
+            const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)pair[0], 0x130, 0xf, 0xf, true);
+#pragma unroll
+            for (int j = 0; j < CPL / 2; ++j)
+                pair[j] = __builtin_amdgcn_alignbit(j + 1 < CPL / 2 ? pair[j + 1] : up, pair[j], odd);
+        }
         uint32_t n[CPL];
 #pragma unroll
-        for (int k = 0; k < CPL; ++k)
-            n[k] = min(min(k ? Q[k - 1] : left, Q[k]), k + 1 < CPL ? Q[k + 1] : right);
+        for (int i = 0; i < CPL; ++i) {
+            const int k = i == 0 ? 0 : i == 1 ? CPL - 1 : i - 1;
+            n[k] = min3u(k ? Q[k - 1] : left, Q[k], k + 1 < CPL ? Q[k + 1] : right);
+        }
 #pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            const uint32_t pair = (uint32_t)(ev[k >> 2] >> (((k >> 1) & 1) * 32));
-            Q[k] = (k & 1) ? mad_hi16(pair, n[k]) : mad_lo16(pair, n[k]);
-            if (EDGE) Q[k] |= em[k];
+        for (int i = 0; i < CPL; ++i) {
+            const int k = i == 0 ? 0 : i == 1 ? CPL - 1 : i - 1;
+            Q[k] = n[k] + ((k & 1) ? pair[k >> 1] >> 16 : pair[k >> 1] & 0xFFFFu);
+            if (EDGE || (GRID && k == 0)) Q[k] |= em[k];
         }
     }
-
-    // Tag of the keys a seam publishes: 1..511, never the 0 of a cleared row.  Every row of ck is
-    // written once per seam, so a reader only has to tell a seam from the one before it.
-    static __device__ __forceinline__ uint32_t seam_tag(int k) { return 1u + (uint32_t)k % 511u; }
 
     // Returns false when the wait for a neighbour's keys timed out (the image's status says so).
     template <bool EDGE, bool TEAM>
@@ -224,23 +264,29 @@ struct Carver {
         const int nsw = (items - tw + TW - 1) / TW;
         const int P0 = (hf[0].B * R + KR - 1) / KR, P1 = (hf[1].B * R + KR - 1) / KR;
         const uint32_t tag = seam_tag(k);
-        const __amdgpu_buffer_rsrc_t re = make_rsrc(d.e, (uint32_t)d.H * (uint32_t)d.ep * 2u);
+        const __amdgpu_buffer_rsrc_t re = energy_rsrc(d);
         const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
         const uint32_t ckrow = (uint32_t)d.xw * 4u;
         const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
+        constexpr uint32_t kGrid = GRID ? ~3u : ~0u;
 
         Item it = make_item(hf, w, ns, tw, TW, 0, 0, lane);
-        uint32_t roff = row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro);
+        uint32_t roff = Rows<R>::template row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro) + (GRID ? 2u * (uint32_t)it.base : 0u);
         uint64_t ring[PF][(CPL + 3) / 4];
 #pragma unroll
         for (int i = 0; i < PF; ++i)
-            load_ev<TEAM, CPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), i < it.drop ? kBufDrop : it.off);
-        uint32_t Q[CPL], em[CPL];
+            load_ev<TEAM, CPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i) & kGrid, it.off);
+        uint32_t Q[CPL], em[CPL];  // em: all ones in columns past the image
+        auto set_em = [&]() {
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            em[c] = EDGE && it.col0 + c >= w ? 0xFFFFFFFFu : 0u;
-            Q[c] = em[c];
-        }
+            for (int c = 0; c < CPL; ++c) em[c] = (EDGE || GRID) && it.col0 + c >= w ? 0xFFFFFFFFu : 0u;
+        };
+        set_em();
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) Q[c] = em[c];
+        // in lane l: half a dword if row l of the item starts off the dword grid
+        auto odd_of = [&](uint32_t r) { return GRID ? (r & 2u) << 3 : 0u; };
+        uint32_t odd = odd_of(roff);
         uint32_t left = 0xFFFFFFFFu, right = 0xFFFFFFFFu;
         for (;;) {
             // the wave's next item: its row offsets now, its first rows during this item's last block
@@ -250,17 +296,20 @@ struct Carver {
             } while (pn < P0 && hf[1].n > 0 && pn >= P1 && ((tw + jn * TW) & 1));
             const bool more = pn < P0;
             const Item nx = more ? make_item(hf, w, ns, tw, TW, pn, jn, lane) : it;
-            const uint32_t roffn = row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro);
+            const uint32_t roffn = Rows<R>::template row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro) + (GRID ? 2u * (uint32_t)nx.base : 0u);
+            // lanes from rg on are ghost columns: KR of them left of the window's right side, or (GRID: the
+            // last strip but one may reach past the image) of the image's
+            const int rg = it.t == ns - 1 ? 64 : GRID ? min(64 - KR / CPL, (w - it.base - KR) / CPL) : 64 - KR / CPL;
             // keys of the row above: the ghost columns, or every column when the wave has several items
             if (it.p == 0) {
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) Q[c] = em[c];
             } else if (ns > 1) {
-                const bool need = nsw > 1 || (it.t > 0 && lane < KR / CPL) || (it.t < ns - 1 && lane >= 64 - KR / CPL);
+                const bool need = nsw > 1 || (it.t > 0 && lane < KR / CPL) || lane >= rg;
                 const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + it.v0 / R - 1) * ckrow;
                 const uint32_t ko = need ? (uint32_t)it.col0 * 4u : kBufDrop;
-                unsigned long long t0 = 0;
-                for (int n = 0;; ++n) {
+                Wait wait;
+                for (;;) {
                     uint32_t x[CPL];
                     if constexpr (CPL == 2) {
                         const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rck, (int)ko, (int)krow, 16);
@@ -274,75 +323,64 @@ struct Carver {
                     }
                     bool ok = true;
 #pragma unroll
-                    for (int c = 0; c < CPL; ++c) ok = ok && (x[c] & 0x1FFu) == tag;
+                    for (int c = 0; c < CPL; ++c) ok = ok && ((x[c] & 0x1FFu) == tag || (GRID && em[c]));
                     if (__all(ok || !need)) {
 #pragma unroll
-                        for (int c = 0; c < CPL; ++c) Q[c] = need ? x[c] & ~0x1FFu : Q[c];
+                        for (int c = 0; c < CPL; ++c) Q[c] = need ? x[c] >> 9 | (GRID ? em[c] : 0u) : Q[c];
                         break;
                     }
-                    __builtin_amdgcn_s_sleep(1);
-                    if ((n & 63) == 63) {  // bounded wait: 10 s at the 100 MHz constant clock
-                        const unsigned long long now = wall_clock64();
-                        if (t0 == 0) t0 = now;
-                        if (now - t0 > 1000000000ull ||
-                            (__hip_atomic_load(gp(d.status), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                             (kStatusTimeout | kStatusPlacement))) {
-                            if (lane == 0)
-                                __hip_atomic_fetch_or(gp(d.status), kStatusTimeout, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-                            return false;
-                        }
-                    }
+                    if (wait.late(d)) return false;
                 }
             }
             // exact columns go out with the seam's tag at every block's last row (whole lanes: a
             // window's side is ghost columns or the image's edge); the next phase's neighbours and
             // the backtrack blocks start from them.  Columns two strips share are stored twice with
             // the same value.
-            const bool pub = (it.t == 0 || lane >= KR / CPL) && (it.t == ns - 1 || lane < 64 - KR / CPL);
+            const bool pub = (it.t == 0 || lane >= KR / CPL) && lane < rg && it.col0 < w;
             auto publish = [&](int v) {  // v: the row just done is v - 1
                 const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + v / R - 1) * ckrow;
                 if constexpr (EDGE) {
 #pragma unroll
                     for (int c = 0; c < CPL; ++c)
-                        __builtin_amdgcn_raw_buffer_store_b32((Q[c] & ~0x1FFu) | tag, rck, (int)(em[c] ? kBufDrop : (uint32_t)(it.col0 + c) * 4u),
+                        __builtin_amdgcn_raw_buffer_store_b32((Q[c] << 9) | tag, rck, (int)(em[c] ? kBufDrop : (uint32_t)(it.col0 + c) * 4u),
                                                               (int)krow, 0);
                 } else {
                     const uint32_t ko = pub ? (uint32_t)it.col0 * 4u : kBufDrop;
                     if constexpr (CPL == 2) {
-                        __builtin_amdgcn_raw_buffer_store_b64((v2u){Q[0] | tag, Q[1] | tag}, rck, (int)ko, (int)krow, 0);
+                        __builtin_amdgcn_raw_buffer_store_b64((v2u){(Q[0] << 9) | tag, (Q[1] << 9) | tag}, rck, (int)ko, (int)krow, 0);
                     } else {
 #pragma unroll
                         for (int c = 0; c < CPL; c += 4)
-                            buf_st128(rck, (v4u){Q[c] | tag, Q[c + 1] | tag, Q[c + 2] | tag, Q[c + 3] | tag},
+                            buf_st128(rck, (v4u){(Q[c] << 9) | tag, (Q[c + 1] << 9) | tag, (Q[c + 2] << 9) | tag, (Q[c + 3] << 9) | tag},
                                       krow + ko + 4u * c);
                     }
                 }
             };
-            int v = it.v0;
+            int v = __builtin_amdgcn_readfirstlane(it.v0);
+            const int v1 = __builtin_amdgcn_readfirstlane(it.v1), v0 = v;
 #pragma unroll 1
-            while (v < it.v1) {
+            while (v < v1) {
                 // the next rows' scalar offsets first: a scalar written by the vector unit may not be
                 // used as a buffer offset for some cycles
-                const bool cross = v + PF >= it.v1;
+                const bool cross = v + PF >= v1;
                 const uint32_t ro = cross ? roffn : roff;
                 const uint32_t eo = cross ? nx.off : it.off;
-                const int l0 = cross ? 0 : v + PF - it.v0;
-                const int dr = cross && more ? nx.drop : 0;
-                uint32_t so[PF];
+                const int l0 = __builtin_amdgcn_readfirstlane(cross ? 0 : v + PF - it.v0);
 #pragma unroll
-                for (int i = 0; i < PF; ++i) so[i] = (uint32_t)__builtin_amdgcn_readlane(ro, l0 + i);
+                for (int g = 0; g < PF; g += 8) {
+                    uint32_t so[8];
 #pragma unroll
-                for (int i = 0; i < PF; ++i) {
-                    cost_step<EDGE>(Q, left, right, ring[i], em);
-                    load_ev<TEAM, CPL>(ring[i], re, so[i], eo);
-                    __builtin_amdgcn_sched_barrier(0);  // keep the prefetch PF rows ahead of its use
-                }
-                if (dr) {  // another first-phase item: its missing rows carry no energy
+                    for (int i = 0; i < 8; ++i) so[i] = (uint32_t)__builtin_amdgcn_readlane(ro, l0 + g + i) & kGrid;
+                    uint32_t sh[8];
 #pragma unroll
-                    for (int i = 0; i < PF; ++i)
+                    for (int i = 0; i < 8; ++i) sh[i] = GRID ? (uint32_t)__builtin_amdgcn_readlane(odd, v - v0 + g + i) : 0u;
+                    arrived(ring[g + 7]);
 #pragma unroll
-                        for (int c = 0; c < (CPL + 3) / 4; ++c) ring[i][c] = i < dr ? 0 : ring[i][c];
+                    for (int i = 0; i < 8; ++i) {
+                        cost_step<EDGE>(Q, left, right, ring[g + i], sh[i], em);
+                        load_ev<TEAM, CPL>(ring[g + i], re, so[i], eo);
+                        __builtin_amdgcn_sched_barrier(0);  // keep the prefetch PF rows ahead of its use
+                    }
                 }
                 v += PF;
                 if (v % R == 0) publish(v);
@@ -350,40 +388,85 @@ struct Carver {
             if (!more) return true;
             it = nx;
             roff = roffn;
+            if constexpr (GRID) {
+                odd = odd_of(roff);
+                set_em();
+            }
         }
     }
+};
+
+// ----------------------------------------------------------------------------------------------
+// The carve engine: one image, carved by a team of G workgroups of NT threads.
+template <int CPL, int KR, int NT>
+struct Carver : Rows<block_rows(KR)> {
+    static constexpr int R = block_rows(KR);  // rows of a backtrack block
+    using Half = typename Rows<R>::Half;
+    using Rows<R>::half_of;
+    using Rows<R>::energy_rsrc;
+    using Narrow = Sweep<CPL, KR, R>;
+    static constexpr bool HAS_WIDE = CPL == 4 && R == 32;
+    using Wide = std::conditional_t<HAS_WIDE, Sweep<8, 32, 32>, Narrow>;  // of the same blocks
+    static constexpr int NW = NT / 64;      // waves per workgroup
+    static constexpr int PB = R;                    // the same of a backtrack block
+    static constexpr int BCPL = 4;            // columns per lane of a backtrack window
+    static constexpr int BW = 64 * BCPL;      // columns of a backtrack window
+    static constexpr int BS = BW - 2 * R;     // of which exact at the block's last row
+    static constexpr int NG = R / 4;          // 4-row direction groups of a block
+    static constexpr int BMAX = (kMaxRows / 2 + 4) / R + 2;  // blocks of half the tallest image
+    static constexpr int CH = 496 / R + 1;    // hops per memory round trip: h * R + 15 < 512 for h < CH
+    static_assert(R % PB == 0 && PB % 8 == 0, "whole prefetch groups");
+
+    struct Smem {
+        int jend[2 * BMAX];            // seam column at the last row of block b of half h at [h * BMAX + b]
+        int2 pos[2];                   // per half: the block the backtrack has reached (-1: done), its column
+        uint32_t cw[2][CH * 256];      // windows of ancestor offsets, 1024 bytes per hop
+        uint32_t al[NW][64];           // ancestor offsets of the waves' windows (a lone workgroup's round)
+        unsigned long long red[NW];
+        int flag;
+        int stop;                      // step mode: the time budget is spent
+    };
 
     // ---- the middle (a4): the cheapest pair of T's and B's last rows, leftmost lower column, then
     // leftmost upper one (an image of one half: the leftmost minimum of T's last row).  Every
     // workgroup of a team finds it by itself.  Key: M << 32 | lower column << 2 | (upper - lower + 1).
-    template <bool COH>
-    static __device__ __forceinline__ unsigned long long middle(const Img& d, Smem& sm, int w) {
-        constexpr int kC = COH ? 16 : 0;
+    template <bool TEAM>
+    static __device__ __forceinline__ unsigned long long middle(const Img& d, Smem& sm, int w, int k) {
+        constexpr int kC = TEAM ? 16 : 0;
         const Half h0 = half_of(d.H, d.mode, 0), h1 = half_of(d.H, d.mode, 1);
         const uint32_t ckrow = (uint32_t)d.xw * 4u;
         const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
-        const uint32_t t0 = (uint32_t)(h0.B - 1) * ckrow, b0 = (uint32_t)(h0.B + max(h1.B, 1) - 1) * ckrow;
+        const uint32_t t0 = (uint32_t)(h0.B - 1) * ckrow;
+        // one half: row t0 stands in for the missing lower one, and counts nothing
+        const uint32_t b0 = h1.n ? (uint32_t)(h0.B + h1.B - 1) * ckrow : t0, bm = h1.n ? ~0u : 0u;
+        const uint32_t tag = seam_tag(k);
         unsigned long long best = ~0ull;
         for (int c0 = 4 * (int)threadIdx.x; c0 < w; c0 += 4 * NT) {
-            const v4u T = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)t0, kC);
-            if (h1.n == 0) {
+            uint32_t x[6], y[4];
+            Wait wait;
+            for (;;) {
+                const v4u T = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)t0, kC);
+                const v4u B = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)b0, kC);
+                x[0] = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)t0, kC);
+                x[5] = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 + 4 < w ? c0 * 4 + 16 : (int)kBufDrop, (int)t0, kC);
+                bool ok = (c0 == 0 || (x[0] & 0x1FFu) == tag) && (c0 + 4 >= w || (x[5] & 0x1FFu) == tag);
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (c0 + c < w)
-                        best = min(best, ((unsigned long long)(T[c] >> 9) << 32) | (unsigned)((c0 + c) << 2) | 1u);
-                continue;
+                for (int c = 0; c < 4; ++c) {
+                    x[c + 1] = T[c];
+                    y[c] = B[c];
+                    ok = ok && (c0 + c >= w || ((T[c] & 0x1FFu) == tag && (B[c] & 0x1FFu) == tag));
+                }
+                if (!TEAM || ok || wait.late(d)) break;
             }
-            const v4u B = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)b0, kC);
-            const uint32_t tl = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)t0, kC);
-            const uint32_t tr = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 + 4 < w ? c0 * 4 + 16 : (int)kBufDrop, (int)t0, kC);
-            const uint32_t x[6] = {tl, T[0], T[1], T[2], T[3], tr};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if (c0 + c >= w) continue;
-                uint32_t m = c0 + c > 0 ? x[c] >> 9 : 0x7FFFFFFFu, dir = 0;
-                if ((x[c + 1] >> 9) < m) m = x[c + 1] >> 9, dir = 1;
-                if (c0 + c + 1 < w && (x[c + 2] >> 9) < m) m = x[c + 2] >> 9, dir = 2;
-                best = min(best, ((unsigned long long)(m + (B[c] >> 9)) << 32) | (unsigned)((c0 + c) << 2) | dir);
+                uint32_t m = x[c + 1] >> 9, dir = 1;
+                if (bm) {
+                    if (c0 + c > 0 && (x[c] >> 9) <= m) m = x[c] >> 9, dir = 0;
+                    if (c0 + c + 1 < w && (x[c + 2] >> 9) < m) m = x[c + 2] >> 9, dir = 2;
+                }
+                best = min(best, ((unsigned long long)(m + ((y[c] & bm) >> 9)) << 32) | (unsigned)((c0 + c) << 2) | dir);
             }
         }
 #pragma unroll
@@ -404,30 +487,44 @@ struct Carver {
     // its last row.  All blocks run at once, one wave each, where the path can still be.
     template <bool EDGE, bool COH>
     static __device__ __forceinline__ void trace_block(const Img& d, const Half& x, int h, int blk, int ckbase, int w,
-                                                       int base, int lane, uint32_t (&pk)[NG], uint32_t (&Q)[BCPL]) {
-        const __amdgpu_buffer_rsrc_t re = make_rsrc(d.e, (uint32_t)d.H * (uint32_t)d.ep * 2u);
+                                                       int k, int base, int lane, uint32_t (&pk)[NG], uint32_t (&Q)[BCPL]) {
+        const __amdgpu_buffer_rsrc_t re = energy_rsrc(d);
         const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
         const uint32_t ckrow = (uint32_t)d.xw * 4u;
         const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
         const int col0 = base + lane * BCPL;
-        const uint32_t roff = row_off<COH>(d, x, h, blk * R + min(lane, R - 1), rro);
-        const v4u kv = __builtin_amdgcn_raw_buffer_load_b128(rck, blk > 0 && col0 < w ? col0 * 4 : (int)kBufDrop,
-                                                             (int)((uint32_t)(ckbase + max(blk, 1) - 1) * ckrow), COH ? 16 : 0);
+        const uint32_t roff = Rows<R>::template row_off<COH>(d, x, h, blk * R + min(lane, R - 1), rro);
+        auto load_keys = [&]() {
+            return __builtin_amdgcn_raw_buffer_load_b128(rck, blk > 0 && col0 < w ? col0 * 4 : (int)kBufDrop,
+                                                         (int)((uint32_t)(ckbase + max(blk, 1) - 1) * ckrow), COH ? 16 : 0);
+        };
+        v4u kv = load_keys();
         const uint32_t eo = (uint32_t)(col0 < w ? col0 : 0) * 2u;
-        const int drop = blk ? 0 : x.pad;  // rows without energy
-        uint64_t ring[PF][1];
+        uint64_t ring[PB][1];
 #pragma unroll
-        for (int i = 0; i < PF; ++i)
-            load_ev<COH, BCPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), i < drop ? kBufDrop : eo);
+        for (int i = 0; i < PB; ++i)
+            load_ev<COH, BCPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), eo);
         bool valid[BCPL];
 #pragma unroll
+        for (int c = 0; c < BCPL; ++c) valid[c] = !EDGE || col0 + c < w;
+        if (COH && blk > 0) {  // the strips' stores may still be on their way
+            Wait wait;
+            for (;;) {
+                bool ok = true;
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) ok = ok && (!valid[c] || (kv[c] & 0x1FFu) == seam_tag(k));
+                if (__all(ok) || wait.late(d)) break;
+                kv = load_keys();
+            }
+        }
+#pragma unroll
         for (int c = 0; c < BCPL; ++c) {
-            valid[c] = !EDGE || col0 + c < w;
             Q[c] = valid[c] ? kv[c] & ~0x1FFu : QINF;
         }
         uint32_t left = QINF, right = QINF, p = 0;
         static_for<R>([&](auto I) {
             constexpr int i = decltype(I)::value;
+            if constexpr (i % 8 == 0) arrived(ring[(i + 7) % PB]);
             uint32_t t[BCPL];
 #pragma unroll
             for (int c = 0; c < BCPL; ++c) t[c] = Q[c] & ~3u;
@@ -437,16 +534,15 @@ struct Carver {
 #pragma unroll
             for (int c = 0; c < BCPL; ++c) {
                 const uint32_t m = min(min(c ? t[c - 1] : left, t[c] + 5u), c + 1 < BCPL ? t[c + 1] + 10u : right);
-                const uint32_t pair = (uint32_t)(ring[i % PF][0] >> ((c >> 1) * 32));
+                const uint32_t pair = (uint32_t)(ring[i % PB][0] >> ((c >> 1) * 32));
                 Q[c] = (c & 1) ? mad_hi16(pair, m) : mad_lo16(pair, m);
                 if (EDGE) Q[c] = valid[c] ? Q[c] : QINF;
                 acc = __builtin_amdgcn_alignbit(m, acc, 2u);
             }
             p = __builtin_amdgcn_perm(acc, p, 0x07030201u);  // this row's byte on top
             if constexpr (i % 4 == 3) pk[i / 4] = p;
-            if constexpr (i + PF < R)
-                load_ev<COH, BCPL>(ring[i % PF], re, (uint32_t)__builtin_amdgcn_readlane(roff, i + PF),
-                                   i + PF < drop ? kBufDrop : eo);
+            if constexpr (i + PB < R)
+                load_ev<COH, BCPL>(ring[i % PB], re, (uint32_t)__builtin_amdgcn_readlane(roff, i + PB), eo);
             __builtin_amdgcn_sched_barrier(0);
         });
     }
@@ -460,7 +556,7 @@ struct Carver {
         for (int q = tw; q < x.B * nw; q += TW) {
             const int blk = q / nw, j = q % nw, base = j * BS, col0 = base + lane * BCPL;
             uint32_t pk[NG], Q[BCPL];
-            trace_block<true, COH>(d, x, 0, blk, 0, w, base, lane, pk, Q);
+            trace_block<true, COH>(d, x, 0, blk, 0, w, 0, base, lane, pk, Q);
             const bool own = (j == 0 || lane >= R / BCPL) && (j == nw - 1 || lane < 64 - R / BCPL);
             for (int i = 0; i < R; ++i) {
                 const int y = blk * R + i - x.pad;
@@ -526,8 +622,8 @@ struct Carver {
             if (act) {
                 uint32_t Q[BCPL];
                 const int ckb = h ? hf[0].B : 0;
-                if (base + BW > w) trace_block<true, TEAM>(d, x, h, blk, ckb, w, base, lane, pk, Q);
-                else trace_block<false, TEAM>(d, x, h, blk, ckb, w, base, lane, pk, Q);
+                if (base + BW > w) trace_block<true, TEAM>(d, x, h, blk, ckb, w, k, base, lane, pk, Q);
+                else trace_block<false, TEAM>(d, x, h, blk, ckb, w, k, base, lane, pk, Q);
                 // ancestor offsets of the exact columns (whole lanes; a lane past w - 1 writes into
                 // the row's slack)
                 const int col0 = base + lane * BCPL;
@@ -535,12 +631,15 @@ struct Carver {
                 uint32_t a = 0;
 #pragma unroll
                 for (int q = 0; q < BCPL; ++q) a |= (((Q[q] >> 2) & 127u) & 0xFFu) << (8 * q);
-                __builtin_amdgcn_raw_buffer_store_b32(a, ranc, (int)(own ? (uint32_t)col0 : kBufDrop),
-                                                      (int)((uint32_t)(ckb + blk) * (uint32_t)d.xw), 0);
+                if constexpr (TEAM)
+                    __builtin_amdgcn_raw_buffer_store_b32(a, ranc, (int)(own ? (uint32_t)col0 : kBufDrop),
+                                                          (int)((uint32_t)(ckb + blk) * (uint32_t)d.xw), 0);
+                else
+                    sm.al[wv][lane] = a;
             }
             if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return false;
             // wave h hops through half h: a block's path column at its last row is within R columns of
-            // the next block's, so a round trip loads the offsets of CH blocks at once (512 bytes of
+            // the next block's, so a round trip loads the offsets of CH blocks at once (1 KB of
             // each row around the current column) and takes CH hops from LDS
             const int hh = wv & 1;
             if (wv < 2 && (hh ? b[1] : b[0]) >= 0) {
@@ -550,31 +649,43 @@ struct Carver {
                 const int low = p - (hh ? nblk[1] : nblk[0]) + 1;
                 bool run = true;
                 if (lane == 0) sm.jend[hh * BMAX + p] = j;
+                if constexpr (!TEAM) {
+                    // the round's offsets are in LDS: block p's window j is wave (p0 - p) * nw + j of this half
+                    const int p0 = p, X = hh ? X0[1] : X0[0], nwh = hh ? nwin[1] : nwin[0];
+                    while (p > 0) {
+                        const int win = min(max((j - X - R) / BS, 0), nwh - 1);
+                        const int idx = (p0 - p) * nwh + win, wo = nopen == 2 ? 2 * idx + hh : idx;
+                        const int bs = min(X + win * BS, max(0, w - BW));
+                        const int a = reinterpret_cast<const uint8_t*>(sm.al[wo])[min(max(j - bs, 0), BW - 1)];
+                        j = __builtin_amdgcn_readfirstlane(min(max(j + a - R, 0), w - 1));
+                        --p;
+                        if (p < low || j < lo || j >= hi) break;
+                        if (lane == 0) sm.jend[hh * BMAX + p] = j;
+                    }
+                    if (p == 0 && p >= low && j >= lo && j < hi) p = -1;
+                    run = false;
+                }
                 while (run) {
-                    const int j0 = j, p0 = p, m = min(CH, p - max(low, 1) + 1);
-                    uint32_t v[CH][2];
+                    const int j0 = j, p0 = p, m = min(TEAM ? Carver::CH : 8, p - max(low, 1) + 1);
+                    constexpr int CH = TEAM ? Carver::CH : 8;  // (a lone workgroup's round has few blocks)
+                    v4u v[CH];
+                    // byte window [o, o + 1024) of every block's row, from a multiple of 16 at or below
+                    // j0 - 512; what lies before the array is dropped
+                    const int w0 = (j0 - 512) & ~15;
 #pragma unroll
                     for (int i = 0; i < CH; ++i) {
-                        // byte window [o, o + 512) of block p - i's row, from a dword at or below j - 256;
-                        // dwords before the array are dropped
-                        const int o = (ckb + p0 - i) * d.xw + ((j0 - 256) & ~3);
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const int bo = o + 4 * (lane + 64 * q);
-                            v[i][q] = buf_ld32<TEAM>(ranc, i < m && bo >= 0 ? (uint32_t)bo : kBufDrop);
-                        }
+                        const int bo = (ckb + p0 - i) * d.xw + w0 + 16 * lane;
+                        v[i] = __builtin_amdgcn_raw_buffer_load_b128(ranc, (int)(i < m && bo >= 0 ? (uint32_t)bo : kBufDrop), 0,
+                                                                     TEAM ? 16 : 0);
                     }
 #pragma unroll
-                    for (int i = 0; i < CH; ++i) {
-                        cw[i * 128 + lane] = v[i][0];
-                        cw[i * 128 + 64 + lane] = v[i][1];
-                    }
+                    for (int i = 0; i < CH; ++i) *reinterpret_cast<v4u*>(cw + i * 256 + 4 * lane) = v[i];
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                     const uint8_t* cb = reinterpret_cast<const uint8_t*>(cw);
                     for (int i = 0; i < m; ++i) {
-                        const int a = (int)(int8_t)cb[i * 512 + min(max(j - ((j0 - 256) & ~3), 0), 511)];
+                        const int a = (int)(int8_t)cb[i * 1024 + min(max(j - w0, 0), 1023)];
                         j = __builtin_amdgcn_readfirstlane(min(max(j + a - R, 0), w - 1));
                         --p;
                         if (p < low || j < lo || j >= hi) {
@@ -609,7 +720,7 @@ struct Carver {
                     if (lane < R && y >= 0) {
                         const int r = h ? d.H - 1 - y : y;
                         const int col = min(max(base + mys, 0), w - 1);
-                        *gp(d.seam + r) = col;
+                        *gp(d.seam + r) = (int32_t)((uint32_t)col | seam_word(k));
                         if (d.seams_out) *gp(d.seams_out + (size_t)k * d.H + r) = col;
                     }
                 }
@@ -625,17 +736,28 @@ struct Carver {
     // without min-side removal always the right side).  A row is only ever written by the wave owning
     // it, so plain loads see its current bytes even in a team.
     template <bool TEAM>
-    static __device__ __forceinline__ void remove_rows(const Img& d, int w, int ra, int rb, int lane) {
+    static __device__ __forceinline__ void remove_rows(const Img& d, int w, int k, int ra, int rb, int lane) {
         const __amdgpu_buffer_rsrc_t rsm = make_rsrc(d.seam, (uint32_t)d.H * 4u);
-        for (int rc = ra; rc < rb; rc += 64) {
-            const int n = min(64, rb - rc);
-            const int s = min(max((int)buf_ld32<TEAM>(rsm, lane < n ? (uint32_t)(rc + lane) * 4u : kBufDrop), 0), w - 1);
-            const int o = lane < n ? *gp(d.ro + rc + lane) : 0;
+        const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
+        for (int row = ra; row < rb; row += 64) {
+            // no branch on a lane's row here: the compiler would carry the row through it in vector
+            // registers, take the planes' descriptors for lane dependent and loop over the lanes at every access
+            const int rc = __builtin_amdgcn_readfirstlane(row);
+            const int n = __builtin_amdgcn_readfirstlane(min(64, rb - row));
+            const uint32_t mine = lane < n ? (uint32_t)(rc + lane) * 4u : kBufDrop;
+            const int o = (int)buf_ld32<false>(rro, mine);
+            uint32_t word;
+            Wait wait;
+            for (;;) {  // the rows' walkers may still be at it
+                word = buf_ld32<TEAM>(rsm, mine);
+                if (!TEAM || __all(lane >= n || (word & 0xFFFF0000u) == seam_word(k)) || wait.late(d)) break;
+            }
+            const int s = min((int)(word & 0xFFFFu), w - 1);
             const bool right = d.minside && s < w - 1 - s;
-            if (lane < n && right) *gp(d.ro + rc + lane) = o + 1;
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(o + 1), rro, (int)(right ? mine : kBufDrop), 0, 0);
             const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
                                           shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, 2)};
-            shift_rows<2, 2>(planes, n, w, s, o, right, lane);
+            shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, 2), lane);
         }
     }
 
@@ -660,15 +782,21 @@ struct Carver {
             if (timer) tm0 = wall_clock64();
             {
                 const Img d = fetch(gd);
-                // a wave that gave up waiting has flagged the image, and the team's barrier abandons it
-                if (w < WIN) cost_sweep<true, TEAM>(d, w, k, tw, TW, lane);
-                else cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
+                // (a wave that gives up waiting flags the image; the others then give up at once)
+                // Wide strips (eight columns per lane) where the waves are too few for one narrow strip
+                // each: their ghost columns are a sixteenth of the window on each side against a quarter.
+                // The 256-image batch by one workgroup per image takes 426 ms so and 515 ms with narrow
+                // strips alone; with a wave for every narrow strip those are faster (1920 x 1080 by 32
+                // workgroups: 27 us per sweep against 50).
+                if (w < Narrow::WIN && Narrow::strips(w) == 1) Narrow::template cost_sweep<true, TEAM>(d, w, k, tw, TW, lane);
+                else if (!HAS_WIDE || 2 * Narrow::strips(w) <= TW || w <= Wide::WINR) Narrow::template cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
+                else Wide::template cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
             }
-            // the keys of every block are complete past here
-            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            // (a team's waves go on to wait for the tags of what they need)
+            if constexpr (!TEAM) __syncthreads();
             {
                 const Img d = fetch(gd);
-                const unsigned long long key = middle<TEAM>(d, sm, w);
+                const unsigned long long key = middle<TEAM>(d, sm, w, k);
                 if (rank == 0 && threadIdx.x == 0 && d.costs_out) *gp(d.costs_out + k) = (long long)(key >> 32);
                 if (timer) tm1 = wall_clock64();
                 if constexpr (MAP) {
@@ -677,8 +805,8 @@ struct Carver {
                 if (!backtrack<TEAM>(d, gd, sm, w, k, tw, TW, lane, G, epoch, key)) return k;
             }
             if (mode) break;
-            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
-            remove_rows<TEAM>(fetch(gd), w, ra, rb, lane);
+            if constexpr (!TEAM) __syncthreads();
+            remove_rows<TEAM>(fetch(gd), w, k, ra, rb, lane);
             if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
             if (timer) tm2 = wall_clock64();
             const Img d = fetch(gd);
@@ -692,7 +820,7 @@ struct Carver {
             for (int rc = ra; rc < rb; rc += 64) {
                 const int r = rc + lane < rb ? rc + lane : ra;
                 const int ru = r > 0 ? r - 1 : 0, rd = r + 1 < H ? r + 1 : H - 1;
-                const int s = min(max((int)buf_ld32<TEAM>(rsm, (uint32_t)r * 4u), 0), w - 1);
+                const int s = min((int)(buf_ld32<TEAM>(rsm, (uint32_t)r * 4u) & 0xFFFFu), w - 1);
                 const int o = (int)buf_ld32<TEAM>(rof, (uint32_t)r * 4u);
                 const uint32_t br = (uint32_t)r * (uint32_t)d.wp + (uint32_t)(o * d.C);
                 const uint32_t bu = (uint32_t)ru * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)ru * 4u) * (uint32_t)d.C;

@@ -102,16 +102,20 @@ __device__ __forceinline__ void static_for(F&& f) {
 // column right (right = true; the row then starts one column later).  A row's pixels start at column
 // o of the plane and w of them are in use.
 //
-// The work is 16-byte slots at aligned offsets, numbered from the seam outward; a lane loads a slot's
-// new bytes with one unaligned 16-byte load (the slot moved by one pixel) and stores it aligned.  Only
-// the seam's own slot (slot 0, lane 0) keeps bytes of the row: those on the other side of the gap.
-// At the far end the last slot may run over bytes that are not in use (past the row's last pixel, or
-// before its first one), never past the row's pitch.  A pass reads one pixel beyond its slots, into
-// the next pass's, so passes go outward and every load of a pass comes before its stores.
+// The work is the row's aligned 16-byte slots in ascending order, one per lane.  A lane loads 16 bytes
+// from its slot (right: from a dword below it) and takes the dword above them from the next lane; its
+// new bytes are then one v_perm per dword, whichever the direction, and the bytes on the far side of
+// the seam pixel, in the seam's slot alone, are kept by that lane's own selectors.  At the other end
+// the last slot runs over bytes of the row that are not in use.  A pass stores 63 slots: its last lane
+// only lends its dword.  Moving right, a pass reads bytes that the pass before it writes, so a pass
+// must load before the pass before it stores.
 //
-// What bounds it: memory latency.  NR rows of NP planes are one item, and the next item's loads go
-// out before this item's stores, so a wait for loads never covers a store (one counter for both,
-// drained in order); nothing branches between them, or the counter's state would be lost.
+// What bounds it: accesses and their latency.  Every access is dword aligned: one that is not costs 64
+// cycles of the compute unit's address path instead of 16 (measured, 16 bytes per lane), which a
+// workgroup moving its rows with unaligned slots ran into (1200 x 1200 by one workgroup: 108 us per
+// seam so, 86 us aligned; 3840 x 2160 by 16: 42 us and 30 us).  NR rows of NP planes are one item, and the next item's loads go out
+// before this item's stores, so a wait for loads never covers a store (one counter for both, drained
+// in order); nothing branches between them, or the counter's state would be lost.
 struct ShiftPlane {
     __amdgpu_buffer_rsrc_t r;  // from 16 bytes below the first row to 64 past the last
     uint32_t pitch;            // bytes per row, a multiple of 16
@@ -123,90 +127,110 @@ __device__ __forceinline__ ShiftPlane shift_plane(void* row0, int n, uint32_t pi
     return {make_rsrc(static_cast<uint8_t*>(row0) - 16, 16u + (uint32_t)n * pitch + 64u), pitch, px};
 }
 
-struct ShiftSlot {
-    v4u v, own;        // the moved bytes; the bytes in place (slot 0)
-    uint32_t vo;       // the store's offset
-    uint64_t k0, k1;   // the bytes slot 0 keeps
-};
-
-__device__ __forceinline__ int shift_load(ShiftSlot& q, const ShiftPlane& p, bool live, int row, int s, int o, int w,
-                                          bool right, int fb, int lane) {
-    const int lo = (right ? o + 1 : o + s) * p.px, hi = (right ? o + s + 1 : o + w - 1) * p.px;
-    const int first = (right ? hi - 1 : lo) & ~15;
-    const int span = right ? first - (lo & ~15) : ((hi - 1) & ~15) - first;
-    const int n = live && hi > lo ? (span >> 4) + 1 : 0;
-    const int f = fb + lane;
-    const uint32_t at = (uint32_t)row * p.pitch + (uint32_t)(16 + first + (right ? -16 : 16) * f);
-    q.vo = f < n ? at : kBufDrop;
-    q.v = __builtin_amdgcn_raw_buffer_load_b128(p.r, (int)(f < n ? at + (uint32_t)(right ? -p.px : p.px) : kBufDrop),
-                                                0, 0);
-    q.own = __builtin_amdgcn_raw_buffer_load_b128(p.r, (int)(f == 0 && n > 0 ? at : kBufDrop), 0, 0);
-    // kept: the first c bytes of the slot, or (right) all but the first c
-    const int c = right ? ((hi - 1) & 15) + 1 : lo & 15;
-    const uint64_t m0 = c >= 8 ? ~0ull : (1ull << (8 * c)) - 1, m1 = c >= 16 ? ~0ull : c > 8 ? (1ull << (8 * c - 64)) - 1 : 0;
-    q.k0 = right ? ~m0 : m0;
-    q.k1 = right ? ~m1 : m1;
-    return n;
-}
-
-__device__ __forceinline__ void shift_store(const ShiftSlot& q, const ShiftPlane& p, int fb, int lane) {
-    const bool z = fb + lane == 0;
-    const uint32_t k[4] = {(uint32_t)q.k0, (uint32_t)(q.k0 >> 32), (uint32_t)q.k1, (uint32_t)(q.k1 >> 32)};
-    v4u o;
+// The n rows of the planes; lane l holds row l's seam s, start o and side.  LPR lanes work on a row
+// (64 / LPR rows share an access; every row then fits LPR - 1 slots).
+template <int LPR, int NR, int NP>
+__device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int lane) {
+    constexpr int RPA = 64 / LPR;  // rows per access
+    // per row and plane: the load offset of slot 0, the slots, the seam slot's selectors
+    int at[NP], cnt[NP];
+    uint32_t sel[NP][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t m = z ? k[i] : 0u;
-        o[i] = (q.own[i] & m) | (q.v[i] & ~m);
+    for (int x = 0; x < NP; ++x) {
+        const int px = p[x].px;
+        const int lo = (right ? o + 1 : o + s) * px, hi = (right ? o + s + 1 : o + w - 1) * px;
+        at[x] = lane * (int)p[x].pitch + 16 + (lo & ~15) - (right ? 4 : 0);
+        cnt[x] = lane < n && hi > lo ? ((hi - 1) >> 4) - (lo >> 4) + 1 : 0;
+        const int z = right ? ((hi - 1) & 15) + 1 : lo & 15;  // kept: the bytes below z, or from z on
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = z - 4 * i;
+            const uint32_t low = c >= 4 ? ~0u : c <= 0 ? 0u : (1u << (8 * c)) - 1u;
+            const uint32_t move = (uint32_t)px * 0x01010101u;
+            // a moved byte of dword i is byte px (right: 4 - px) further on in dwords i, i + 1
+            sel[x][i] = 0x03020100u + (right ? 0x04040404u - (move & low) : move & ~low);
+        }
     }
-    buf_st128(p.r, o, q.vo);
-}
-
-// The n rows of the planes; lane l holds row l's seam s, start o and side.
-template <int NR, int NP>
-__device__ __forceinline__ void shift_rows(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int lane) {
-    const int rt = right;
-    auto load = [&](ShiftSlot (&b)[NR][NP], int i, int fb) {
+    const int sub = lane / LPR, f0 = lane % LPR;
+    auto row_of = [&](int v, int i) {  // row i's value, in the lanes that work on it
+        if constexpr (LPR == 64) return __builtin_amdgcn_readlane(v, i);
+        else return __shfl(v, i + sub, 64);
+    };
+    const int side = right;
+    struct Slot {
+        v4u v;
+        uint32_t vo;
+        int kf;  // the seam's slot
+        int li;  // the row, in sel
+        int sd;
+    };
+    auto load = [&](Slot (&b)[NR][NP], int i, int fb) {  // rows i .. i + NR * RPA - 1, from slot fb of each
         int most = 0;
 #pragma unroll
         for (int a = 0; a < NR; ++a) {
-            const int li = min(i + a, n - 1);
-            const int si = __builtin_amdgcn_readlane(s, li), oi = __builtin_amdgcn_readlane(o, li);
-            const bool ri = __builtin_amdgcn_readlane(rt, li) != 0;
+            const int li = min(i + a * RPA, 64 - RPA);  // rows past n have no slots
+            const bool live = i + a * RPA < n;
+            const int sd = row_of(side, li);
 #pragma unroll
-            for (int x = 0; x < NP; ++x)
-                most = max(most, shift_load(b[a][x], p[x], i + a < n, li, si, oi, w, ri, fb, lane));
+            for (int x = 0; x < NP; ++x) {
+                const int base = row_of(at[x], li), c = live ? row_of(cnt[x], li) : 0;
+                const int f = fb + f0;
+                const uint32_t off = (uint32_t)(base + 16 * f);
+                Slot& q = b[a][x];
+                q.v = __builtin_amdgcn_raw_buffer_load_b128(p[x].r, (int)(f <= c && c > 0 ? off : kBufDrop), 0, 0);
+                q.vo = f < c && f0 < LPR - 1 ? off + (sd ? 4u : 0u) : kBufDrop;
+                q.kf = (sd ? c - 1 : 0) - fb;
+                q.li = li;
+                q.sd = sd;
+                if constexpr (LPR == 64) most = max(most, c);
+            }
         }
         return most;
     };
-    auto store = [&](const ShiftSlot (&b)[NR][NP], int fb) {
+    auto store = [&](const Slot (&b)[NR][NP]) {
 #pragma unroll
         for (int a = 0; a < NR; ++a)
 #pragma unroll
-            for (int x = 0; x < NP; ++x) shift_store(b[a][x], p[x], fb, lane);
+            for (int x = 0; x < NP; ++x) {
+                const Slot& q = b[a][x];
+                const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)q.v[0], 0x130, 0xf, 0xf, true);
+                const uint32_t y[5] = {q.v[0], q.v[1], q.v[2], q.v[3], up};
+                const uint32_t all = 0x03020100u + (uint32_t)(q.sd ? 4 - p[x].px : p[x].px) * 0x01010101u;
+                v4u out;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t own = (uint32_t)row_of((int)sel[x][i], q.li);
+                    out[i] = __builtin_amdgcn_perm(y[i + 1], y[i], f0 == q.kf ? own : all);
+                }
+                buf_st128(p[x].r, out, q.vo);
+            }
     };
     int i = 0, fb = 0;
     auto step = [&](int most) {  // the next pass of these rows, or the next rows
-        const bool again = fb + 64 < most;
-        i = again ? i : i + NR;
-        fb = again ? fb + 64 : 0;
+        const bool again = LPR == 64 && fb + 63 < most;
+        i = again ? i : i + NR * RPA;
+        fb = again ? fb + 63 : 0;
     };
-    ShiftSlot A[NR][NP], B[NR][NP];
-    int fa = 0, fbb;
+    Slot A[NR][NP], B[NR][NP];
     step(load(A, i, fb));
     for (;;) {
-        fbb = fb;
         const bool mb = i < n;
-        const int nb = load(B, i, fb);
-        step(nb);
-        store(A, fa);
+        step(load(B, i, fb));
+        store(A);
         if (!mb) break;
-        fa = fb;
         const bool ma = i < n;
-        const int na = load(A, i, fb);
-        step(na);
-        store(B, fbb);
+        step(load(A, i, fb));
+        store(B);
         if (!ma) break;
     }
+}
+
+// `most`: the bytes that the widest row may have to move.  Rows of narrow images share accesses.
+template <int NR, int NP>
+__device__ __forceinline__ void shift_rows(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int most,
+                                           int lane) {
+    if (most <= 208) shift_rows_lpr<16, NR / 2, NP>(p, n, w, s, o, right, lane);
+    else shift_rows_lpr<64, NR, NP>(p, n, w, s, o, right, lane);
 }
 
 // dst bytes [dst, dst + n) take the bytes of [src, src + n), one wave; the buffers do not overlap.

@@ -486,7 +486,7 @@ struct Carver {
                 // included, so column w-1 then holds a copy of the new last pixel
                 const ShiftPlane planes[1] = {shift_plane(d.wk + (size_t)(r0 + ia) * d.wp, ib - ia, (uint32_t)d.wp, 4)};
                 const int sl = min(max(__shfl(mys, min(ia + lane, 63), 64), 0), w - 1);  // row ia + lane
-                shift_rows<4, 1>(planes, ib - ia, w + 1, sl, 0, false, lane);
+                shift_rows<4, 1>(planes, ib - ia, w + 1, sl, 0, false, w * 4, lane);
                 // a seam at the last column removed the pixel the copy repeated: the new last pixel
                 // (w-2) is copied to w-1 (after the shift's store to it, same wave)
                 if (lane < ib - ia && w >= 2 && sl == w - 1) {

@@ -16,7 +16,7 @@ struct Img {
     int32_t* seams_out;  // optional, (W-target_w)*H
     long long* costs_out;  // optional, W-target_w
     // workspace pieces
-    uint16_t* e;   // energy plane, H rows of `ep` uint16
+    uint16_t* e;   // energy plane, H rows of `ep` uint16 and a row of zeros
     uint8_t* dirs; // forward energy: parent directions, 2 bits per cell, H rows of `db` bytes
     int8_t* anc;   // the ancestor offset of every column at the last row of a block (`xw` bytes per row)
                    // or, forward energy, of a DP phase
@@ -29,7 +29,7 @@ struct Img {
     unsigned* bar;             // team barrier counter
     unsigned* status;          // error bits
     int ep, db, xw, P;         // pitches; rows of published keys (forward energy: DP phases)
-    int wp;                    // bytes per row of wk
+    int wp;                    // bytes per row of wk, at least 16 more than its pixels
     int G;                     // team size (workgroups) carving this image
     int mode;                  // 0 = carve, 1 = one seam only, no removal (sc_dp_seam), 2 = the same
                                // and the direction of every cell as a byte in img (H x W)

@@ -76,6 +76,7 @@ __device__ void prepare_tile(const Img& d, const uint8_t* srcimg, int y0, int y1
         if (y + 1 < y1) nx.load(srcimg, d.pitch, W, min(y + 2, H - 1), x0);
         if (act) {
             if (d.e) {
+                if (y == H - 1) *gp(reinterpret_cast<v2u*>(d.e + (long long)H * d.ep + x0)) = v2u{0u, 0u};  // row of zeros
                 uint32_t e[4];
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
@@ -120,7 +121,10 @@ __device__ void prepare_image(const Img& d, int tile0, int tstep) {
     for (int tile = tile0; tile < ns * nc; tile += tstep) {
         const int strip = tile % ns, chunk = tile / ns;
         const int y0 = chunk * kTileRows, y1 = min(d.H, y0 + kTileRows);
-        if (strip == 0 && (int)threadIdx.x < y1 - y0) *gp(d.ro + y0 + threadIdx.x) = 0;
+        if (strip == 0 && (int)threadIdx.x < y1 - y0) {
+            *gp(d.ro + y0 + threadIdx.x) = 0;
+            *gp(d.seam + y0 + threadIdx.x) = 0;  // no seam's tag
+        }
         switch (d.C) {
             case 1: prepare_tile<1>(d, srcimg, y0, y1, strip * kTileCols); break;
             case 2: prepare_tile<2>(d, srcimg, y0, y1, strip * kTileCols); break;
@@ -154,6 +158,7 @@ __global__ void prepare_from_i32_kernel(Img d, const int32_t* __restrict__ e) {
     for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < d.W; x += gridDim.x * blockDim.x) {
         *gp(d.e + (long long)y * d.ep + x) = (uint16_t)*gp(e + (long long)y * d.W + x);
         if (y < d.P) *gp(d.xq + (size_t)y * d.xw + x) = 0u;
+        if (y == d.H - 1) *gp(d.e + (long long)d.H * d.ep + x) = 0;  // the plane's row of zeros
     }
 }
 

@@ -320,7 +320,7 @@ struct Carver : PixRow<C, CPL> {
                     const int si = lane < n ? min(max(*gp(d.seam + r + lane), 0), w - 1) : 0;
                     const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)r * d.wp, n, (uint32_t)d.wp, C),
                                                   shift_plane(d.mk + (size_t)r * d.mp, n, (uint32_t)d.mp, 1)};
-                    shift_rows<2, 2>(planes, n, w, si, 0, false, lane);
+                    shift_rows<2, 2>(planes, n, w, si, 0, false, w * C, lane);
                 }
             }
             __syncthreads();

@@ -1,0 +1,62 @@
+"""GPU: the carve at the sizes where its tiling changes shape, bit-exact against the oracle.
+
+Strips of the cost sweep (a window of 256 columns, or 504 of a 512-column one when there are too few
+waves for narrow strips), halves and blocks of 24 or 32 rows, rows that share an access of the row
+shifter (up to 208 bytes to move) or take several passes (63 slots of 16 bytes each).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import dev, host, log
+
+pytestmark = pytest.mark.gpu
+
+from paper_2410_21207_amd import api  # noqa: E402
+
+
+def _check(H, W, C, k, alpha=256, **kw):
+    log("carve shape", H, W, C, k, alpha, kw)
+    img = np.random.default_rng(H * 7919 + W + C).integers(0, alpha, size=(H, W, C), dtype=np.uint8)
+    out, seams, costs = api.carve(dev(img), W - k, **kw)
+    o_out, o_seams, o_costs = oracle.carve(img, W - k)
+    assert np.array_equal(host(seams), o_seams) and np.array_equal(host(costs), o_costs)
+    assert np.array_equal(host(out), o_out)
+
+
+@pytest.mark.parametrize("team", [1, 2, 3])
+@pytest.mark.parametrize("W", [257, 385, 505, 513, 954, 1403, 1852])
+def test_strip_edges(W, team):
+    """Widths that cross a strip boundary while they shrink, one workgroup to three."""
+    _check(150, W, 3, 6, alpha=5 if team == 2 else 256, team=team)
+
+
+@pytest.mark.parametrize("H", [1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 63, 64, 65, 66, 128, 129, 130, 260])
+@pytest.mark.parametrize("variant", [7, 9])
+def test_split_rows(H, variant):
+    """Heights around the split of the image in halves and in blocks."""
+    _check(H, 90, 1, 8, alpha=3, variant=variant, team=2 if H % 2 else 1)
+
+
+@pytest.mark.parametrize("C,W", [(1, 207), (1, 420), (2, 209), (3, 138), (3, 141), (4, 103), (4, 106), (3, 1400), (4, 1100)])
+@pytest.mark.parametrize("minside", [True, False])
+def test_row_shifts(C, W, minside):
+    """Every pixel size at the widths where rows stop sharing accesses, and where a row takes
+    several passes; moving either side or only the right one."""
+    _check(37, W, C, 20, minside=minside, team=1)
+
+
+@pytest.mark.parametrize("team", [1, 4])
+def test_path_leaves_its_window(team):
+    """A seam that runs diagonally across the image: the backtrack needs several rounds."""
+    H, W = 700, 1000
+    img = np.full((H, W, 1), 128, np.uint8)
+    img[::2, ::2] = 255
+    for y in range(H):  # a quiet diagonal of constant pixels, five wide
+        x = 100 + y
+        img[y, x:x + 5] = 128
+    log("diagonal seam", team)
+    out, seams, costs = api.carve(dev(img), W - 3, team=team)
+    o_out, o_seams, o_costs = oracle.carve(img, W - 3)
+    assert np.array_equal(host(seams), o_seams) and np.array_equal(host(costs), o_costs)
+    assert np.array_equal(host(out), o_out)
