@@ -6,8 +6,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <numeric>
-#include <queue>
 #include <vector>
 
 #include "../../include/sc.h"
@@ -46,7 +46,7 @@ static_assert(sizeof(sc::Ctl) == 128, "ctl size");
 static_assert(sc::kWsImgOffset + sizeof(sc::Img) <= sc::kWsHeadBytes, "a single image's descriptor fits the header");
 
 constexpr int kMaxCostBound = 8388000;  // H*510*C: the column cost must fit 23 bits
-constexpr int kDefaultTeamSingle = 8;   // workgroups carving one image (sc_carve)
+constexpr int kMaxTeamSingle = 16;      // largest team sc_carve and sc_dp_seam choose themselves
 constexpr int kDefaultTeamBatch = 16;   // largest team for one image of a batch
 
 sc_status check_image(int H, int W, int C, int pitch) {
@@ -99,6 +99,148 @@ sc::Img make_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long lon
 int resolve_variant(const sc_tune* t) {
     if (t && t->variant >= 0) return t->variant < sc::variant_count() ? t->variant : -1;
     return sc::default_variant();
+}
+
+// Microseconds one seam of an H x w image takes a team of G workgroups of nw waves: the sweep from
+// both ends (by strips of 128 columns, or of 448 where those are more than the waves), the walk
+// back over blocks of rows, the removal and the band of new energies.  Fitted to 25 sizes from 64 x 64 to
+// 2100 x 2100 with six team sizes each on an idle MI355X; the team it ranks first is within 4 % of
+// the fastest there, except on images of 64 rows that are wider than 500 columns.
+double seam_us(int H, int w, int G, int nw) {
+    const int tw = G * nw;
+    const auto strips = [](int cols, int win, int step) { return cols <= win ? 1 : (cols - win + step - 1) / step + 1; };
+    const double rows = H / 2 + 16;
+    const int n4 = 2 * strips(w, 256, 128), n8 = 2 * strips(w, 504, 448);
+    const double sweep = n4 <= tw || w <= 504
+                             ? rows * (0.047 + (n4 > 2 ? 0.0085 * std::max(0.0, (double)n4 / G - 2) : 0.0))
+                             : rows * (0.045 + 0.0175 * n8 / G);
+    const int each = (H + tw - 1) / tw, blocks = 2 * ((H + 63) / 64);
+    const double back = 4.5 + 4.8 * ((blocks + tw - 1) / tw - 1);
+    const double remove = 2.5 + each * (0.085 + (w <= 138 ? 0.2 : 0.45 + std::max(0, w - 600) * 0.00037));
+    return sweep + back + remove + (G > 1 ? 5.5 + 0.0012 * H + 0.002 * w : 0.0);
+}
+
+constexpr int kTeamSizes[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+
+// The team of a single image: the smallest that seam_us puts within 3 % of the fastest one.  At most
+// 16: four streams (the hardware queues of a process) then find room for a whole team each among the
+// 64 workgroups of an XCD, whatever order their workgroups arrive in.
+int single_team(int H, int w, int nw) {
+    double best = 1e30;
+    for (int g : kTeamSizes)
+        if (g <= kMaxTeamSingle) best = std::min(best, seam_us(H, w, g, nw));
+    for (int g : kTeamSizes)
+        if (seam_us(H, w, g, nw) <= 1.03 * best) return g;
+    return 1;
+}
+
+// A launch plan of a batch: the workgroups of every image and the order of the blocks.
+struct BatchPlan {
+    std::vector<int> team;               // workgroups per job
+    std::vector<int2> blk, teams;        // block -> (team, member), team -> (first of team_imgs, count)
+    std::vector<int> team_imgs;
+    double us = 0;                       // the time the plan should take
+};
+
+// Every image gets the smallest team that carves it within `limit` microseconds (or the one that
+// carves it fastest), from t[job * nsizes + size].  Teams come first, largest first and each on the XCD with the most free
+// workgroups, so that all of them are resident at once; the images of one workgroup follow, longest
+// first, each on the XCD (block index mod 8) that is free earliest.
+BatchPlan place_batch(const std::vector<double>& t, const std::vector<int>& cap, int n, double limit, int per_xcd) {
+    constexpr int ns = sizeof(kTeamSizes) / sizeof(kTeamSizes[0]);
+    BatchPlan p;
+    p.team.assign(n, 1);
+    std::vector<double> us(n);
+    std::vector<int> order(n);
+    std::iota(order.begin(), order.end(), 0);
+    for (int i = 0; i < n; ++i) {
+        int pick = 0;
+        for (int g = 0; g < ns && kTeamSizes[g] <= cap[i]; ++g) {
+            if (t[i * ns + g] < t[i * ns + pick]) pick = g;
+            if (t[i * ns + pick] <= limit) break;
+        }
+        p.team[i] = kTeamSizes[pick];
+        us[i] = t[i * ns + pick];
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return p.team[a] != p.team[b] ? p.team[a] > p.team[b] : us[a] > us[b];
+    });
+    std::vector<int2> col[8];             // the blocks of each XCD
+    std::vector<double> busy[8];          // when each of its workgroup slots is free: min-heaps
+    size_t first_single = 0;
+    for (; first_single < (size_t)n && p.team[order[first_single]] > 1; ++first_single) {
+        const int i = order[first_single];
+        int x = 0;
+        for (int c = 1; c < 8; ++c)
+            if (col[c].size() < col[x].size()) x = c;
+        if ((int)col[x].size() + p.team[i] > per_xcd) {  // no room for a resident team
+            p.team[i] = 1;
+            us[i] = t[i * ns];
+            continue;
+        }
+        for (int r = 0; r < p.team[i]; ++r) {
+            col[x].push_back(make_int2((int)p.teams.size(), r));
+            busy[x].push_back(us[i]);
+        }
+        p.teams.push_back(make_int2((int)p.team_imgs.size(), 1));
+        p.team_imgs.push_back(i);
+        p.us = std::max(p.us, us[i]);
+    }
+    order.erase(std::remove_if(order.begin(), order.end(), [&](int i) { return p.team[i] > 1; }), order.end());
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return us[a] > us[b]; });
+    for (auto& h : busy) {
+        h.resize(per_xcd, 0.0);
+        std::make_heap(h.begin(), h.end(), std::greater<double>());
+    }
+    for (int i : order) {
+        int x = 0;
+        for (int c = 1; c < 8; ++c)
+            if (busy[c][0] < busy[x][0] || (busy[c][0] == busy[x][0] && col[c].size() < col[x].size())) x = c;
+        std::pop_heap(busy[x].begin(), busy[x].end(), std::greater<double>());
+        busy[x].back() += us[i];
+        p.us = std::max(p.us, busy[x].back());
+        std::push_heap(busy[x].begin(), busy[x].end(), std::greater<double>());
+        col[x].push_back(make_int2((int)p.teams.size(), 0));
+        p.teams.push_back(make_int2((int)p.team_imgs.size(), 1));
+        p.team_imgs.push_back(i);
+    }
+    size_t rows = 0;
+    for (const auto& c : col) rows = std::max(rows, c.size());
+    for (size_t r = 0; r < rows; ++r)
+        for (const auto& c : col) p.blk.push_back(r < c.size() ? c[r] : make_int2(-1, -1));
+    while (!p.blk.empty() && p.blk.back().x < 0) p.blk.pop_back();
+    return p;
+}
+
+// The plan whose limit gives the shortest estimated time.  max_team bounds the teams; the image with
+// the longest chain alone may have twice that.  Teams sized by an image's share of the pixels instead fill
+// every slot, and the images of one workgroup only begin when the teams end: 256 images up to
+// 2000 x 2000 took 204 ms that way and take 170 ms here, 512 thumbnails up to 250 x 250 took 3.3 ms and take 2.7.
+// (All the images at once wait for memory, so they take 2 to 3 times the estimate; the order of the
+// plans holds: limits of 0.8, 1.1, 1.6 and 2 times the chosen one took 205, 185, 185 and 203 ms.)
+BatchPlan plan_batch(const sc_job* jobs, int n, int max_team, int per_xcd, int nw) {
+    constexpr int ns = sizeof(kTeamSizes) / sizeof(kTeamSizes[0]);
+    std::vector<double> t((size_t)n * ns);
+    std::vector<int> cap(n, std::min(max_team, per_xcd));
+    double longest = 0, shortest = 0, total = 0;
+    int crit = 0;
+    for (int i = 0; i < n; ++i) {
+        const int k = jobs[i].W - jobs[i].target_w;
+        double best = 1e30;
+        for (int g = 0; g < ns; ++g) {
+            t[i * ns + g] = k * seam_us(jobs[i].H, jobs[i].W - k / 2, kTeamSizes[g], nw);
+            if (kTeamSizes[g] <= cap[i]) best = std::min(best, t[i * ns + g]);
+        }
+        if (t[i * ns] > longest) longest = t[i * ns], crit = i;
+        shortest = std::max(shortest, best);
+    }
+    if (max_team > 1 && n > 1) cap[crit] = std::min(std::min(2 * max_team, 32), per_xcd);
+    BatchPlan best = place_batch(t, cap, n, longest, per_xcd);
+    for (double limit = 0.85 * longest; limit > 0.3 * shortest; limit *= 0.85) {
+        BatchPlan p = place_batch(t, cap, n, limit, per_xcd);
+        if (p.us < best.us) best = std::move(p);
+    }
+    return best;
 }
 
 }  // namespace
@@ -169,14 +311,15 @@ sc_status sc_dp_seam(const int32_t* energy, int H, int W, int32_t* seam, int64_t
     const size_t need = sc_workspace_bytes(H, W, 1);
     if (ws_bytes < need) return fail(SC_ENOMEM, "workspace %zu < %zu bytes", ws_bytes, need);
     const int v = sc::default_variant();
+    const int G = single_team(H, W, sc::variant(v).threads / 64);
     char* base = static_cast<char*>(ws);
     sc::Ctl* ctl = reinterpret_cast<sc::Ctl*>(base + sizeof(WsHead));
     // with dirs_out the sweep runs down over all rows (mode 2) and writes the map itself
     sc::Img d = make_img(nullptr, dirs_out, H, W, 1, W, W > 1 ? W - 1 : 1, seam, cost, base + ctl_region(1), ctl,
-                         sc::variant(v).kr, 1, dirs_out ? 2 : 1);
+                         sc::variant(v).kr, G, dirs_out ? 2 : 1);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = sc::launch_prepare_from_i32(d, energy, st);
-    if (e == hipSuccess) e = sc::launch_carve_single(d, v, 1, 0, st);
+    if (e == hipSuccess) e = sc::launch_carve_single(d, v, G, 0, st);
     if (e != hipSuccess) return hip_fail(e, "dp launch");
     return ok();
 }
@@ -215,7 +358,7 @@ sc_status sc_carve(uint8_t* img, int H, int W, int C, int target_w, int pitch, i
     if (ws_bytes < need) return fail(SC_ENOMEM, "workspace %zu < %zu bytes", ws_bytes, need);
     const int v = resolve_variant(tune);
     if (v < 0) return fail(SC_EINVAL, "unknown kernel variant %d", tune->variant);
-    const int G = tune && tune->team > 0 ? tune->team : kDefaultTeamSingle;
+    const int G = tune && tune->team > 0 ? tune->team : single_team(H, W - (W - target_w) / 2, sc::variant(v).threads / 64);
     if (G > 32) return fail(SC_EUNSUPPORTED, "team of %d workgroups > 32", G);
     char* base = static_cast<char*>(ws);
     sc::Ctl* ctl = reinterpret_cast<sc::Ctl*>(base + sizeof(WsHead));
@@ -355,85 +498,15 @@ sc_status sc_batch_prepare(const sc_job* jobs, int n, const sc_tune* tune, void*
     int G = tune && tune->team > 0 ? tune->team : kDefaultTeamBatch;
     if (G > 32) return fail(SC_EUNSUPPORTED, "team of %d workgroups > 32", G);
 
-    // work of every image: pixel-seams = sum over seams of the current image's pixels
-    std::vector<double> work(n);
-    for (int i = 0; i < n; ++i) {
-        const double k = jobs[i].W - jobs[i].target_w;
-        work[i] = (double)jobs[i].H * (k * jobs[i].W - k * (k - 1) / 2) + 1.0;
-    }
-    std::vector<int> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
-
-    // Team sizes.  An image whose work exceeds the average work per workgroup slot gets a team
-    // of up to G workgroups on one XCD (their blocks come first in the grid, so every team is
-    // resident at once); every other image gets one workgroup, launched longest first so the
-    // dispatcher hands the next image to whichever slot frees up.
     int dev = 0, ncu = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he == hipSuccess) he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (he != hipSuccess) return hip_fail(he, "device query");
-    const int per_cu = std::max(1, sc::carve_blocks_per_cu(v));
-    const int per_xcd = per_cu * ncu / 8;
-    double total = 0;
-    for (double x : work) total += x;
-    const double per_slot = total / std::max(1, per_cu * ncu);
-    std::vector<int> gsz(n, 1);
-    if (G > 1)
-        for (int i = 0; i < n; ++i) gsz[i] = (int)std::min<double>(G, std::max(1.0, std::ceil(work[i] / per_slot)));
-    // The image with the longest chain of seams x rows sets the batch time; it alone gets twice
-    // the largest team (its removal and band work split over more waves), room permitting.
-    if (G > 1 && n > 1) {
-        int crit = 0;
-        double cbest = -1;
-        for (int i = 0; i < n; ++i) {
-            const double c = (double)(jobs[i].W - jobs[i].target_w) * (jobs[i].H + 64);
-            if (c > cbest) cbest = c, crit = i;
-        }
-        gsz[crit] = std::min(std::min(2 * G, 32), per_xcd);
-    }
-    std::vector<int2> blk, teams;
-    std::vector<int> team_imgs;
-    int slots[8] = {0};
-    std::vector<std::pair<int, int2>> placed;
-    int nb_team = 0;
-    for (int i : order) {
-        if (gsz[i] < 2) continue;
-        // the XCD with the most free slots
-        int x = 0;
-        for (int c = 1; c < 8; ++c)
-            if (slots[c] < slots[x]) x = c;
-        if (slots[x] + gsz[i] > per_xcd) {
-            gsz[i] = 1;  // no room for a resident team: carve it with one workgroup
-            continue;
-        }
-        const int t = (int)teams.size();
-        teams.push_back(make_int2((int)team_imgs.size(), 1));
-        team_imgs.push_back(i);
-        for (int r = 0; r < gsz[i]; ++r) {
-            const int b = x + 8 * (slots[x] + r);
-            placed.push_back({b, make_int2(t, r)});
-            nb_team = std::max(nb_team, b + 1);
-        }
-        slots[x] += gsz[i];
-    }
-    blk.assign(nb_team, make_int2(-1, -1));
-    for (auto& pr : placed) blk[pr.first] = pr.second;
-    // one workgroup per remaining image, in order of decreasing chain (seams x rows): a single
-    // workgroup's carve time follows its row chain more than its pixel work (a tall narrow image
-    // has little work but a long chain), and the longest must start first
-    std::vector<int> singles;
-    for (int i : order)
-        if (gsz[i] < 2) singles.push_back(i);
-    std::stable_sort(singles.begin(), singles.end(), [&](int a, int b) {
-        return (double)(jobs[a].W - jobs[a].target_w) * jobs[a].H > (double)(jobs[b].W - jobs[b].target_w) * jobs[b].H;
-    });
-    for (int i : singles) {
-        const int t = (int)teams.size();
-        teams.push_back(make_int2((int)team_imgs.size(), 1));
-        team_imgs.push_back(i);
-        blk.push_back(make_int2(t, 0));
-    }
+    const int per_xcd = std::max(1, sc::carve_blocks_per_cu(v) * ncu / 8);
+    const BatchPlan plan = plan_batch(jobs, n, G, per_xcd, sc::variant(v).threads / 64);
+    const std::vector<int>& gsz = plan.team;
+    const std::vector<int2>&blk = plan.blk, &teams = plan.teams;
+    const std::vector<int>& team_imgs = plan.team_imgs;
 
     // host image of the plan region
     const size_t off_imgs = ctl_region(n);
@@ -524,19 +597,26 @@ int sc_read_status(const void* ws, uint32_t* flags, int max_n) {
         fail(SC_EHIP, "device synchronize failed");
         return -1;
     }
-    WsHead h;
-    if (hipMemcpy(&h, ws, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess || h.magic != kMagic || h.n < 1) {
+    // the head and the first image's flags in one copy: all of them for a single image
+    struct {
+        WsHead h;
+        sc::Ctl c;
+    } first;
+    static_assert(sizeof(first) == sizeof(WsHead) + sizeof(sc::Ctl), "no gap");
+    if (hipMemcpy(&first, ws, sizeof(first), hipMemcpyDeviceToHost) != hipSuccess || first.h.magic != kMagic ||
+        first.h.n < 1) {
         fail(SC_EINVAL, "not a prepared workspace");
         return -1;
     }
-    const int n = std::min(h.n, max_n);
-    std::vector<sc::Ctl> c(n);
-    if (hipMemcpy(c.data(), static_cast<const char*>(ws) + sizeof(WsHead), n * sizeof(sc::Ctl),
-                  hipMemcpyDeviceToHost) != hipSuccess) {
+    const int n = std::min(first.h.n, max_n);
+    flags[0] = first.c.status;
+    std::vector<sc::Ctl> c(n - 1);
+    if (n > 1 && hipMemcpy(c.data(), static_cast<const char*>(ws) + sizeof(first), (n - 1) * sizeof(sc::Ctl),
+                           hipMemcpyDeviceToHost) != hipSuccess) {
         fail(SC_EHIP, "status copy failed");
         return -1;
     }
-    for (int i = 0; i < n; ++i) flags[i] = c[i].status;
+    for (int i = 1; i < n; ++i) flags[i] = c[i - 1].status;
     ok();
     return n;
 }

@@ -60,3 +60,16 @@ def test_path_leaves_its_window(team):
     o_out, o_seams, o_costs = oracle.carve(img, W - 3)
     assert np.array_equal(host(seams), o_seams) and np.array_equal(host(costs), o_costs)
     assert np.array_equal(host(out), o_out)
+
+
+@pytest.mark.parametrize("H,W", [(1, 5), (2, 900), (63, 64), (65, 513), (300, 1403), (700, 257), (1100, 700)])
+@pytest.mark.parametrize("dirs", [False, True])
+def test_one_seam_by_a_team(H, W, dirs):
+    """The seam of a given energy map, by the team its size gets, with and without the direction map."""
+    e = np.random.default_rng(H * 7 + W).integers(0, 12, size=(H, W)).astype(np.int32)
+    want, cost, _, D = oracle.dp_seam(e, full=True)
+    got = api.dp_seam(dev(e), dirs=dirs)
+    assert np.array_equal(host(got[0]), want)
+    assert int(host(got[1])[0]) == cost
+    if dirs:
+        assert np.array_equal(host(got[2])[1:], D[1:])
