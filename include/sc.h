@@ -110,8 +110,8 @@ sc_status sc_transpose_u8(const uint8_t* src, int H, int W, int C, int src_pitch
 
 /* Launch shape of the persistent carve kernel; NULL selects the built-in choice. */
 typedef struct {
-    int team;    /* workgroups working together on one image (0 = default: 8 for sc_carve,
-                    at most 16 per image in a batch; teams run on one XCD) */
+    int team;    /* workgroups working together on one image (0 = default: by the image's
+                    size, at most 16; teams run on one XCD); in a batch the largest team */
     int variant; /* kernel variant id (see sc_variant_count); -1 = default */
     int flags;   /* SC_TUNE_* bits */
 } sc_tune;
@@ -261,11 +261,8 @@ sc_status sc_carve_batch(const sc_job* jobs, int n, const sc_tune* tune, void* w
  * outside the row is clamped to it (so a border pixel costs its difference to
  * the pixel that becomes the border).  Ties, backtrack, removal and the seam
  * loop are those of sc_carve; the costs are recomputed from the current pixels
- * for every seam.  A team of 256-thread workgroups on one XCD carves one
- * image: each DP member computes 976 columns and owns the middle 752; every
- * second 56-row phase the members exchange the keys of the 112 columns on
- * each side.  sc_carve_forward sizes the team so that every wave walks and
- * removes about 8 rows of a seam (at most 32 workgroups).
+ * for every seam.  A team of at most 32 workgroups on one XCD carves one image;
+ * its size follows from the image's (an estimate of a seam's time).
  *
  * sc_carve_forward: arguments as sc_carve (no tune); seams_out/costs_out
  *   (nullable) receive every seam and its forward cost.  ws: at least
@@ -276,7 +273,9 @@ sc_status sc_carve_batch(const sc_job* jobs, int n, const sc_tune* tune, void* w
  *   enqueues the copy-in pass and the carve (no allocation, no host copy; the
  *   info must come from sc_forward_batch_prepare).  Per-image clocks:
  *   sc_read_times on the same ws.
- * Limits: those of sc_carve, plus W <= 8192 and H*roundup(W*C, 64) < 2^31.
+ * Limits: those of sc_carve, plus W <= 8192 and H*roundup(W*C, 64) < 2^31; a
+ *   batch holds at most 512 units (images of up to 968 columns are one, wider
+ *   ones one per 752 columns).
  * Errors: SC_EINVAL, SC_ENOMEM (workspace too small), SC_EUNSUPPORTED, SC_EHIP.
  */
 size_t sc_forward_workspace_bytes(int H, int W, int C);

@@ -47,6 +47,7 @@ static_assert(sc::kWsImgOffset + sizeof(sc::Img) <= sc::kWsHeadBytes, "a single 
 
 constexpr int kMaxCostBound = 8388000;  // H*510*C: the column cost must fit 23 bits
 constexpr int kMaxTeamSingle = 16;      // largest team sc_carve and sc_dp_seam choose themselves
+constexpr int kMaxTeamForward = 32;     // and sc_carve_forward
 constexpr int kDefaultTeamBatch = 16;   // largest team for one image of a batch
 
 sc_status check_image(int H, int W, int C, int pitch) {
@@ -104,8 +105,8 @@ int resolve_variant(const sc_tune* t) {
 // Microseconds one seam of an H x w image takes a team of G workgroups of nw waves: the sweep from
 // both ends (by strips of 128 columns, or of 448 where those are more than the waves), the walk
 // back over blocks of rows, the removal and the band of new energies.  Fitted to 25 sizes from 64 x 64 to
-// 2100 x 2100 with six team sizes each on an idle MI355X; the team it ranks first is within 4 % of
-// the fastest there, except on images of 64 rows that are wider than 500 columns.
+// 2100 x 2100 with six team sizes each on an idle MI355X; the team it ranks first is within 6 % of
+// the fastest there.  Forward energy takes up to a third more or less and ranks the teams the same way.
 double seam_us(int H, int w, int G, int nw) {
     const int tw = G * nw;
     const auto strips = [](int cols, int win, int step) { return cols <= win ? 1 : (cols - win + step - 1) / step + 1; };
@@ -117,18 +118,18 @@ double seam_us(int H, int w, int G, int nw) {
     const int each = (H + tw - 1) / tw, blocks = 2 * ((H + 63) / 64);
     const double back = 4.5 + 4.8 * ((blocks + tw - 1) / tw - 1);
     const double remove = 2.5 + each * (0.085 + (w <= 138 ? 0.2 : 0.45 + std::max(0, w - 600) * 0.00037));
-    return sweep + back + remove + (G > 1 ? 5.5 + 0.0012 * H + 0.002 * w : 0.0);
+    return sweep + back + remove + (G > 1 ? 5.5 + 0.0012 * H + 0.002 * w : std::min(3.5, 0.006 * w));
 }
 
 constexpr int kTeamSizes[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
 // The team of a single image: the smallest that seam_us puts within 3 % of the fastest one.  At most
-// 16: four streams (the hardware queues of a process) then find room for a whole team each among the
+// 16 by default: four streams (the hardware queues of a process) then find room for a whole team each among the
 // 64 workgroups of an XCD, whatever order their workgroups arrive in.
-int single_team(int H, int w, int nw) {
+int single_team(int H, int w, int nw, int most = kMaxTeamSingle) {
     double best = 1e30;
     for (int g : kTeamSizes)
-        if (g <= kMaxTeamSingle) best = std::min(best, seam_us(H, w, g, nw));
+        if (g <= most) best = std::min(best, seam_us(H, w, g, nw));
     for (int g : kTeamSizes)
         if (seam_us(H, w, g, nw) <= 1.03 * best) return g;
     return 1;
@@ -801,33 +802,32 @@ extern "C" sc_status sc_slots_step_teams(const void* table, int table_slots, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Forward energy (sec. "Forward Energy Calculation"): teams of 256-thread workgroups on one XCD,
-// a dword per working pixel, no energy plane.
+// Forward energy (sec. "Forward Energy Calculation"): the carve engine on a dword per working pixel,
+// no energy plane.
 namespace {
 
 struct FwdLayout {
-    size_t dirs, anc, xq, amk, wk, total;
-    int db, wp, xw, P;
+    size_t anc, xq, seam, ro, wk, total;
+    int wp, xw, P;
 };
 
 FwdLayout fwd_layout(int H, int W, int C) {
     (void)C;
     FwdLayout L;
-    L.P = (H + sc::kFwtPhaseRows - 1) / sc::kFwtPhaseRows;
-    L.db = (int)sc::align_up((size_t)(W + 3) / 4, 16);  // direction bytes (4 columns each) per row
-    L.wp = (int)sc::align_up((size_t)(W + 1) * 4 + 16, 16);  // one dword per pixel, a copy of the last, a gap
-    L.xw = (int)sc::align_up((size_t)W + 8, 64);
+    L.P = sc::key_rows(H, sc::kFwdKR, 0);
+    L.wp = (int)sc::align_up((size_t)W * 4 + 16, 16);  // 16 bytes between rows: the row shifter's last slot
+    L.xw = sc::key_pitch(W);
     size_t off = 0;
-    L.dirs = off;
-    off = sc::align_up(off + (size_t)((H + 3) / 4) * L.db * 4, sc::kAlign);  // rows grouped by four
     L.anc = off;
-    off = sc::align_up(off + (size_t)L.P * W, sc::kAlign);
+    off = sc::align_up(off + (size_t)L.P * L.xw, sc::kAlign);
     L.xq = off;
-    off = sc::align_up(off + (size_t)2 * L.xw * 4, sc::kAlign);
-    L.amk = off;
-    off = sc::align_up(off + 2 * sizeof(unsigned long long), sc::kAlign);
-    L.wk = off;
-    off = sc::align_up(off + (size_t)H * L.wp + sc::kFwdSlack, sc::kAlign);
+    off = sc::align_up(off + (size_t)L.P * L.xw * 4, sc::kAlign);
+    L.seam = off;
+    off = sc::align_up(off + (size_t)H * 4, sc::kAlign);
+    L.ro = off;
+    off = sc::align_up(off + (size_t)H * 4, sc::kAlign);
+    L.wk = off + 64;  // the row shifter may write up to 16 bytes below a plane
+    off = sc::align_up(L.wk + (size_t)(H + 1) * L.wp + 64, sc::kAlign);  // and a row of zeros
     L.total = off;
     return L;
 }
@@ -842,17 +842,7 @@ sc_status check_fwd_image(int H, int W, int C, int pitch) {
     return SC_OK;
 }
 
-// DP members of a forward team (the members whose windows cover the columns) and the team size
-// whose waves (four per member) each walk and remove at most 4/rows_per_wave_phases phases of
-// rows (half a phase by default).
-int fwd_dp_members(int W) { return W <= sc::kFwtSingle ? 1 : (W + sc::kFwtOwned - 1) / sc::kFwtOwned; }
-int fwd_team_target(int H, int W, int rows_per_wave_phases = 2) {
-    const int P = (H + sc::kFwtPhaseRows - 1) / sc::kFwtPhaseRows;
-    return std::min(32, std::max(fwd_dp_members(W), (P + rows_per_wave_phases - 1) / rows_per_wave_phases));
-}
-// A single image has the device to itself: its team grows until every wave walks and removes
-// about 8 rows (measured at 1920x1080: 97 ms with 32 workgroups, 99 ms with 20, 109 ms with 10).
-int fwd_single_team(int H, int W) { return std::min(32, std::max(fwd_dp_members(W), (H + 31) / 32)); }
+int fwd_units(int W) { return W <= sc::kFwdUnitFirst ? 1 : (W + sc::kFwdUnitCols - 1) / sc::kFwdUnitCols; }
 
 sc::Img make_fwd_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long long pitch, int target_w,
                      int32_t* seams_out, int64_t* costs_out, char* base, sc::Ctl* ctl, int G) {
@@ -868,25 +858,22 @@ sc::Img make_fwd_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long
     d.target_w = target_w;
     d.seams_out = seams_out;
     d.costs_out = reinterpret_cast<long long*>(costs_out);
-    d.dirs = reinterpret_cast<uint8_t*>(base + L.dirs);
     d.anc = reinterpret_cast<int8_t*>(base + L.anc);
     d.xq = reinterpret_cast<uint32_t*>(base + L.xq);
     d.xw = L.xw;
-    d.amk = reinterpret_cast<unsigned long long*>(base + L.amk);
+    d.seam = reinterpret_cast<int32_t*>(base + L.seam);
+    d.ro = reinterpret_cast<int32_t*>(base + L.ro);
     d.wk = reinterpret_cast<uint8_t*>(base + L.wk);
     d.wp = L.wp;
-    d.db = L.db;
+    d.e = reinterpret_cast<uint16_t*>(d.wk);
+    d.ep = L.wp / 2;
+    d.minside = 1;
     d.P = L.P;
     d.amin = &ctl->amin;
     d.bar = &ctl->bar;
     d.status = &ctl->status;
     d.G = G;
     return d;
-}
-
-double fwd_work(const sc_job& j) {  // pixel-seams: rows times the widths the seams are taken from
-    const double k = j.W - j.target_w;
-    return (double)j.H * k * (j.W + j.target_w + 1) / 2.0;
 }
 
 }  // namespace
@@ -908,7 +895,7 @@ extern "C" sc_status sc_carve_forward(uint8_t* img, int H, int W, int C, int tar
     char* base = static_cast<char*>(ws);
     sc::Ctl* ctl = reinterpret_cast<sc::Ctl*>(base + sizeof(WsHead));
     const size_t off_img = ctl_region(1);
-    const int G = fwd_single_team(H, W);
+    const int G = single_team(H, W - (W - target_w) / 2, sc::kFwdThreads / 64, kMaxTeamForward);
     const sc::Img d = make_fwd_img(src, img, H, W, C, pitch, target_w, seams_out, costs_out,
                                    base + off_img + sc::align_up(sizeof(sc::Img), sc::kAlign), ctl, G);
     // header (magic, one image) and the descriptor, which the kernels read from the workspace
@@ -955,53 +942,21 @@ extern "C" sc_status sc_forward_batch_prepare(const sc_job* jobs, int n, void* w
     const size_t need = sc_forward_batch_workspace_bytes(jobs, n);
     if (ws_bytes < need) return fail(SC_ENOMEM, "workspace %zu < %zu bytes", ws_bytes, need);
 
-    // Teams.  Every team's workgroups must be resident at once on one XCD (they wait for each
-    // other), so the whole plan fits the device's resident workgroups: every image first gets its
-    // DP members, then images in order of decreasing work grow toward a team in which every wave
-    // walks and removes at most one phase of rows.
     int dev = 0, ncu = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he == hipSuccess) he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (he != hipSuccess) return hip_fail(he, "device query");
-    // two thirds of the occupancy the runtime reports: a plan that needed every last slot could
-    // leave a team partly resident behind others (measured: planning for 3 workgroups per compute
-    // unit made teams wait out their barriers)
-    const int per_xcd = std::max(1, 2 * sc::fwt_blocks_per_cu() * ncu / 3 / 8);
-    std::vector<int> order(n), gsz(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fwd_work(jobs[a]) > fwd_work(jobs[b]); });
-    long long used = 0;
-    for (int i = 0; i < n; ++i) used += gsz[i] = fwd_dp_members(jobs[i].W);
-    const long long cap = 8ll * per_xcd;
-    if (used > cap)
-        return fail(SC_EUNSUPPORTED, "%lld workgroups of forward teams exceed the %lld resident ones; split the batch",
-                    used, cap);
-    // grow the teams while room is left: the image with the most work first toward half a phase of
-    // rows per wave (it sets the batch time), then every image toward a phase per wave, then toward
-    // half a phase, longest first
-    auto grow_to = [&](int i, int per) {
-        const int grow = std::min<long long>(fwd_team_target(jobs[i].H, jobs[i].W, per) - gsz[i], cap - used);
-        if (grow > 0) gsz[i] += grow, used += grow;
-    };
-    grow_to(order[0], 2);
-    for (int per : {4, 2})
-        for (int i : order) grow_to(i, per);
-    // placement: longest first, each team on the XCD with the most free slots
-    int slots[8] = {0};
-    std::vector<int2> blk;
-    for (int i : order) {
-        int x = 0;
-        for (int c = 1; c < 8; ++c)
-            if (slots[c] < slots[x]) x = c;
-        while (slots[x] + gsz[i] > per_xcd && gsz[i] > fwd_dp_members(jobs[i].W)) --gsz[i];
-        if (slots[x] + gsz[i] > per_xcd) return fail(SC_EUNSUPPORTED, "no XCD has room for the team of job %d", i);
-        for (int r = 0; r < gsz[i]; ++r) {
-            const size_t b = (size_t)x + 8 * (size_t)(slots[x] + r);
-            if (blk.size() <= b) blk.resize(b + 1, make_int2(-1, -1));
-            blk[b] = make_int2(i, r);
-        }
-        slots[x] += gsz[i];
-    }
+    long long units = 0;
+    for (int i = 0; i < n; ++i) units += fwd_units(jobs[i].W);
+    if (units > sc::kFwdBatchUnits)
+        return fail(SC_EUNSUPPORTED, "%lld units of %d columns exceed the %d of a forward batch; split the batch", units,
+                    sc::kFwdUnitCols, sc::kFwdBatchUnits);
+    const int per_xcd = std::max(1, sc::fwt_blocks_per_cu() * ncu / 8);
+    const BatchPlan plan = plan_batch(jobs, n, kDefaultTeamBatch, per_xcd, sc::kFwdThreads / 64);
+    const std::vector<int>& gsz = plan.team;
+    std::vector<int2> blk(plan.blk);
+    for (int2& b : blk)
+        if (b.x >= 0) b.x = plan.team_imgs[plan.teams[b.x].x];
     if (blk.size() > (size_t)8 * 32 * n) return fail(SC_EUNSUPPORTED, "plan too large");
     const size_t off_imgs = ctl_region(n);
     const size_t off_blk = off_imgs + sc::align_up((size_t)n * sizeof(sc::Img), sc::kAlign);

@@ -87,6 +87,11 @@ __device__ __forceinline__ void load_ev(uint64_t (&e)[(N + 3) / 4], __amdgpu_buf
         const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, (int)off, (int)soff, COH ? 16 : 0);
         e[0] = ((uint64_t)v[1] << 32) | v[0];
         e[1] = ((uint64_t)v[3] << 32) | v[2];
+        if constexpr (N == 16) {
+            const v4u u = __builtin_amdgcn_raw_buffer_load_b128(re, (int)(off + 16u), (int)soff, COH ? 16 : 0);
+            e[2] = ((uint64_t)u[1] << 32) | u[0];
+            e[3] = ((uint64_t)u[3] << 32) | u[2];
+        }
     }
 }
 
@@ -122,8 +127,11 @@ __device__ __forceinline__ uint32_t seam_tag(int k) { return 1u + (uint32_t)k % 
 // The same of a row's seam column (16 bits, columns below 65535), in the upper half of its word.
 __device__ __forceinline__ uint32_t seam_word(int k) { return ((uint32_t)k + 1u) << 16; }
 
-template <int R>
+// What the sweep and the backtrack read: the plane of 16-bit energies or, FWD (forward energy), the
+// current pixels, a dword each; CB bytes per column.
+template <int R, bool FWD>
 struct Rows {
+    static constexpr uint32_t CB = FWD ? 4 : 2;
     // The rows of one half (h = 0: from the top down to the split row, 1: from the bottom up).
     // Virtual row v of a half is image row v - pad counted from the half's border; the rows below
     // pad do not exist and read the plane's row of zeros (row H), so that the half is a whole number
@@ -147,7 +155,7 @@ struct Rows {
                                                        __amdgpu_buffer_rsrc_t rro) {
         const int i = min(v - x.pad, x.n - 1);
         const int r = i < 0 ? d.H : h ? d.H - 1 - i : i;
-        return (uint32_t)r * (uint32_t)d.ep * 2u + 2u * buf_ld32<COH>(rro, i < 0 ? kBufDrop : (uint32_t)r * 4u);
+        return (uint32_t)r * (uint32_t)d.ep * 2u + CB * buf_ld32<COH>(rro, i < 0 ? kBufDrop : (uint32_t)r * 4u);
     }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t energy_rsrc(const Img& d) {
         return make_rsrc(d.e, (uint32_t)(d.H + 1) * (uint32_t)d.ep * 2u);
@@ -168,14 +176,20 @@ struct Rows {
 // ancestor offsets a row is a v_min3 and an add per column and two wave shifts (15 instructions for
 // 256 columns), and the two ends halve the chain.  Rows are loaded a block ahead, one wait per eight
 // rows.  1920 x 1080 by 32 workgroups: 27 us per seam where the one-ended sweep with directions took 106.
-template <int CPL, int KR, int R>
-struct Sweep : Rows<R> {
-    using Half = typename Rows<R>::Half;
-    using Rows<R>::half_of;
-    using Rows<R>::energy_rsrc;
+template <int CPL, int KR, int R, bool FWD>
+struct Sweep : Rows<R, FWD> {
+    using Half = typename Rows<R, FWD>::Half;
+    using Rows<R, FWD>::half_of;
+    using Rows<R, FWD>::energy_rsrc;
+    using Rows<R, FWD>::CB;
+    static constexpr int ND = FWD ? CPL / 2 : (CPL + 3) / 4;  // 64-bit words of a lane's columns
+    // FWD needs the row above too, so a row's registers are loaded anew only after the next row.
+    static constexpr int LATE = FWD ? 1 : 0;
+    // The cost of a missing parent, more than any real one; FWD adds to it and must not wrap.
+    static constexpr uint32_t INF = FWD ? 0x40000000u : 0xFFFFFFFFu;
     static constexpr int WIN = 64 * CPL;    // columns a wave computes
     static constexpr int S = WIN - 2 * KR;  // columns a strip adds: KR ghost columns on each side
-    static constexpr int PF = R == 32 ? (CPL == 8 ? 16 : 32) : R;  // rows of energy prefetched ahead
+    static constexpr int PF = R == 32 ? (FWD ? 64 : 128) / CPL : R;  // rows prefetched ahead
     static_assert(CPL == 2 || CPL == 4 || CPL == 8, "one energy load per lane and row");
     static_assert(KR % R == 0 && R % PF == 0 && PF % 8 == 0 && KR <= 64 && R <= 63 && KR % CPL == 0 && S > 0, "phase shape");
 
@@ -184,7 +198,7 @@ struct Sweep : Rows<R> {
     // four times as much, and strips this wide run several to a compute unit).  A lane takes the dword
     // after its own from the next lane; lane 63 has none, so it is ghost columns, or past the image:
     // the last strip's window runs eight columns past w, and the first of them stays all ones.
-    static constexpr bool GRID = CPL == 8;
+    static constexpr bool GRID = CPL == 8 && !FWD;  // (a row of pixels starts on the grid)
     static constexpr int WINR = GRID ? WIN - CPL : WIN;  // columns of the last strip's window in the image
 
     static __device__ __forceinline__ int strips(int w) { return w <= WINR ? 1 : (w - WINR + S - 1) / S + 1; }
@@ -216,14 +230,14 @@ struct Sweep : Rows<R> {
         it.v0 = __builtin_amdgcn_readfirstlane(it.v0);
         it.v1 = __builtin_amdgcn_readfirstlane(it.v1);
         it.col0 = base + lane * CPL;
-        it.off = GRID ? (uint32_t)lane * (2u * CPL) : (uint32_t)(it.col0 < w ? it.col0 : 0) * 2u;
+        it.off = GRID ? (uint32_t)lane * (2u * CPL) : (uint32_t)(it.col0 < w ? it.col0 : 0) * CB;
         return it;
     }
 
     // EDGE: the one strip of an image narrower than a window (columns from w on are kept all ones).
     template <bool EDGE>
     static __device__ __forceinline__ void cost_step(uint32_t (&Q)[CPL], uint32_t& left, uint32_t& right,
-                                                     const uint64_t (&raw)[(CPL + 3) / 4], uint32_t odd, const uint32_t (&em)[CPL]) {
+                                                     const uint64_t (&raw)[ND], uint32_t odd, const uint32_t (&em)[CPL]) {
         // Neighbours of the lane's first and last column come from lanes -1 and +1.  Lane 0's left and
         // lane 63's right keep all ones: a window's side is either the image's edge, where that is the
         // missing parent, or ghost columns, where a wrong value moves one column inward per row and
@@ -255,6 +269,42 @@ struct Sweep : Rows<R> {
         }
     }
 
+    // The same row of the forward energy: the parents' keys cost the pairs of pixels that become
+    // neighbours (D = one v_sad_u8 on packed channels, which adds the key too).  The row formula
+    // is the same upward: the child at the left costs D(left pixel, pixel below), the one at the right
+    // D(right pixel, pixel below).  A pixel missing at a window's side is the lane's own: at the image's
+    // edge that is the clamp, elsewhere the side is ghost columns.  last: columns whose right neighbour
+    // is past the image (EDGE).
+    template <bool EDGE>
+    static __device__ __forceinline__ void forward_step(uint32_t (&Q)[CPL], uint32_t& left, uint32_t& right,
+                                                        const uint64_t (&above)[ND], const uint64_t (&raw)[ND],
+                                                        const uint32_t (&em)[CPL], const bool (&last)[CPL]) {
+        uint32_t p[CPL], P[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            p[c] = (uint32_t)(raw[c >> 1] >> ((c & 1) * 32));
+            P[c] = (uint32_t)(above[c >> 1] >> ((c & 1) * 32));
+        }
+        left = (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)Q[CPL - 1], 0x138, 0xf, 0xf, false);
+        right = (uint32_t)__builtin_amdgcn_update_dpp((int)right, (int)Q[0], 0x130, 0xf, 0xf, false);
+        const uint32_t pl = (uint32_t)__builtin_amdgcn_update_dpp((int)p[0], (int)p[CPL - 1], 0x138, 0xf, 0xf, false);
+        const uint32_t pr = (uint32_t)__builtin_amdgcn_update_dpp((int)p[CPL - 1], (int)p[0], 0x130, 0xf, 0xf, false);
+        uint32_t n[CPL];
+#pragma unroll
+        for (int i = 0; i < CPL; ++i) {
+            const int k = i == 0 ? 0 : i == 1 ? CPL - 1 : i - 1;
+            const uint32_t l = k ? p[k - 1] : pl;
+            uint32_t r = k + 1 < CPL ? p[k + 1] : pr;
+            if (EDGE) r = last[k] ? p[k] : r;
+            const uint32_t a = __builtin_amdgcn_sad_u8(P[k], l, k ? Q[k - 1] : left);
+            const uint32_t b = __builtin_amdgcn_sad_u8(P[k], r, k + 1 < CPL ? Q[k + 1] : right);
+            n[k] = __builtin_amdgcn_sad_u8(l, r, min3u(a, Q[k], b));
+            if (EDGE) n[k] |= em[k];
+        }
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) Q[c] = n[c];
+    }
+
     // Returns false when the wait for a neighbour's keys timed out (the image's status says so).
     template <bool EDGE, bool TEAM>
     static __device__ __forceinline__ bool cost_sweep(const Img& d, int w, int k, int tw, int TW, int lane) {
@@ -271,23 +321,26 @@ struct Sweep : Rows<R> {
         constexpr uint32_t kGrid = GRID ? ~3u : ~0u;
 
         Item it = make_item(hf, w, ns, tw, TW, 0, 0, lane);
-        uint32_t roff = Rows<R>::template row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro) + (GRID ? 2u * (uint32_t)it.base : 0u);
-        uint64_t ring[PF][(CPL + 3) / 4];
+        uint32_t roff = Rows<R, FWD>::template row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro) + (GRID ? 2u * (uint32_t)it.base : 0u);
+        uint64_t ring[PF][ND];
 #pragma unroll
-        for (int i = 0; i < PF; ++i)
-            load_ev<TEAM, CPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i) & kGrid, it.off);
+        for (int i = 0; i + LATE < PF; ++i)
+            load_ev<TEAM, (int)CB * CPL / 2>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i) & kGrid, it.off);
         uint32_t Q[CPL], em[CPL];  // em: all ones in columns past the image
         auto set_em = [&]() {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) em[c] = (EDGE || GRID) && it.col0 + c >= w ? 0xFFFFFFFFu : 0u;
+            for (int c = 0; c < CPL; ++c) em[c] = (EDGE || GRID) && it.col0 + c >= w ? INF : 0u;
         };
         set_em();
 #pragma unroll
         for (int c = 0; c < CPL; ++c) Q[c] = em[c];
+        bool last[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) last[c] = FWD && EDGE && it.col0 + c + 1 >= w;
         // in lane l: half a dword if row l of the item starts off the dword grid
         auto odd_of = [&](uint32_t r) { return GRID ? (r & 2u) << 3 : 0u; };
         uint32_t odd = odd_of(roff);
-        uint32_t left = 0xFFFFFFFFu, right = 0xFFFFFFFFu;
+        uint32_t left = INF, right = INF;
         for (;;) {
             // the wave's next item: its row offsets now, its first rows during this item's last block
             int pn = it.p, jn = it.j;
@@ -296,7 +349,7 @@ struct Sweep : Rows<R> {
             } while (pn < P0 && hf[1].n > 0 && pn >= P1 && ((tw + jn * TW) & 1));
             const bool more = pn < P0;
             const Item nx = more ? make_item(hf, w, ns, tw, TW, pn, jn, lane) : it;
-            const uint32_t roffn = Rows<R>::template row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro) + (GRID ? 2u * (uint32_t)nx.base : 0u);
+            const uint32_t roffn = Rows<R, FWD>::template row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro) + (GRID ? 2u * (uint32_t)nx.base : 0u);
             // lanes from rg on are ghost columns: KR of them left of the window's right side, or (GRID: the
             // last strip but one may reach past the image) of the image's
             const int rg = it.t == ns - 1 ? 64 : GRID ? min(64 - KR / CPL, (w - it.base - KR) / CPL) : 64 - KR / CPL;
@@ -304,7 +357,14 @@ struct Sweep : Rows<R> {
             if (it.p == 0) {
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) Q[c] = em[c];
+                if constexpr (FWD) {
+#pragma unroll
+                    for (int c = 0; c < ND; ++c) ring[PF - 1][c] = 0;
+                }
             } else if (ns > 1) {
+                if (FWD && nsw > 1)  // the wave comes from another strip
+                    load_ev<TEAM, (int)CB * CPL / 2>(ring[PF - 1], re, (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(
+                                                                           d, it.h ? hf[1] : hf[0], it.h, it.v0 - 1, rro)), it.off);
                 const bool need = nsw > 1 || (it.t > 0 && lane < KR / CPL) || lane >= rg;
                 const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + it.v0 / R - 1) * ckrow;
                 const uint32_t ko = need ? (uint32_t)it.col0 * 4u : kBufDrop;
@@ -370,15 +430,20 @@ struct Sweep : Rows<R> {
                 for (int g = 0; g < PF; g += 8) {
                     uint32_t so[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) so[i] = (uint32_t)__builtin_amdgcn_readlane(ro, l0 + g + i) & kGrid;
+                    for (int i = 0; i < 8; ++i) {
+                        const bool own = LATE && g + i == 0;  // the current block's last row
+                        so[i] = (uint32_t)__builtin_amdgcn_readlane(own ? roff : ro, own ? v - v0 + PF - 1 : l0 + g + i - LATE) & kGrid;
+                    }
                     uint32_t sh[8];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) sh[i] = GRID ? (uint32_t)__builtin_amdgcn_readlane(odd, v - v0 + g + i) : 0u;
-                    arrived(ring[g + 7]);
+                    arrived(ring[g + 7 - LATE]);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        cost_step<EDGE>(Q, left, right, ring[g + i], sh[i], em);
-                        load_ev<TEAM, CPL>(ring[g + i], re, so[i], eo);
+                        const int r = (g + i + PF - LATE) % PF;  // FWD: the row above's slot
+                        if constexpr (FWD) forward_step<EDGE>(Q, left, right, ring[r], ring[g + i], em, last);
+                        else cost_step<EDGE>(Q, left, right, ring[g + i], sh[i], em);
+                        load_ev<TEAM, (int)CB * CPL / 2>(ring[r], re, so[i], LATE && g + i == 0 ? it.off : eo);
                         __builtin_amdgcn_sched_barrier(0);  // keep the prefetch PF rows ahead of its use
                     }
                 }
@@ -398,17 +463,18 @@ struct Sweep : Rows<R> {
 
 // ----------------------------------------------------------------------------------------------
 // The carve engine: one image, carved by a team of G workgroups of NT threads.
-template <int CPL, int KR, int NT>
-struct Carver : Rows<block_rows(KR)> {
+template <int CPL, int KR, int NT, bool FWD = false>
+struct Carver : Rows<block_rows(KR), FWD> {
     static constexpr int R = block_rows(KR);  // rows of a backtrack block
-    using Half = typename Rows<R>::Half;
-    using Rows<R>::half_of;
-    using Rows<R>::energy_rsrc;
-    using Narrow = Sweep<CPL, KR, R>;
+    using Half = typename Rows<R, FWD>::Half;
+    using Rows<R, FWD>::half_of;
+    using Rows<R, FWD>::energy_rsrc;
+    using Rows<R, FWD>::CB;
+    using Narrow = Sweep<CPL, KR, R, FWD>;
     static constexpr bool HAS_WIDE = CPL == 4 && R == 32;
-    using Wide = std::conditional_t<HAS_WIDE, Sweep<8, 32, 32>, Narrow>;  // of the same blocks
+    using Wide = std::conditional_t<HAS_WIDE, Sweep<8, 32, 32, FWD>, Narrow>;  // of the same blocks
     static constexpr int NW = NT / 64;      // waves per workgroup
-    static constexpr int PB = R;                    // the same of a backtrack block
+    static constexpr int PB = FWD ? R / 2 : R;   // rows of a backtrack block prefetched ahead
     static constexpr int BCPL = 4;            // columns per lane of a backtrack window
     static constexpr int BW = 64 * BCPL;      // columns of a backtrack window
     static constexpr int BS = BW - 2 * R;     // of which exact at the block's last row
@@ -443,6 +509,24 @@ struct Carver : Rows<block_rows(KR)> {
         unsigned long long best = ~0ull;
         for (int c0 = 4 * (int)threadIdx.x; c0 < w; c0 += 4 * NT) {
             uint32_t x[6], y[4];
+            // FWD: what the lower column's diagonal parents add
+            uint32_t dl[4] = {}, dr[4] = {};
+            if constexpr (FWD) {
+                if (bm) {
+                    const __amdgpu_buffer_rsrc_t re = energy_rsrc(d), rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
+                    const uint32_t ou = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(d, h0, 0, h0.B * R - 1, rro));
+                    const uint32_t od = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(d, h1, 1, h1.B * R - 1, rro));
+                    const v4u u = __builtin_amdgcn_raw_buffer_load_b128(re, c0 * 4, (int)ou, kC);
+                    const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, c0 * 4, (int)od, kC);
+                    const uint32_t vl = __builtin_amdgcn_raw_buffer_load_b32(re, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)od, kC);
+                    const uint32_t vr = __builtin_amdgcn_raw_buffer_load_b32(re, c0 * 4 + 16, (int)od, kC);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        dl[c] = __builtin_amdgcn_sad_u8(u[c], c ? v[c - 1] : vl, 0u);
+                        dr[c] = __builtin_amdgcn_sad_u8(u[c], c < 3 ? v[c + 1] : vr, 0u);
+                    }
+                }
+            }
             Wait wait;
             for (;;) {
                 const v4u T = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)t0, kC);
@@ -463,8 +547,9 @@ struct Carver : Rows<block_rows(KR)> {
                 if (c0 + c >= w) continue;
                 uint32_t m = x[c + 1] >> 9, dir = 1;
                 if (bm) {
-                    if (c0 + c > 0 && (x[c] >> 9) <= m) m = x[c] >> 9, dir = 0;
-                    if (c0 + c + 1 < w && (x[c + 2] >> 9) < m) m = x[c + 2] >> 9, dir = 2;
+                    const uint32_t ml = (x[c] >> 9) + dl[c], mr = (x[c + 2] >> 9) + dr[c];
+                    if (c0 + c > 0 && ml <= m) m = ml, dir = 0;
+                    if (c0 + c + 1 < w && mr < m) m = mr, dir = 2;
                 }
                 best = min(best, ((unsigned long long)(m + ((y[c] & bm) >> 9)) << 32) | (unsigned)((c0 + c) << 2) | dir);
             }
@@ -493,17 +578,30 @@ struct Carver : Rows<block_rows(KR)> {
         const uint32_t ckrow = (uint32_t)d.xw * 4u;
         const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
         const int col0 = base + lane * BCPL;
-        const uint32_t roff = Rows<R>::template row_off<COH>(d, x, h, blk * R + min(lane, R - 1), rro);
+        // lane l < R: row l; the others: the row before the block (of zeros before the first one)
+        const uint32_t roff = Rows<R, FWD>::template row_off<COH>(d, x, h, blk * R + (lane < R ? lane : -1), rro);
         auto load_keys = [&]() {
             return __builtin_amdgcn_raw_buffer_load_b128(rck, blk > 0 && col0 < w ? col0 * 4 : (int)kBufDrop,
                                                          (int)((uint32_t)(ckbase + max(blk, 1) - 1) * ckrow), COH ? 16 : 0);
         };
         v4u kv = load_keys();
-        const uint32_t eo = (uint32_t)(col0 < w ? col0 : 0) * 2u;
-        uint64_t ring[PB][1];
+        const uint32_t eo = (uint32_t)(col0 < w ? col0 : 0) * CB;
+        uint64_t ring[PB][FWD ? 2 : 1];
 #pragma unroll
         for (int i = 0; i < PB; ++i)
-            load_ev<COH, BCPL>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), eo);
+            load_ev<COH, (int)CB * BCPL / 2>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), eo);
+        uint32_t P[BCPL] = {};  // FWD: the pixels of the row above
+        if constexpr (FWD) {
+            uint64_t a[2];
+            load_ev<COH, (int)CB * BCPL / 2>(a, re, (uint32_t)__builtin_amdgcn_readlane(roff, R), eo);
+#pragma unroll
+            for (int c = 0; c < BCPL; ++c) P[c] = (uint32_t)(a[c >> 1] >> ((c & 1) * 32));
+        }
+        // FWD adds to the keys of missing parents, so those are all ones only after that
+        const uint32_t noL = lane == 0 ? ~0u : 0u;
+        uint32_t noR[BCPL];
+#pragma unroll
+        for (int c = 0; c < BCPL; ++c) noR[c] = (EDGE && col0 + c + 1 >= w) || (lane == 63 && c == BCPL - 1) ? ~0u : 0u;
         bool valid[BCPL];
 #pragma unroll
         for (int c = 0; c < BCPL; ++c) valid[c] = !EDGE || col0 + c < w;
@@ -531,18 +629,42 @@ struct Carver : Rows<block_rows(KR)> {
             left = (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)t[BCPL - 1], 0x138, 0xf, 0xf, false);
             right = (uint32_t)__builtin_amdgcn_update_dpp((int)right, (int)(t[0] + 10u), 0x130, 0xf, 0xf, false);
             uint32_t acc = 0;
+            if constexpr (FWD) {
+                uint32_t px[BCPL];
 #pragma unroll
-            for (int c = 0; c < BCPL; ++c) {
-                const uint32_t m = min(min(c ? t[c - 1] : left, t[c] + 5u), c + 1 < BCPL ? t[c + 1] + 10u : right);
-                const uint32_t pair = (uint32_t)(ring[i % PB][0] >> ((c >> 1) * 32));
-                Q[c] = (c & 1) ? mad_hi16(pair, m) : mad_lo16(pair, m);
-                if (EDGE) Q[c] = valid[c] ? Q[c] : QINF;
-                acc = __builtin_amdgcn_alignbit(m, acc, 2u);
+                for (int c = 0; c < BCPL; ++c) px[c] = (uint32_t)(ring[i % PB][c >> 1] >> ((c & 1) * 32));
+                const uint32_t pl = (uint32_t)__builtin_amdgcn_update_dpp((int)px[0], (int)px[BCPL - 1], 0x138, 0xf, 0xf, false);
+                const uint32_t pr = (uint32_t)__builtin_amdgcn_update_dpp((int)px[BCPL - 1], (int)px[0], 0x130, 0xf, 0xf, false);
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) {
+                    const uint32_t l = c ? px[c - 1] : pl;
+                    uint32_t r = c + 1 < BCPL ? px[c + 1] : pr;
+                    if (EDGE) r = noR[c] ? px[c] : r;
+                    uint32_t a = (__builtin_amdgcn_sad_u8(P[c], l, 0u) << 9) + (c ? t[c - 1] : left);
+                    uint32_t b = (__builtin_amdgcn_sad_u8(P[c], r, 0u) << 9) + (c + 1 < BCPL ? t[c + 1] + 10u : right);
+                    if (c == 0) a |= noL;
+                    if (EDGE || c == BCPL - 1) b |= noR[c];
+                    const uint32_t m = min3u(a, t[c] + 5u, b);
+                    Q[c] = (__builtin_amdgcn_sad_u8(l, r, 0u) << 9) + m;
+                    if (EDGE) Q[c] = valid[c] ? Q[c] : QINF;
+                    acc = __builtin_amdgcn_alignbit(m, acc, 2u);
+                }
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) P[c] = px[c];
+            } else {
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) {
+                    const uint32_t m = min(min(c ? t[c - 1] : left, t[c] + 5u), c + 1 < BCPL ? t[c + 1] + 10u : right);
+                    const uint32_t pair = (uint32_t)(ring[i % PB][0] >> ((c >> 1) * 32));
+                    Q[c] = (c & 1) ? mad_hi16(pair, m) : mad_lo16(pair, m);
+                    if (EDGE) Q[c] = valid[c] ? Q[c] : QINF;
+                    acc = __builtin_amdgcn_alignbit(m, acc, 2u);
+                }
             }
             p = __builtin_amdgcn_perm(acc, p, 0x07030201u);  // this row's byte on top
             if constexpr (i % 4 == 3) pk[i / 4] = p;
             if constexpr (i + PB < R)
-                load_ev<COH, BCPL>(ring[i % PB], re, (uint32_t)__builtin_amdgcn_readlane(roff, i + PB), eo);
+                load_ev<COH, (int)CB * BCPL / 2>(ring[i % PB], re, (uint32_t)__builtin_amdgcn_readlane(roff, i + PB), eo);
             __builtin_amdgcn_sched_barrier(0);
         });
     }
@@ -755,9 +877,14 @@ struct Carver : Rows<block_rows(KR)> {
             const int s = min((int)(word & 0xFFFFu), w - 1);
             const bool right = d.minside && s < w - 1 - s;
             __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(o + 1), rro, (int)(right ? mine : kBufDrop), 0, 0);
-            const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
-                                          shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, 2)};
-            shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, 2), lane);
+            if constexpr (FWD) {
+                const ShiftPlane planes[1] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, 4)};
+                shift_rows<4, 1>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * 4, lane);
+            } else {
+                const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
+                                              shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, 2)};
+                shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, 2), lane);
+            }
         }
     }
 
@@ -809,28 +936,30 @@ struct Carver : Rows<block_rows(KR)> {
             remove_rows<TEAM>(fetch(gd), w, k, ra, rb, lane);
             if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
             if (timer) tm2 = wall_clock64();
-            const Img d = fetch(gd);
-            // ---- band energy (a2): only the new columns s-1 and s of each row changed.  Buffer
-            // loads (sc1 in a team: the rows above and below were shifted by other workgroups) at
-            // 32-bit offsets; a lane past the wave's rows reads row ra and stores nothing.
-            const int w2 = w - 1;
-            const __amdgpu_buffer_rsrc_t rwk = make_rsrc(d.wk, (uint32_t)H * (uint32_t)d.wp);
-            const __amdgpu_buffer_rsrc_t rsm = make_rsrc(d.seam, (uint32_t)H * 4u);
-            const __amdgpu_buffer_rsrc_t rof = make_rsrc(d.ro, (uint32_t)H * 4u);
-            for (int rc = ra; rc < rb; rc += 64) {
-                const int r = rc + lane < rb ? rc + lane : ra;
-                const int ru = r > 0 ? r - 1 : 0, rd = r + 1 < H ? r + 1 : H - 1;
-                const int s = min((int)(buf_ld32<TEAM>(rsm, (uint32_t)r * 4u) & 0xFFFFu), w - 1);
-                const int o = (int)buf_ld32<TEAM>(rof, (uint32_t)r * 4u);
-                const uint32_t br = (uint32_t)r * (uint32_t)d.wp + (uint32_t)(o * d.C);
-                const uint32_t bu = (uint32_t)ru * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)ru * 4u) * (uint32_t)d.C;
-                const uint32_t bd = (uint32_t)rd * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)rd * 4u) * (uint32_t)d.C;
-                const uint32_t e0 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s - 1);
-                const uint32_t e1 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s);
-                if (rc + lane < rb) {
-                    uint16_t* er = d.e + (size_t)r * d.ep + o;
-                    if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = (uint16_t)e0;
-                    if (s < w2) *gp(er + s) = (uint16_t)e1;
+            if constexpr (!FWD) {
+                const Img d = fetch(gd);
+                // ---- band energy (a2): only the new columns s-1 and s of each row changed.  Buffer
+                // loads (sc1 in a team: the rows above and below were shifted by other workgroups) at
+                // 32-bit offsets; a lane past the wave's rows reads row ra and stores nothing.
+                const int w2 = w - 1;
+                const __amdgpu_buffer_rsrc_t rwk = make_rsrc(d.wk, (uint32_t)H * (uint32_t)d.wp);
+                const __amdgpu_buffer_rsrc_t rsm = make_rsrc(d.seam, (uint32_t)H * 4u);
+                const __amdgpu_buffer_rsrc_t rof = make_rsrc(d.ro, (uint32_t)H * 4u);
+                for (int rc = ra; rc < rb; rc += 64) {
+                    const int r = rc + lane < rb ? rc + lane : ra;
+                    const int ru = r > 0 ? r - 1 : 0, rd = r + 1 < H ? r + 1 : H - 1;
+                    const int s = min((int)(buf_ld32<TEAM>(rsm, (uint32_t)r * 4u) & 0xFFFFu), w - 1);
+                    const int o = (int)buf_ld32<TEAM>(rof, (uint32_t)r * 4u);
+                    const uint32_t br = (uint32_t)r * (uint32_t)d.wp + (uint32_t)(o * d.C);
+                    const uint32_t bu = (uint32_t)ru * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)ru * 4u) * (uint32_t)d.C;
+                    const uint32_t bd = (uint32_t)rd * (uint32_t)d.wp + buf_ld32<TEAM>(rof, (uint32_t)rd * 4u) * (uint32_t)d.C;
+                    const uint32_t e0 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s - 1);
+                    const uint32_t e1 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s);
+                    if (rc + lane < rb) {
+                        uint16_t* er = d.e + (size_t)r * d.ep + o;
+                        if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = (uint16_t)e0;
+                        if (s < w2) *gp(er + s) = (uint16_t)e1;
+                    }
                 }
             }
             // a team's time budget: its first member decides before the seam's last barrier, every
@@ -838,7 +967,7 @@ struct Carver : Rows<block_rows(KR)> {
             if (deadline && G > 1 && k + 1 < k_end && rank == 0 && threadIdx.x == 0)
                 __hip_atomic_store(&ctl->stop, wall_clock64() >= deadline ? 1u : 0u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
+            if (!FWD && !team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
             if (deadline && G > 1 && k + 1 < k_end && __hip_atomic_load(&ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) k_end = k + 1;
             if (timer) {
                 const unsigned long long tm3 = wall_clock64();
@@ -864,6 +993,15 @@ struct Carver : Rows<block_rows(KR)> {
 #pragma unroll 1
                 for (int i = 0; i < n; ++i) {
                     const int o = __builtin_amdgcn_readlane(rof, i);
+                    if constexpr (FWD) {  // the low C bytes of each pixel's dword
+                        const uint32_t* src = reinterpret_cast<const uint32_t*>(d.wk + (long long)(rc + i) * d.wp) + o;
+                        uint8_t* dst = d.img + (long long)(rc + i) * d.pitch;
+                        for (int x = lane; x < d.target_w; x += 64) {
+                            const uint32_t px = *gp(src + x);
+                            for (int c = 0; c < d.C; ++c) *gp(dst + (long long)x * d.C + c) = (uint8_t)(px >> (8 * c));
+                        }
+                        continue;
+                    }
                     copy_bytes_wave(d.img + (long long)(rc + i) * d.pitch, d.wk + (long long)(rc + i) * d.wp + (long long)o * d.C,
                                     nb, lane);
                 }

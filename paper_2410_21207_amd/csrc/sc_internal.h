@@ -16,25 +16,21 @@ struct Img {
     int32_t* seams_out;  // optional, (W-target_w)*H
     long long* costs_out;  // optional, W-target_w
     // workspace pieces
-    uint16_t* e;   // energy plane, H rows of `ep` uint16 and a row of zeros
-    uint8_t* dirs; // forward energy: parent directions, 2 bits per cell, H rows of `db` bytes
+    uint16_t* e;   // energy plane, H rows of `ep` uint16 and a row of zeros (forward energy: wk, so too)
     int8_t* anc;   // the ancestor offset of every column at the last row of a block (`xw` bytes per row)
-                   // or, forward energy, of a DP phase
-    uint32_t* xq;  // published DP keys: P rows of `xw` uint32, the last row of every block; or, forward
-                   // energy, 2 rows exchanged between members at phase ends
+    uint32_t* xq;  // published DP keys: P rows of `xw` uint32, the last row of every block
     int32_t* seam; // current seam, H
     int32_t* ro;   // per row: physical column of the row's first pixel (min-side removal), H
     uint8_t* wk;   // working copy of the image, H rows of `wp` bytes (64-byte aligned rows)
     unsigned long long* amin;  // packed (cost << 32 | column) argmin of the current seam
     unsigned* bar;             // team barrier counter
     unsigned* status;          // error bits
-    int ep, db, xw, P;         // pitches; rows of published keys (forward energy: DP phases)
+    int ep, xw, P;             // pitches; rows of published keys
     int wp;                    // bytes per row of wk, at least 16 more than its pixels
     int G;                     // team size (workgroups) carving this image
     int mode;                  // 0 = carve, 1 = one seam only, no removal (sc_dp_seam), 2 = the same
                                // and the direction of every cell as a byte in img (H x W)
     int minside;               // 1 = remove a seam pixel by moving the shorter side of its row
-    unsigned long long* amk;   // forward teams: the argmin words of even and odd seams
 };
 
 // Control words of one image (zeroed by the energy pass of every launch).
@@ -129,24 +125,23 @@ hipError_t launch_insert_seams(const uint8_t* img, int H, int W, int C, long lon
                                uint8_t* out, long long out_pitch, hipStream_t st);
 constexpr int kInsertMaxWidth = 65536;
 
-// Limits of the one-workgroup-row kernels (object removal) and the forward teams: widths up to
-// kFwdMaxW, rows up to kFwdMaxH; loads of a row may read up to kFwdSlack bytes past the last row of
-// a working copy.  kFwdPhaseRows: rows per backtrack phase of the object-removal DP.
+// Limits of the object-removal and forward-energy kernels: widths up to kFwdMaxW, rows up to
+// kFwdMaxH; loads of a row may read up to kFwdSlack bytes past the last row of a working copy.
+// kFwdPhaseRows: rows per backtrack phase of the object-removal DP.
 constexpr int kFwdMaxW = 8192;
 constexpr int kFwdMaxH = 16448;
 constexpr int kFwdPhaseRows = 60;
 constexpr size_t kFwdSlack = 256;
 
-// Forward-energy carve by teams of 256-thread workgroups on one XCD (sc_forward.hip).  A working
-// pixel is one dword.  Member g of a team with more than one DP member computes columns
-// [g*kFwtOwned - 2*kFwtPhaseRows, (g+1)*kFwtOwned + 2*kFwtPhaseRows) and owns [g*kFwtOwned,
-// (g+1)*kFwtOwned); a team of images up to kFwtSingle columns has one DP member.  blk: block ->
-// (image, member), or nullptr for one image whose members are blocks xcd, xcd + 8, ...
-constexpr int kFwtThreads = 256;
-constexpr int kFwtWindow = 976;  // 4 waves x 240 exact columns + 8 ghost columns on each side
-constexpr int kFwtPhaseRows = 56;
-constexpr int kFwtOwned = kFwtWindow - 4 * kFwtPhaseRows;  // keys exchanged every second phase
-constexpr int kFwtSingle = kFwtWindow - 8;  // widest image a single DP member carves
+// Forward-energy carve by teams of workgroups on one XCD (sc_forward.hip).  A working pixel is one
+// dword; Img::e and ep are that plane.  blk: block -> (image, member), or nullptr for one image
+// whose members are blocks xcd, xcd + 8, ...  A batch holds at most kFwdBatchUnits units of
+// kFwdUnitCols columns (an image of up to kFwdUnitFirst columns is one).
+constexpr int kFwdThreads = 512;
+constexpr int kFwdKR = 64;  // rows per sweep phase, four columns per lane
+constexpr int kFwdBatchUnits = 512;
+constexpr int kFwdUnitCols = 752;
+constexpr int kFwdUnitFirst = 968;
 hipError_t launch_fwt_prepare(const Img* imgs, int n, int max_rows, hipStream_t st);
 hipError_t launch_fwt_carve(const Img* imgs, const int2* blk, int nblocks, int xcd, hipStream_t st);
 int fwt_blocks_per_cu();

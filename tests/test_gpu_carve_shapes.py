@@ -6,6 +6,7 @@ shifter (up to 208 bytes to move) or take several passes (63 slots of 16 bytes e
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from gpu_helpers import dev, host, log
@@ -73,3 +74,31 @@ def test_one_seam_by_a_team(H, W, dirs):
     assert int(host(got[1])[0]) == cost
     if dirs:
         assert np.array_equal(host(got[2])[1:], D[1:])
+
+
+def _check_forward(img, k, got):
+    out, seams, costs = oracle.carve_forward(img, img.shape[1] - k)
+    assert np.array_equal(host(got[1]), seams)
+    assert np.array_equal(host(got[2]), costs)
+    assert np.array_equal(host(got[0]), out)
+
+
+@pytest.mark.parametrize("H,W,C", [(1, 9, 3), (2, 300, 1), (4, 257, 3), (5, 1403, 2), (33, 256, 4), (64, 513, 3),
+                                   (66, 255, 1), (130, 385, 3), (300, 954, 1), (640, 70, 3)])
+def test_forward_shapes(H, W, C):
+    """Forward energy at the edges of strips, halves and blocks; few values, so that ties abound."""
+    img = np.random.default_rng(H * 11 + W).integers(0, 3, size=(H, W, C)).astype(np.uint8)
+    k = min(W - 1, 6)
+    _check_forward(img, k, api.carve_forward(dev(img), W - k))
+
+
+def test_forward_batch_of_lone_workgroups():
+    """More images than workgroups' teams: wide strips, several to a wave, carved by one workgroup each."""
+    rng = np.random.default_rng(5)
+    imgs = [rng.integers(0, 4, size=(33 + i % 40, 505 + 3 * i, 3)).astype(np.uint8) for i in range(150)]
+    srcs = [dev(i) for i in imgs]
+    fb = api.ForwardBatch([torch.empty_like(x) for x in srcs], [i.shape[1] - 3 for i in imgs], srcs=srcs)
+    fb.launch()
+    res = fb.results()
+    for i in range(0, len(imgs), 14):
+        _check_forward(imgs[i], 3, res[i])
