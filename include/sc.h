@@ -326,7 +326,8 @@ sc_status sc_forward_batch_launch_carve(const sc_batch_info* info, void* ws, voi
  *               256-byte aligned.
  * Synchronous: the frame and the output size depend on the mask, so the call
  * waits for the device (after the mask extent and after the carve) and
- * returns with out complete.  One 1024-thread workgroup carves the frame.
+ * returns with out complete.  A team of workgroups carves the frame, or one
+ * workgroup where half its rows times B exceed 31 bits.
  * Limits: carved frame of at most 8192 columns and rows*510*C <= 8388000.
  * Errors: SC_EINVAL, SC_ENOMEM (workspace too small), SC_EUNSUPPORTED, SC_EHIP.
  */

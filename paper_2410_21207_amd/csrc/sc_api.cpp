@@ -1024,13 +1024,15 @@ extern "C" sc_status sc_forward_batch_launch_carve(const sc_batch_info* info, vo
 namespace {
 
 struct ObjLayout {
-    size_t ctl, desc, wk, mk, dirs, anc, seam, buf_a, buf_b, ins, ins_bytes, total;
-    int wp, mp, db;
+    size_t ctl, desc, tctl, wk, mk, dirs, anc, seam, buf_a, buf_b, ins, ins_bytes, total;
+    size_t e, canc, xq, ro;  // by teams
+    int wp, mp, db, ep, P, xw;
 };
 
 // Workspace of one carved frame of h rows by w0 columns.
 ObjLayout obj_layout(int h, int w0, int C, bool restore) {
     ObjLayout L;
+    memset(&L, 0, sizeof(L));
     const int P = (h + sc::kFwdPhaseRows - 1) / sc::kFwdPhaseRows;
     L.wp = (int)sc::align_up((size_t)w0 * C + 16, 64);  // 16 bytes between rows: the row shifter's last slot
     L.mp = (int)sc::align_up((size_t)w0 + 16, 64);
@@ -1040,8 +1042,10 @@ ObjLayout obj_layout(int h, int w0, int C, bool restore) {
     off = sc::align_up(off + sizeof(sc::ObjCtl), sc::kAlign);
     L.desc = off;
     off = sc::align_up(off + sizeof(sc::ObjImg), sc::kAlign);
-    L.wk = off;
-    off = sc::align_up(off + (size_t)h * L.wp + sc::kFwdSlack, sc::kAlign);
+    L.tctl = off;
+    off = sc::align_up(off + sizeof(sc::Ctl), sc::kAlign);
+    L.wk = off + 64;  // the row shifter may write up to 16 bytes below a plane
+    off = sc::align_up(L.wk + (size_t)h * L.wp + sc::kFwdSlack, sc::kAlign);
     L.mk = off;
     off = sc::align_up(off + (size_t)h * L.mp + sc::kFwdSlack, sc::kAlign);
     L.dirs = off;
@@ -1050,6 +1054,19 @@ ObjLayout obj_layout(int h, int w0, int C, bool restore) {
     off = sc::align_up(off + (size_t)P * w0, sc::kAlign);
     L.seam = off;
     off = sc::align_up(off + (size_t)h * 4, sc::kAlign);
+    if (sc::masked_by_teams(h, C)) {
+        L.P = sc::key_rows(h, sc::kObjKR, 0);
+        L.xw = sc::key_pitch(w0);
+        L.ep = (int)sc::align_up((size_t)w0 * 4 + 16, 16) / 2;
+        L.e = off + 64;
+        off = sc::align_up(L.e + (size_t)(h + 1) * L.ep * 2 + 64, sc::kAlign);
+        L.canc = off;
+        off = sc::align_up(off + (size_t)L.P * L.xw, sc::kAlign);
+        L.xq = off;
+        off = sc::align_up(off + (size_t)L.P * L.xw * 4, sc::kAlign);
+        L.ro = off;
+        off = sc::align_up(off + (size_t)h * 4, sc::kAlign);
+    }
     L.buf_a = L.buf_b = L.ins = L.ins_bytes = 0;
     if (restore && w0 >= 2) {
         L.buf_a = off;
@@ -1057,7 +1074,7 @@ ObjLayout obj_layout(int h, int w0, int C, bool restore) {
         L.buf_b = off;
         off = sc::align_up(off + (size_t)h * L.wp, sc::kAlign);
         L.ins = off;
-        L.ins_bytes = sc_insert_workspace_bytes(h, w0, C, L.wp, w0 - 1);  // the largest round
+        L.ins_bytes = sc_insert_workspace_bytes(h, w0, C, std::max(L.wp, 2 * L.ep), w0 - 1);  // the largest round
         off = sc::align_up(off + L.ins_bytes, sc::kAlign);
     }
     L.total = off;
@@ -1162,9 +1179,36 @@ extern "C" sc_status sc_remove_object(const uint8_t* img, const uint8_t* mask, i
     d.mp = L.mp;
     d.db = L.db;
     d.max_seams = w0 - 1;
+    const bool teams = sc::masked_by_teams(h, C);
+    if (teams) {
+        sc::Ctl* tc = reinterpret_cast<sc::Ctl*>(base + L.tctl);
+        d.c.img = reinterpret_cast<uint8_t*>(base + L.e);  // the carved rows, once the energies have served
+        d.c.pitch = 2ll * L.ep;
+        d.c.H = h;
+        d.c.W = w0;
+        d.c.C = C;
+        d.c.target_w = 1;
+        d.c.seams_out = seams_out;
+        d.c.costs_out = reinterpret_cast<long long*>(costs_out);
+        d.c.e = reinterpret_cast<uint16_t*>(base + L.e);
+        d.c.ep = L.ep;
+        d.c.anc = reinterpret_cast<int8_t*>(base + L.canc);
+        d.c.xq = reinterpret_cast<uint32_t*>(base + L.xq);
+        d.c.P = L.P;
+        d.c.xw = L.xw;
+        d.c.seam = d.seam;
+        d.c.ro = reinterpret_cast<int32_t*>(base + L.ro);
+        d.c.wk = wk;
+        d.c.wp = L.wp;
+        d.c.amin = &tc->amin;
+        d.c.bar = &tc->bar;
+        d.c.status = &tc->status;
+        d.c.minside = 1;
+        d.c.G = single_team(h, w0, sc::kObjThreads / 64, sc::kObjMaxTeam);
+    }
     sc::ObjImg* desc = reinterpret_cast<sc::ObjImg*>(base + L.desc);
     e = hipMemcpyAsync(desc, &d, sizeof(d), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = sc::launch_obj_carve(desc, 1, w0, st);
+    if (e == hipSuccess) e = sc::launch_obj_carve(desc, 1, teams ? 0 : w0, st);
     if (e == hipSuccess) e = hipMemcpyAsync(&hc, ctl, sizeof(hc), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e, "object carve");
@@ -1173,25 +1217,27 @@ extern "C" sc_status sc_remove_object(const uint8_t* img, const uint8_t* mask, i
     if (k < 0 || k > w0 - 1 || rw != w0 - k) return fail(SC_EHIP, "object carve returned k=%d w=%d", k, rw);
 
     // restore the size by seam insertion, in rounds of at most (current width - 1) seams
-    const uint8_t* cur = wk;
+    const uint8_t* cur = teams && k > 0 ? d.c.img : wk;
+    int curp = teams && k > 0 ? 2 * L.ep : L.wp;
     if (restore && k > 0) {
         if (rw < 2) return fail(SC_EINVAL, "the carve left one column: nothing to insert seams into");
         uint8_t* bufs[2] = {reinterpret_cast<uint8_t*>(base + L.buf_a), reinterpret_cast<uint8_t*>(base + L.buf_b)};
         int nb = 0;
         while (rw < w0) {
             const int n = std::min(w0 - rw, rw - 1);
-            s = sc_insert_seams(cur, h, rw, C, L.wp, n, bufs[nb], L.wp, nullptr, nullptr, base + L.ins, L.ins_bytes,
+            s = sc_insert_seams(cur, h, rw, C, curp, n, bufs[nb], L.wp, nullptr, nullptr, base + L.ins, L.ins_bytes,
                                 stream);
             if (s != SC_OK) return s;
             cur = bufs[nb];
+            curp = L.wp;
             nb ^= 1;
             rw += n;
         }
     }
 
     // the result in the caller's orientation
-    if (vert) e = sc::launch_copy_rows(cur, L.wp, out, out_pitch, h, rw * C, st);
-    else e = sc::launch_transpose(cur, h, rw, C, L.wp, out, out_pitch, st);
+    if (vert) e = sc::launch_copy_rows(cur, curp, out, out_pitch, h, rw * C, st);
+    else e = sc::launch_transpose(cur, h, rw, C, curp, out, out_pitch, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e, "object output");
     int dev = 0, khz = 0;

@@ -121,17 +121,27 @@ struct Wait {
     }
 };
 
-// Tag of the keys a seam publishes: 1..511, never the 0 of a cleared row.  Every row of ck is
-// written once per seam, so a reader only has to tell a seam from the one before it.
-__device__ __forceinline__ uint32_t seam_tag(int k) { return 1u + (uint32_t)k % 511u; }
-// The same of a row's seam column (16 bits, columns below 65535), in the upper half of its word.
+// Tag of a row's seam column (16 bits, columns below 65535), in the upper half of its word: never 0.
 __device__ __forceinline__ uint32_t seam_word(int k) { return ((uint32_t)k + 1u) << 16; }
 
-// What the sweep and the backtrack read: the plane of 16-bit energies or, FWD (forward energy), the
-// current pixels, a dword each; CB bytes per column.
-template <int R, bool FWD>
+// What the sweep and the backtrack read: the plane of 16-bit energies; the current pixels, a dword
+// each (forward energy); or energies of 32 bits, those of pixels outside the mask raised by
+// masked_bias (object removal).
+enum Kind { kEnergy, kForward, kMasked };
+// Tag of the keys a seam publishes, never the 0 of a cleared row.  Every row of ck is written once
+// per seam, so a reader only has to tell a seam from the one before it: 1..511 in nine bits, or one
+// bit under the 31-bit costs of a masked image.
+template <Kind KD>
+__device__ __forceinline__ uint32_t seam_tag(int k) {
+    return KD == kMasked ? ~(uint32_t)k & 1u : 1u + (uint32_t)k % 511u;
+}
+
+template <int R, Kind KD>
 struct Rows {
-    static constexpr uint32_t CB = FWD ? 4 : 2;
+    static constexpr bool FWD = KD == kForward, MSK = KD == kMasked;
+    static constexpr uint32_t CB = KD == kEnergy ? 2 : 4;  // bytes per column
+    static constexpr int SH = MSK ? 1 : 9;                 // bits of a published key's tag
+    static constexpr uint32_t TAG = (1u << SH) - 1;
     // The rows of one half (h = 0: from the top down to the split row, 1: from the bottom up).
     // Virtual row v of a half is image row v - pad counted from the half's border; the rows below
     // pad do not exist and read the plane's row of zeros (row H), so that the half is a whole number
@@ -176,20 +186,24 @@ struct Rows {
 // ancestor offsets a row is a v_min3 and an add per column and two wave shifts (15 instructions for
 // 256 columns), and the two ends halve the chain.  Rows are loaded a block ahead, one wait per eight
 // rows.  1920 x 1080 by 32 workgroups: 27 us per seam where the one-ended sweep with directions took 106.
-template <int CPL, int KR, int R, bool FWD>
-struct Sweep : Rows<R, FWD> {
-    using Half = typename Rows<R, FWD>::Half;
-    using Rows<R, FWD>::half_of;
-    using Rows<R, FWD>::energy_rsrc;
-    using Rows<R, FWD>::CB;
-    static constexpr int ND = FWD ? CPL / 2 : (CPL + 3) / 4;  // 64-bit words of a lane's columns
+template <int CPL, int KR, int R, Kind KD>
+struct Sweep : Rows<R, KD> {
+    using Half = typename Rows<R, KD>::Half;
+    using Rows<R, KD>::half_of;
+    using Rows<R, KD>::energy_rsrc;
+    using Rows<R, KD>::CB;
+    using Rows<R, KD>::FWD;
+    using Rows<R, KD>::MSK;
+    using Rows<R, KD>::SH;
+    using Rows<R, KD>::TAG;
+    static constexpr int ND = CB == 4 ? CPL / 2 : (CPL + 3) / 4;  // 64-bit words of a lane's columns
     // FWD needs the row above too, so a row's registers are loaded anew only after the next row.
     static constexpr int LATE = FWD ? 1 : 0;
     // The cost of a missing parent, more than any real one; FWD adds to it and must not wrap.
     static constexpr uint32_t INF = FWD ? 0x40000000u : 0xFFFFFFFFu;
     static constexpr int WIN = 64 * CPL;    // columns a wave computes
     static constexpr int S = WIN - 2 * KR;  // columns a strip adds: KR ghost columns on each side
-    static constexpr int PF = R == 32 ? (FWD ? 64 : 128) / CPL : R;  // rows prefetched ahead
+    static constexpr int PF = R == 32 ? (CB == 4 ? 64 : 128) / CPL : R;  // rows prefetched ahead
     static_assert(CPL == 2 || CPL == 4 || CPL == 8, "one energy load per lane and row");
     static_assert(KR % R == 0 && R % PF == 0 && PF % 8 == 0 && KR <= 64 && R <= 63 && KR % CPL == 0 && S > 0, "phase shape");
 
@@ -198,7 +212,7 @@ struct Sweep : Rows<R, FWD> {
     // four times as much, and strips this wide run several to a compute unit).  A lane takes the dword
     // after its own from the next lane; lane 63 has none, so it is ghost columns, or past the image:
     // the last strip's window runs eight columns past w, and the first of them stays all ones.
-    static constexpr bool GRID = CPL == 8 && !FWD;  // (a row of pixels starts on the grid)
+    static constexpr bool GRID = CPL == 8 && CB == 2;  // (dwords start on the grid)
     static constexpr int WINR = GRID ? WIN - CPL : WIN;  // columns of the last strip's window in the image
 
     static __device__ __forceinline__ int strips(int w) { return w <= WINR ? 1 : (w - WINR + S - 1) / S + 1; }
@@ -248,7 +262,7 @@ struct Sweep : Rows<R, FWD> {
         // one instruction more per pair) first and last column first, for the next row's wave shifts
         uint32_t pair[CPL / 2];  // energies of columns 2j, 2j + 1
 #pragma unroll
-        for (int j = 0; j < CPL / 2; ++j) pair[j] = (uint32_t)(raw[j >> 1] >> ((j & 1) * 32));
+        for (int j = 0; j < CPL / 2; ++j) pair[j] = MSK ? 0u : (uint32_t)(raw[j >> 1] >> ((j & 1) * 32));
         if constexpr (GRID) {  // odd: 0 or 16
             const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)pair[0], 0x130, 0xf, 0xf, true);
 #pragma unroll
@@ -264,7 +278,8 @@ struct Sweep : Rows<R, FWD> {
 #pragma unroll
         for (int i = 0; i < CPL; ++i) {
             const int k = i == 0 ? 0 : i == 1 ? CPL - 1 : i - 1;
-            Q[k] = n[k] + ((k & 1) ? pair[k >> 1] >> 16 : pair[k >> 1] & 0xFFFFu);
+            if constexpr (MSK) Q[k] = n[k] + (uint32_t)(raw[k >> 1] >> ((k & 1) * 32));
+            else Q[k] = n[k] + ((k & 1) ? pair[k >> 1] >> 16 : pair[k >> 1] & 0xFFFFu);
             if (EDGE || (GRID && k == 0)) Q[k] |= em[k];
         }
     }
@@ -313,7 +328,7 @@ struct Sweep : Rows<R, FWD> {
         if (tw >= items) return true;
         const int nsw = (items - tw + TW - 1) / TW;
         const int P0 = (hf[0].B * R + KR - 1) / KR, P1 = (hf[1].B * R + KR - 1) / KR;
-        const uint32_t tag = seam_tag(k);
+        const uint32_t tag = seam_tag<KD>(k);
         const __amdgpu_buffer_rsrc_t re = energy_rsrc(d);
         const __amdgpu_buffer_rsrc_t rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
         const uint32_t ckrow = (uint32_t)d.xw * 4u;
@@ -321,7 +336,7 @@ struct Sweep : Rows<R, FWD> {
         constexpr uint32_t kGrid = GRID ? ~3u : ~0u;
 
         Item it = make_item(hf, w, ns, tw, TW, 0, 0, lane);
-        uint32_t roff = Rows<R, FWD>::template row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro) + (GRID ? 2u * (uint32_t)it.base : 0u);
+        uint32_t roff = Rows<R, KD>::template row_off<TEAM>(d, it.h ? hf[1] : hf[0], it.h, it.v0 + lane, rro) + (GRID ? 2u * (uint32_t)it.base : 0u);
         uint64_t ring[PF][ND];
 #pragma unroll
         for (int i = 0; i + LATE < PF; ++i)
@@ -349,7 +364,7 @@ struct Sweep : Rows<R, FWD> {
             } while (pn < P0 && hf[1].n > 0 && pn >= P1 && ((tw + jn * TW) & 1));
             const bool more = pn < P0;
             const Item nx = more ? make_item(hf, w, ns, tw, TW, pn, jn, lane) : it;
-            const uint32_t roffn = Rows<R, FWD>::template row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro) + (GRID ? 2u * (uint32_t)nx.base : 0u);
+            const uint32_t roffn = Rows<R, KD>::template row_off<TEAM>(d, nx.h ? hf[1] : hf[0], nx.h, nx.v0 + lane, rro) + (GRID ? 2u * (uint32_t)nx.base : 0u);
             // lanes from rg on are ghost columns: KR of them left of the window's right side, or (GRID: the
             // last strip but one may reach past the image) of the image's
             const int rg = it.t == ns - 1 ? 64 : GRID ? min(64 - KR / CPL, (w - it.base - KR) / CPL) : 64 - KR / CPL;
@@ -363,7 +378,7 @@ struct Sweep : Rows<R, FWD> {
                 }
             } else if (ns > 1) {
                 if (FWD && nsw > 1)  // the wave comes from another strip
-                    load_ev<TEAM, (int)CB * CPL / 2>(ring[PF - 1], re, (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(
+                    load_ev<TEAM, (int)CB * CPL / 2>(ring[PF - 1], re, (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, KD>::template row_off<TEAM>(
                                                                            d, it.h ? hf[1] : hf[0], it.h, it.v0 - 1, rro)), it.off);
                 const bool need = nsw > 1 || (it.t > 0 && lane < KR / CPL) || lane >= rg;
                 const uint32_t krow = (uint32_t)((it.h ? hf[0].B : 0) + it.v0 / R - 1) * ckrow;
@@ -383,10 +398,10 @@ struct Sweep : Rows<R, FWD> {
                     }
                     bool ok = true;
 #pragma unroll
-                    for (int c = 0; c < CPL; ++c) ok = ok && ((x[c] & 0x1FFu) == tag || (GRID && em[c]));
+                    for (int c = 0; c < CPL; ++c) ok = ok && ((x[c] & TAG) == tag || (GRID && em[c]));
                     if (__all(ok || !need)) {
 #pragma unroll
-                        for (int c = 0; c < CPL; ++c) Q[c] = need ? x[c] >> 9 | (GRID ? em[c] : 0u) : Q[c];
+                        for (int c = 0; c < CPL; ++c) Q[c] = need ? x[c] >> SH | (GRID ? em[c] : 0u) : Q[c];
                         break;
                     }
                     if (wait.late(d)) return false;
@@ -402,16 +417,16 @@ struct Sweep : Rows<R, FWD> {
                 if constexpr (EDGE) {
 #pragma unroll
                     for (int c = 0; c < CPL; ++c)
-                        __builtin_amdgcn_raw_buffer_store_b32((Q[c] << 9) | tag, rck, (int)(em[c] ? kBufDrop : (uint32_t)(it.col0 + c) * 4u),
+                        __builtin_amdgcn_raw_buffer_store_b32((Q[c] << SH) | tag, rck, (int)(em[c] ? kBufDrop : (uint32_t)(it.col0 + c) * 4u),
                                                               (int)krow, 0);
                 } else {
                     const uint32_t ko = pub ? (uint32_t)it.col0 * 4u : kBufDrop;
                     if constexpr (CPL == 2) {
-                        __builtin_amdgcn_raw_buffer_store_b64((v2u){(Q[0] << 9) | tag, (Q[1] << 9) | tag}, rck, (int)ko, (int)krow, 0);
+                        __builtin_amdgcn_raw_buffer_store_b64((v2u){(Q[0] << SH) | tag, (Q[1] << SH) | tag}, rck, (int)ko, (int)krow, 0);
                     } else {
 #pragma unroll
                         for (int c = 0; c < CPL; c += 4)
-                            buf_st128(rck, (v4u){(Q[c] << 9) | tag, (Q[c + 1] << 9) | tag, (Q[c + 2] << 9) | tag, (Q[c + 3] << 9) | tag},
+                            buf_st128(rck, (v4u){(Q[c] << SH) | tag, (Q[c + 1] << SH) | tag, (Q[c + 2] << SH) | tag, (Q[c + 3] << SH) | tag},
                                       krow + ko + 4u * c);
                     }
                 }
@@ -463,18 +478,22 @@ struct Sweep : Rows<R, FWD> {
 
 // ----------------------------------------------------------------------------------------------
 // The carve engine: one image, carved by a team of G workgroups of NT threads.
-template <int CPL, int KR, int NT, bool FWD = false>
-struct Carver : Rows<block_rows(KR), FWD> {
+template <int CPL, int KR, int NT, Kind KD = kEnergy>
+struct Carver : Rows<block_rows(KR), KD> {
     static constexpr int R = block_rows(KR);  // rows of a backtrack block
-    using Half = typename Rows<R, FWD>::Half;
-    using Rows<R, FWD>::half_of;
-    using Rows<R, FWD>::energy_rsrc;
-    using Rows<R, FWD>::CB;
-    using Narrow = Sweep<CPL, KR, R, FWD>;
+    using Half = typename Rows<R, KD>::Half;
+    using Rows<R, KD>::half_of;
+    using Rows<R, KD>::energy_rsrc;
+    using Rows<R, KD>::CB;
+    using Rows<R, KD>::FWD;
+    using Rows<R, KD>::MSK;
+    using Rows<R, KD>::SH;
+    using Rows<R, KD>::TAG;
+    using Narrow = Sweep<CPL, KR, R, KD>;
     static constexpr bool HAS_WIDE = CPL == 4 && R == 32;
-    using Wide = std::conditional_t<HAS_WIDE, Sweep<8, 32, 32, FWD>, Narrow>;  // of the same blocks
+    using Wide = std::conditional_t<HAS_WIDE, Sweep<8, 32, 32, KD>, Narrow>;  // of the same blocks
     static constexpr int NW = NT / 64;      // waves per workgroup
-    static constexpr int PB = FWD ? R / 2 : R;   // rows of a backtrack block prefetched ahead
+    static constexpr int PB = CB == 4 ? R / 2 : R;   // rows of a backtrack block prefetched ahead
     static constexpr int BCPL = 4;            // columns per lane of a backtrack window
     static constexpr int BW = 64 * BCPL;      // columns of a backtrack window
     static constexpr int BS = BW - 2 * R;     // of which exact at the block's last row
@@ -495,7 +514,8 @@ struct Carver : Rows<block_rows(KR), FWD> {
 
     // ---- the middle (a4): the cheapest pair of T's and B's last rows, leftmost lower column, then
     // leftmost upper one (an image of one half: the leftmost minimum of T's last row).  Every
-    // workgroup of a team finds it by itself.  Key: M << 32 | lower column << 2 | (upper - lower + 1).
+    // workgroup of a team finds it by itself.  Key: M << KC | lower column << 2 | (upper - lower + 1).
+    static constexpr int KC = 18;
     template <bool TEAM>
     static __device__ __forceinline__ unsigned long long middle(const Img& d, Smem& sm, int w, int k) {
         constexpr int kC = TEAM ? 16 : 0;
@@ -505,7 +525,7 @@ struct Carver : Rows<block_rows(KR), FWD> {
         const uint32_t t0 = (uint32_t)(h0.B - 1) * ckrow;
         // one half: row t0 stands in for the missing lower one, and counts nothing
         const uint32_t b0 = h1.n ? (uint32_t)(h0.B + h1.B - 1) * ckrow : t0, bm = h1.n ? ~0u : 0u;
-        const uint32_t tag = seam_tag(k);
+        const uint32_t tag = seam_tag<KD>(k);
         unsigned long long best = ~0ull;
         for (int c0 = 4 * (int)threadIdx.x; c0 < w; c0 += 4 * NT) {
             uint32_t x[6], y[4];
@@ -514,8 +534,8 @@ struct Carver : Rows<block_rows(KR), FWD> {
             if constexpr (FWD) {
                 if (bm) {
                     const __amdgpu_buffer_rsrc_t re = energy_rsrc(d), rro = make_rsrc(d.ro, (uint32_t)d.H * 4u);
-                    const uint32_t ou = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(d, h0, 0, h0.B * R - 1, rro));
-                    const uint32_t od = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, FWD>::template row_off<TEAM>(d, h1, 1, h1.B * R - 1, rro));
+                    const uint32_t ou = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, KD>::template row_off<TEAM>(d, h0, 0, h0.B * R - 1, rro));
+                    const uint32_t od = (uint32_t)__builtin_amdgcn_readfirstlane(Rows<R, KD>::template row_off<TEAM>(d, h1, 1, h1.B * R - 1, rro));
                     const v4u u = __builtin_amdgcn_raw_buffer_load_b128(re, c0 * 4, (int)ou, kC);
                     const v4u v = __builtin_amdgcn_raw_buffer_load_b128(re, c0 * 4, (int)od, kC);
                     const uint32_t vl = __builtin_amdgcn_raw_buffer_load_b32(re, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)od, kC);
@@ -533,25 +553,25 @@ struct Carver : Rows<block_rows(KR), FWD> {
                 const v4u B = __builtin_amdgcn_raw_buffer_load_b128(rck, c0 * 4, (int)b0, kC);
                 x[0] = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 > 0 ? c0 * 4 - 4 : (int)kBufDrop, (int)t0, kC);
                 x[5] = __builtin_amdgcn_raw_buffer_load_b32(rck, c0 + 4 < w ? c0 * 4 + 16 : (int)kBufDrop, (int)t0, kC);
-                bool ok = (c0 == 0 || (x[0] & 0x1FFu) == tag) && (c0 + 4 >= w || (x[5] & 0x1FFu) == tag);
+                bool ok = (c0 == 0 || (x[0] & TAG) == tag) && (c0 + 4 >= w || (x[5] & TAG) == tag);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     x[c + 1] = T[c];
                     y[c] = B[c];
-                    ok = ok && (c0 + c >= w || ((T[c] & 0x1FFu) == tag && (B[c] & 0x1FFu) == tag));
+                    ok = ok && (c0 + c >= w || ((T[c] & TAG) == tag && (B[c] & TAG) == tag));
                 }
                 if (!TEAM || ok || wait.late(d)) break;
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if (c0 + c >= w) continue;
-                uint32_t m = x[c + 1] >> 9, dir = 1;
+                uint32_t m = x[c + 1] >> SH, dir = 1;
                 if (bm) {
-                    const uint32_t ml = (x[c] >> 9) + dl[c], mr = (x[c + 2] >> 9) + dr[c];
+                    const uint32_t ml = (x[c] >> SH) + dl[c], mr = (x[c + 2] >> SH) + dr[c];
                     if (c0 + c > 0 && ml <= m) m = ml, dir = 0;
                     if (c0 + c + 1 < w && mr < m) m = mr, dir = 2;
                 }
-                best = min(best, ((unsigned long long)(m + ((y[c] & bm) >> 9)) << 32) | (unsigned)((c0 + c) << 2) | dir);
+                best = min(best, (((unsigned long long)m + ((y[c] & bm) >> SH)) << KC) | (unsigned)((c0 + c) << 2) | dir);
             }
         }
 #pragma unroll
@@ -579,14 +599,14 @@ struct Carver : Rows<block_rows(KR), FWD> {
         const __amdgpu_buffer_rsrc_t rck = make_rsrc(d.xq, (uint32_t)d.P * ckrow);
         const int col0 = base + lane * BCPL;
         // lane l < R: row l; the others: the row before the block (of zeros before the first one)
-        const uint32_t roff = Rows<R, FWD>::template row_off<COH>(d, x, h, blk * R + (lane < R ? lane : -1), rro);
+        const uint32_t roff = Rows<R, KD>::template row_off<COH>(d, x, h, blk * R + (lane < R ? lane : -1), rro);
         auto load_keys = [&]() {
             return __builtin_amdgcn_raw_buffer_load_b128(rck, blk > 0 && col0 < w ? col0 * 4 : (int)kBufDrop,
                                                          (int)((uint32_t)(ckbase + max(blk, 1) - 1) * ckrow), COH ? 16 : 0);
         };
         v4u kv = load_keys();
         const uint32_t eo = (uint32_t)(col0 < w ? col0 : 0) * CB;
-        uint64_t ring[PB][FWD ? 2 : 1];
+        uint64_t ring[PB][CB == 4 ? 2 : 1];
 #pragma unroll
         for (int i = 0; i < PB; ++i)
             load_ev<COH, (int)CB * BCPL / 2>(ring[i], re, (uint32_t)__builtin_amdgcn_readlane(roff, i), eo);
@@ -610,7 +630,7 @@ struct Carver : Rows<block_rows(KR), FWD> {
             for (;;) {
                 bool ok = true;
 #pragma unroll
-                for (int c = 0; c < BCPL; ++c) ok = ok && (!valid[c] || (kv[c] & 0x1FFu) == seam_tag(k));
+                for (int c = 0; c < BCPL; ++c) ok = ok && (!valid[c] || (kv[c] & TAG) == seam_tag<KD>(k));
                 if (__all(ok) || wait.late(d)) break;
                 kv = load_keys();
             }
@@ -618,6 +638,12 @@ struct Carver : Rows<block_rows(KR), FWD> {
 #pragma unroll
         for (int c = 0; c < BCPL; ++c) {
             Q[c] = valid[c] ? kv[c] & ~0x1FFu : QINF;
+        }
+        // masked: costs of 31 bits in words of their own, Q holds only offset and tag
+        uint32_t M[BCPL], ml = ~0u, mr = ~0u;
+        if constexpr (MSK) {
+#pragma unroll
+            for (int c = 0; c < BCPL; ++c) M[c] = valid[c] ? kv[c] >> SH : ~0u, Q[c] = 0;
         }
         uint32_t left = QINF, right = QINF, p = 0;
         static_for<R>([&](auto I) {
@@ -651,6 +677,23 @@ struct Carver : Rows<block_rows(KR), FWD> {
                 }
 #pragma unroll
                 for (int c = 0; c < BCPL; ++c) P[c] = px[c];
+            } else if constexpr (MSK) {
+                ml = (uint32_t)__builtin_amdgcn_update_dpp((int)ml, (int)M[BCPL - 1], 0x138, 0xf, 0xf, false);
+                mr = (uint32_t)__builtin_amdgcn_update_dpp((int)mr, (int)M[0], 0x130, 0xf, 0xf, false);
+                uint32_t n[BCPL];
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) {
+                    const uint32_t a = c ? M[c - 1] : ml, b = c + 1 < BCPL ? M[c + 1] : mr;
+                    const uint32_t m = min3u(a, M[c], b);
+                    uint32_t q = M[c] == m ? t[c] + 5u : (c + 1 < BCPL ? t[c + 1] + 10u : right);
+                    q = a == m ? (c ? t[c - 1] : left) : q;
+                    n[c] = m + (uint32_t)(ring[i % PB][c >> 1] >> ((c & 1) * 32));
+                    if (EDGE) n[c] = valid[c] ? n[c] : ~0u;
+                    Q[c] = q;
+                    acc = __builtin_amdgcn_alignbit(q, acc, 2u);
+                }
+#pragma unroll
+                for (int c = 0; c < BCPL; ++c) M[c] = n[c];
             } else {
 #pragma unroll
                 for (int c = 0; c < BCPL; ++c) {
@@ -710,7 +753,7 @@ struct Carver : Rows<block_rows(KR), FWD> {
         const Half hf[2] = {half_of(d.H, d.mode, 0), half_of(d.H, d.mode, 1)};
         const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const __amdgpu_buffer_rsrc_t ranc = make_rsrc(d.anc, (uint32_t)d.P * (uint32_t)d.xw);
-        int cB = min(max((int)((key & 0xffffffffu) >> 2), 0), w - 1);
+        int cB = min(max((int)((key & ((1ull << KC) - 1)) >> 2), 0), w - 1);
         int b[2], c[2];
         b[0] = hf[0].B - 1;
         b[1] = hf[1].B - 1;  // -1 when there is no lower half
@@ -882,8 +925,8 @@ struct Carver : Rows<block_rows(KR), FWD> {
                 shift_rows<4, 1>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * 4, lane);
             } else {
                 const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
-                                              shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, 2)};
-                shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, 2), lane);
+                                              shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, (int)CB)};
+                shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, (int)CB), lane);
             }
         }
     }
@@ -904,7 +947,15 @@ struct Carver : Rows<block_rows(KR), FWD> {
         GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(gd->amin));
         const bool timer = rank == 0 && threadIdx.x == 0;  // one clock reader per image
         unsigned long long tm0 = 0, tm1 = 0, tm2 = 0;
+        // masked pixels left in the image (kMasked: the carve ends with the last of them)
+        int left = 0;
+        if constexpr (MSK) left = (int)__hip_atomic_load(&ctl->left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned bias = masked_bias(H, gd->C);
         for (int k = k_begin; k < k_end; ++k) {
+            if (MSK && left <= 0) {
+                k_end = k;
+                break;
+            }
             const int w = W - k;
             if (timer) tm0 = wall_clock64();
             {
@@ -919,13 +970,20 @@ struct Carver : Rows<block_rows(KR), FWD> {
                 else if (!HAS_WIDE || 2 * Narrow::strips(w) <= TW || w <= Wide::WINR) Narrow::template cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
                 else Wide::template cost_sweep<false, TEAM>(d, w, k, tw, TW, lane);
             }
+            if (MSK && timer) tm1 = wall_clock64();
             // (a team's waves go on to wait for the tags of what they need)
             if constexpr (!TEAM) __syncthreads();
             {
                 const Img d = fetch(gd);
                 const unsigned long long key = middle<TEAM>(d, sm, w, k);
-                if (rank == 0 && threadIdx.x == 0 && d.costs_out) *gp(d.costs_out + k) = (long long)(key >> 32);
-                if (timer) tm1 = wall_clock64();
+                long long cost = (long long)(key >> KC);
+                if constexpr (MSK) {  // the pixels outside the mask pay the bias here, those inside get it
+                    const int out = (int)(cost / bias);
+                    left -= H - out;
+                    cost -= (long long)H * bias;
+                }
+                if (rank == 0 && threadIdx.x == 0 && d.costs_out) *gp(d.costs_out + k) = cost;
+                if (!MSK && timer) tm1 = wall_clock64();
                 if constexpr (MAP) {
                     if (mode == 2) write_map<TEAM>(d, w, tw, TW, lane);
                 }
@@ -933,9 +991,10 @@ struct Carver : Rows<block_rows(KR), FWD> {
             }
             if (mode) break;
             if constexpr (!TEAM) __syncthreads();
+            if (MSK && timer) tm2 = wall_clock64();
             remove_rows<TEAM>(fetch(gd), w, k, ra, rb, lane);
             if (!team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
-            if (timer) tm2 = wall_clock64();
+            if (!MSK && timer) tm2 = wall_clock64();
             if constexpr (!FWD) {
                 const Img d = fetch(gd);
                 // ---- band energy (a2): only the new columns s-1 and s of each row changed.  Buffer
@@ -956,9 +1015,15 @@ struct Carver : Rows<block_rows(KR), FWD> {
                     const uint32_t e0 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s - 1);
                     const uint32_t e1 = energy_buf<TEAM>(rwk, br, bu, bd, w2, d.C, s);
                     if (rc + lane < rb) {
-                        uint16_t* er = d.e + (size_t)r * d.ep + o;
-                        if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = (uint16_t)e0;
-                        if (s < w2) *gp(er + s) = (uint16_t)e1;
+                        if constexpr (MSK) {
+                            uint32_t* er = reinterpret_cast<uint32_t*>(d.e + (size_t)r * d.ep) + o;
+                            if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = e0 + (*gp(er + s - 1) >= bias ? bias : 0u);
+                            if (s < w2) *gp(er + s) = e1 + (*gp(er + s) >= bias ? bias : 0u);
+                        } else {
+                            uint16_t* er = d.e + (size_t)r * d.ep + o;
+                            if (s - 1 >= 0 && s - 1 < w2) *gp(er + s - 1) = (uint16_t)e0;
+                            if (s < w2) *gp(er + s) = (uint16_t)e1;
+                        }
                     }
                 }
             }
@@ -985,8 +1050,8 @@ struct Carver : Rows<block_rows(KR), FWD> {
         }
         // ---- after the last seam, the carved rows go from wk (each from its start offset) to img
         const Img d = fetch(gd);
-        if (!mode && k_end == W - d.target_w && k_end > k_begin) {
-            const int nb = d.target_w * d.C;
+        if (!mode && (MSK || k_end == W - d.target_w) && k_end > k_begin) {
+            const int nb = (W - k_end) * d.C;
             for (int rc = ra; rc < rb; rc += 64) {
                 const int n = min(64, rb - rc);
                 const int rof = lane < n ? *gp(d.ro + rc + lane) : 0;
@@ -1008,6 +1073,7 @@ struct Carver : Rows<block_rows(KR), FWD> {
             }
             team_sync<TEAM>(gd, epoch, G, &sm.flag);
         }
+        if (MSK && rank == 0 && threadIdx.x == 0) ctl->left = (unsigned)left;
         return k_end;
     }
 
@@ -1045,7 +1111,7 @@ struct Carver : Rows<block_rows(KR), FWD> {
         __syncthreads();
         if (rank == 0 && threadIdx.x == 0) {
             ctl->done = (unsigned)kd;
-            if (kd == nseams) ctl->t_end = wall_clock64();
+            if (MSK || kd == nseams) ctl->t_end = wall_clock64();
             if (max_seams > 0) {  // every member ended this call at the same barrier count
                 ctl->ebase = epoch;
                 ctl->xmask = 0;

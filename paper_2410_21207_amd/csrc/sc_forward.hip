@@ -18,7 +18,7 @@
 
 namespace sc {
 
-using FwdCarver = Carver<4, kFwdKR, kFwdThreads, true>;
+using FwdCarver = Carver<4, kFwdKR, kFwdThreads, kForward>;
 
 // Batched forward carve: block b is member blk[b].y of the team of image blk[b].x (-1: no work).
 // Single image: the team's members are blocks xcd, xcd + 8, ... (the others exit at once).

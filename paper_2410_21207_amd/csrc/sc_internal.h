@@ -46,7 +46,8 @@ struct Ctl {
     // stop decision of the team's first member at the end of a seam
     unsigned ebase;
     unsigned stop;
-    unsigned pad[14];
+    unsigned left;  // object removal: masked pixels in the image
+    unsigned pad[13];
 };
 constexpr unsigned kStatusTimeout = 1u;    // a team barrier timed out
 constexpr unsigned kStatusPlacement = 2u;  // a team's workgroups were not on one XCD
@@ -102,6 +103,14 @@ __host__ __device__ constexpr int key_rows(int H, int kr, int mode) {
 // three past the image's last one.
 __host__ __device__ constexpr int key_pitch(int W) { return (W + 7) & ~3; }
 
+// What a pixel outside the mask costs more than one inside (object removal): over the e1 energy of
+// any whole seam, so fewer such pixels win before energy does.
+__host__ __device__ constexpr unsigned masked_bias(int H, int C) { return (unsigned)H * 510u * (unsigned)C + 1u; }
+// Whether the costs of half an image with that bias fit the 31 bits of a published key.
+__host__ __device__ constexpr bool masked_by_teams(int H, int C) {
+    return (unsigned long long)(split_row(H, 0) + 1) * masked_bias(H, C) < (1ull << 31);
+}
+
 // Launchers (sc_kernels.hip).  Return hipSuccess or the launch error.
 hipError_t launch_energy_i32(const uint8_t* img, int H, int W, int C, long long pitch, int32_t* out,
                              hipStream_t st);
@@ -146,8 +155,8 @@ hipError_t launch_fwt_prepare(const Img* imgs, int n, int max_rows, hipStream_t 
 hipError_t launch_fwt_carve(const Img* imgs, const int2* blk, int nblocks, int xcd, hipStream_t st);
 int fwt_blocks_per_cu();
 
-// Object removal with a mask (one 1024-thread workgroup per image, the forward kernel's limits:
-// frame width <= kFwdMaxW, frame rows <= kFwdMaxH).  The carved frame is h = H rows by W columns
+// Object removal with a mask (frame width <= kFwdMaxW, frame rows <= kFwdMaxH): a team of workgroups
+// of the carve engine per image (max_w 0), or one 1024-thread workgroup (max_w: the widest frame).  The carved frame is h = H rows by W columns
 // (the transpose of the image for horizontal seams).
 struct ObjCtl {
     int k;        // seams removed
@@ -159,6 +168,7 @@ struct ObjCtl {
     unsigned long long t_stage[3];      // device clock in: DP sweep; argmin + backtrack; removal
 };
 struct ObjImg {
+    Img c;                 // the frame for the carve engine: wk, e the plane of biased energies (dwords)
     uint8_t* wk;           // working image, H rows of wp bytes (64-byte aligned rows)
     uint8_t* mk;           // working mask, H rows of mp bytes (nonzero = masked)
     uint8_t* dirs;         // 2-bit direction map, rows grouped by four, db bytes per row group lane
@@ -171,6 +181,9 @@ struct ObjImg {
     long long out_pitch;
     int H, W, C, wp, mp, db, max_seams;
 };
+constexpr int kObjThreads = 512;
+constexpr int kObjKR = 64;
+constexpr int kObjMaxTeam = 16;
 hipError_t launch_obj_reset(ObjCtl* ctl, int n, hipStream_t st);
 hipError_t launch_obj_carve(const ObjImg* imgs, int n, int max_w, hipStream_t st);
 hipError_t launch_mask_bbox(const uint8_t* mask, int H, int W, long long mpitch, int* bbox, hipStream_t st);

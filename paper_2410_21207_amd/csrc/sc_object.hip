@@ -4,21 +4,28 @@
 // mask alike until no masked pixel remains.
 //
 // The masked energy of a pixel is its e1 energy minus B = h*510*C + 1 under the mask (h = rows of
-// the carved frame).  B exceeds the e1 energy of any whole seam, so over the paths reaching a
-// cell in row i (all of i+1 pixels) the masked cost E - B*m orders exactly like the pair
-// (q, E) with q = i+1-m, the number of unmasked pixels, compared first: the DP carries q and E as
-// one 64-bit key (q in the high word; E << 9 | ancestor offset in the low word, with the
-// direction tag in bits 7-8 while the three parents are compared) and never forms the negative
-// sum.  Ties fall to the leftmost parent and the leftmost last-row column, as in the plain carve,
-// so the seam is the oracle's minimum of E - B*m.
+// the carved frame).  B exceeds the e1 energy of any whole seam, so the masked cost E - B*m of a path
+// orders like the pair (q, E), q = the number of its unmasked pixels, compared first.  Ties fall to the
+// leftmost parent and the leftmost last-row column, as in the plain carve, so the seam is the
+// oracle's minimum of E - B*m.
 //
-// One 1024-thread workgroup carves one image (thread t owns columns [CPL*t, CPL*t + CPL)), in
-// the row-synchronous style of the forward-energy kernel: the e1 energy of every cell is computed
-// from the current pixels while the DP sweeps the rows (three pixel rows around the cell), so
-// there is no energy plane to keep up to date; neighbour keys cross threads through LDS with one
-// barrier per row; the 2-bit direction map and per-phase ancestor offsets drive the backtrack;
-// the removal shifts the pixel row and the mask row of every seam row in one pass.
-#include "sc_device.h"
+// By teams (kMasked): the carve engine on a plane of dwords e + (unmasked ? B : 0), which hold the
+// mask too, so the rows of the plane move with the pixels' and the two new energies of a row keep
+// their masks.  A path's cost q*B + E is exact in 31 bits while half the frame's rows times B are
+// below 2^31 (1670 rows of three channels); published keys then carry a one-bit tag, and the
+// backtrack keeps cost and ancestor offset in two words (10 instructions per column and row, where one
+// word takes five).  The seam's cost says how many masked pixels it takes, and the carve ends when none is left.  What bounds it
+// is the plain carve's chain of rows; 1080p with a mask of 401 x 201 and the size restored:
+// 198 ms by one workgroup (below), 27 ms by a team of 16.
+//
+// Taller frames: one 1024-thread workgroup carves one image (thread t owns columns [CPL*t, CPL*t +
+// CPL)), with (q, E) as one 64-bit key (q in the high word; E << 9 | ancestor offset in the low word,
+// with the direction tag in bits 7-8 while the three parents are compared): the e1 energy of every
+// cell is computed from the current pixels while the DP sweeps the rows (three pixel rows around the
+// cell), so there is no energy plane to keep up to date; neighbour keys cross threads through LDS
+// with one barrier per row; the 2-bit direction map and per-phase ancestor offsets drive the
+// backtrack; the removal shifts the pixel row and the mask row of every seam row in one pass.
+#include "sc_carver.h"
 
 namespace sc {
 namespace obj {
@@ -352,6 +359,84 @@ struct Carver : PixRow<C, CPL> {
 
 }  // namespace obj
 
+// ---- by teams: the carve engine on a plane of 32-bit energies e + (unmasked ? bias : 0).
+using MaskedCarver = Carver<4, kObjKR, kObjThreads, kMasked>;
+
+__global__ void obj_begin_kernel(const ObjImg* __restrict__ imgs, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) reset_ctl(imgs[i].c);
+}
+
+// Rows row0, row0 + rstep, ... of the plane from the pixels and the mask; returns the thread's number
+// of masked pixels.
+template <int C>
+__device__ int obj_weight_rows(const Img& d, const uint8_t* mk, int mp, int row0, int rstep) {
+    const uint32_t bias = masked_bias(d.H, C);
+    int cnt = 0;
+    for (int y = row0; y < d.H; y += rstep) {
+        uint32_t* er = reinterpret_cast<uint32_t*>(d.e + (size_t)y * d.ep);
+        for (int x0 = 4 * (int)threadIdx.x; x0 < d.W; x0 += 4 * (int)blockDim.x) {
+            SrcRow<C> up, cur, dn;
+            up.load(d.wk, d.wp, d.W, max(y - 1, 0), x0);
+            cur.load(d.wk, d.wp, d.W, y, x0);
+            dn.load(d.wk, d.wp, d.W, min(y + 1, d.H - 1), x0);
+            const uint32_t m = *gp(reinterpret_cast<const uint32_t*>(mk + (size_t)y * mp + x0));
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                if (x0 + p >= d.W) continue;
+                const uint32_t l = x0 + p > 0 ? cur.px(p - 1) : cur.px(p);
+                const uint32_t r = x0 + p + 1 < d.W ? cur.px(p + 1) : cur.px(p);
+                const uint32_t e = __builtin_amdgcn_sad_u8(up.px(p), dn.px(p), __builtin_amdgcn_sad_u8(l, r, 0u));
+                const bool in = ((m >> (8 * p)) & 0xFFu) != 0u;
+                cnt += in;
+                *gp(er + x0 + p) = e + (in ? 0u : bias);
+            }
+        }
+    }
+    return cnt;
+}
+
+__global__ __launch_bounds__(256) void obj_weights_kernel(const ObjImg* __restrict__ imgs) {
+    const ObjImg* o = imgs + blockIdx.y;
+    const Img d = o->c;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    for (int x = t; x < d.H; x += nt) *gp(d.ro + x) = *gp(d.seam + x) = 0;
+    for (int x = t; x < d.P * d.xw; x += nt) *gp(d.xq + x) = 0u;
+    for (int x = t; x < d.ep / 2; x += nt) *gp(reinterpret_cast<uint32_t*>(d.e + (size_t)d.H * d.ep) + x) = 0u;
+    int cnt = 0;
+    switch (d.C) {
+        case 1: cnt = obj_weight_rows<1>(d, o->mk, o->mp, blockIdx.x, gridDim.x); break;
+        case 2: cnt = obj_weight_rows<2>(d, o->mk, o->mp, blockIdx.x, gridDim.x); break;
+        case 3: cnt = obj_weight_rows<3>(d, o->mk, o->mp, blockIdx.x, gridDim.x); break;
+        default: cnt = obj_weight_rows<4>(d, o->mk, o->mp, blockIdx.x, gridDim.x); break;
+    }
+#pragma unroll
+    for (int x = 32; x > 0; x >>= 1) cnt += __shfl_xor(cnt, x);
+    if ((threadIdx.x & 63) == 0 && cnt)
+        __hip_atomic_fetch_add(&gp(reinterpret_cast<Ctl*>(d.amin))->left, (unsigned)cnt, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Members of image blockIdx.y: blocks 0, 8, 16, ... (on one XCD); the others exit at once.
+__global__ __launch_bounds__(kObjThreads, 4) void obj_team_kernel(const ObjImg* __restrict__ imgs) {
+    __shared__ MaskedCarver::Smem sm;
+    const ObjImg* o = imgs + blockIdx.y;
+    const CAS Img* gd = (const CAS Img*)&o->c;
+    const int rank = blockIdx.x >> 3, G = gd->G;
+    if ((blockIdx.x & 7) || rank >= G) return;
+    MaskedCarver::carve_image(gd, rank, G, sm, 0);
+    if (rank == 0 && threadIdx.x == 0) {
+        const GAS Ctl* c = gp(reinterpret_cast<const Ctl*>(gd->amin));
+        GAS ObjCtl* r = gp(o->ctl);
+        r->k = __hip_atomic_load(&c->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : (int)c->done;
+        r->left = (int)__hip_atomic_load(&c->left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        r->w = gd->W - (int)c->done;
+        r->t_begin = c->t_begin;
+        r->t_end = c->t_end;
+        for (int i = 0; i < 3; ++i) r->t_stage[i] = c->t_stage[i];
+    }
+}
+
 // One workgroup per image of `imgs`.
 template <int CPL>
 __global__ __launch_bounds__(obj::NT, 1) void obj_carve_kernel(const ObjImg* __restrict__ imgs, int n) {
@@ -421,7 +506,11 @@ hipError_t launch_obj_reset(ObjCtl* ctl, int n, hipStream_t st) {
 
 hipError_t launch_obj_carve(const ObjImg* imgs, int n, int max_w, hipStream_t st) {
     if (max_w > kFwdMaxW) return hipErrorInvalidValue;
-    if (max_w <= 4096) hipLaunchKernelGGL(obj_carve_kernel<4>, dim3(n), dim3(obj::NT), 0, st, imgs, n);
+    if (max_w == 0) {
+        hipLaunchKernelGGL(obj_begin_kernel, dim3((n + 63) / 64), dim3(64), 0, st, imgs, n);
+        hipLaunchKernelGGL(obj_weights_kernel, dim3(512, n), dim3(256), 0, st, imgs);
+        hipLaunchKernelGGL(obj_team_kernel, dim3(8 * kObjMaxTeam, n), dim3(kObjThreads), 0, st, imgs);
+    } else if (max_w <= 4096) hipLaunchKernelGGL(obj_carve_kernel<4>, dim3(n), dim3(obj::NT), 0, st, imgs, n);
     else hipLaunchKernelGGL(obj_carve_kernel<8>, dim3(n), dim3(obj::NT), 0, st, imgs, n);
     return hipGetLastError();
 }

@@ -102,3 +102,22 @@ def test_forward_batch_of_lone_workgroups():
     res = fb.results()
     for i in range(0, len(imgs), 14):
         _check_forward(imgs[i], 3, res[i])
+
+
+# the last two: costs of half the image above 31 bits, which one workgroup carves with wider keys
+@pytest.mark.parametrize("H,W,C", [(1, 40, 1), (3, 300, 3), (64, 513, 3), (131, 257, 2), (300, 70, 4), (500, 1100, 3), (1640, 40, 3),
+                                   (2040, 24, 4), (2400, 30, 3)])
+def test_object_shapes(H, W, C):
+    """Masked costs at the edges of strips, halves and blocks, and on both sides of the 31-bit limit."""
+    rng = np.random.default_rng(H * 13 + W)
+    img = rng.integers(0, 3, size=(H, W, C)).astype(np.uint8)
+    mask = np.zeros((H, W), np.uint8)
+    for _ in range(3):
+        y, x = int(rng.integers(0, H)), int(rng.integers(0, W - 3))
+        mask[y:y + max(1, H // 5), x:x + 3] = 255
+    log("object shape", H, W, C)
+    o_out, o_info, o_seams, o_costs = oracle.remove_object(img, mask, 0)
+    out, info, seams, costs = api.remove_object(dev(img), dev(mask), 0)
+    assert info["k"] == o_info["k"] and info["left"] == o_info["left"]
+    assert np.array_equal(host(seams), o_seams) and np.array_equal(host(costs), o_costs)
+    assert np.array_equal(host(out), o_out)
