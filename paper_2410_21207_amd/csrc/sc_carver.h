@@ -6,28 +6,28 @@
 // Seams"), repeated once per seam on the current image (flowchart loop).
 //
 // Design (nothing here is a contraction, so no MFMA; every step is integer):
-//  * The energy plane is kept on the device as uint16 (max e = 510*C <= 2040).
-//  * The DP keeps a row of packed 32-bit keys in registers: bits [31:9] hold
-//    M, bits [8:2] an ancestor offset, bits [1:0] the direction tag.  Each lane
-//    owns CPL consecutive columns; neighbours in other lanes arrive through DPP
-//    wave shifts.  The three parent candidates get tags 0/1/2 (left, up,
-//    right) so one v_min3 picks the minimum AND the leftmost tie (reading R5),
-//    and the same add moves the ancestor offset.  The direction bits are
-//    shifted into a byte per lane with v_alignbit (half a byte with CPL 2,
-//    which a lane pair joins) and stored as a 2-bit map.
-//  * A wave owns a strip of S = 64*CPL - 2*KR columns and computes KR halo
-//    columns on each side, so it runs KR rows with no exchange at all
-//    ("ghost zone" tiling); waves exchange the last row of every KR-row phase
-//    through memory and a barrier.
-//  * At the last row of each phase every owned column records how far its
-//    minimal path moved within the phase; the backtrack then hops phase by
-//    phase (one load per phase) and walks the KR rows of every phase in
-//    parallel from an LDS window of the direction map.
-//  * Removal shifts the shorter side of each row one pixel toward the seam
-//    (the right side only when min-side removal is off), row-parallel with
-//    coalesced 16-byte slots, for the image and the energy plane alike;
-//    the energy is then recomputed only at the two new columns {s-1, s} of
-//    each row (the only cells whose stencil changed).
+//  * The cost table is swept from both ends of the image at once, costs only: a row is a v_min3 and an
+//    add per column and two DPP wave shifts, and the chain of dependent rows is half the image.
+//  * A wave owns a strip of columns and computes KR ghost columns on each side, so it runs KR rows
+//    without its neighbours ("ghost zone" tiling).  Every R rows the exact costs go out to memory
+//    with the seam's tag; whoever needs them (the neighbours at the next phase, the middle, the
+//    backtrack) loads until the tag shows, so a team's waves wait for data and not for each other.
+//  * The cheapest pair of neighbouring cells in the two middle rows gives the seam's cost and its two
+//    middle columns.
+//  * The backtrack computes the directions again, in blocks of R rows, all at once and only for 256
+//    columns around the path: keys M << 9 | u << 2 | tag carry the direction tag (0/1/2: left, up, right, so
+//    one minimum picks the value AND the leftmost tie, reading R5) and the ancestor's offset; the path
+//    then hops from block to block and is walked from registers.  No direction map goes to memory.
+//  * Removal shifts the shorter side of each row one pixel toward the seam (the right side only when
+//    min-side removal is off); the energy is then recomputed only at the two new columns {s-1, s} of each
+//    row (the only cells whose stencil changed).
+//
+// Three kinds of image share the engine (Kind below): energies, forward energy and masked energies.
+//
+// What bounds it (1920 x 1080 by 32 workgroups on MI355X, us per seam, in all 57, 122 before the sweep
+// from both ends): sweep 28 (issue: a wave starts an instruction every 5.3 cycles, 14 of them per
+// row, and waits about a microsecond for its neighbours at each of nine phases), middle 2.5, trace
+// 4.4, barrier and hops 7.7, walk 0.8, removal 10.3, barrier and new energies 4.2.
 #pragma once
 #include "sc_device.h"
 
@@ -173,7 +173,7 @@ struct Rows {
 
 };
 
-// ---- the cost sweep (a3): costs only, no directions; published as M << 9 | tag.
+// ---- the cost sweep (a3): costs only, no directions; published as M << SH | tag.
 //
 // A seam's cost table is swept from both ends of the image at once, T from the top row down to
 // the split row and B from the bottom row up, and the cheapest pair of adjacent cells in the two
@@ -926,7 +926,7 @@ struct Carver : Rows<block_rows(KR), KD> {
             } else {
                 const ShiftPlane planes[2] = {shift_plane(d.wk + (size_t)rc * d.wp, n, (uint32_t)d.wp, d.C),
                                               shift_plane(d.e + (size_t)rc * d.ep, n, (uint32_t)d.ep * 2u, (int)CB)};
-                shift_rows<4, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, (int)CB), lane);
+                shift_rows<3, 2>(planes, n, w, s, o, right, (d.minside ? w / 2 : w) * max(d.C, (int)CB), lane);
             }
         }
     }

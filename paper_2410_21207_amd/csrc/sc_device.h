@@ -104,18 +104,23 @@ __device__ __forceinline__ void static_for(F&& f) {
 //
 // The work is the row's aligned 16-byte slots in ascending order, one per lane.  A lane loads 16 bytes
 // from its slot (right: from a dword below it) and takes the dword above them from the next lane; its
-// new bytes are then one v_perm per dword, whichever the direction, and the bytes on the far side of
-// the seam pixel, in the seam's slot alone, are kept by that lane's own selectors.  At the other end
-// the last slot runs over bytes of the row that are not in use.  A pass stores 63 slots: its last lane
-// only lends its dword.  Moving right, a pass reads bytes that the pass before it writes, so a pass
-// must load before the pass before it stores.
+// new bytes are then one v_perm per dword, whichever the direction.  The seam's slot, where the bytes on
+// the far side of the seam pixel are kept, is left to lane l for row l, with selectors of its own: it
+// is loaded before anything is stored and no other slot reads it.  At the other end the last slot runs
+// over bytes of the row that are not in use.  A pass stores 63 slots: its last lane only lends its
+// dword.  Moving right, a pass reads bytes that the pass before it writes, so a pass must load before
+// the pass before it stores.
 //
 // What bounds it: accesses and their latency.  Every access is dword aligned: one that is not costs 64
 // cycles of the compute unit's address path instead of 16 (measured, 16 bytes per lane), which a
 // workgroup moving its rows with unaligned slots ran into (1200 x 1200 by one workgroup: 108 us per
-// seam so, 86 us aligned; 3840 x 2160 by 16: 42 us and 30 us).  NR rows of NP planes are one item, and the next item's loads go out
-// before this item's stores, so a wait for loads never covers a store (one counter for both, drained
-// in order); nothing branches between them, or the counter's state would be lost.
+// seam so, 86 us aligned; 3840 x 2160 by 16: 42 us and 30 us).  NR rows of NP planes are one item, and
+// the next item's loads go out before this item's stores, so a wait for loads never covers a store (one
+// counter for both, drained in order); nothing branches between them, or the counter's state would be
+// lost.  Handing the seam slot's selectors to its lane in every pass cost four readlanes per row and plane, a third of
+// the instructions: 1200 x 1200 by one workgroup 141 us of walk and removal so, 127 us with the
+// seams' slots apart; 1920 x 1080 by 32 24.5 and 22 us.  Three rows to an item: four spill (512 thumbnails 2.98 ms
+// against 2.75), two are as fast.
 struct ShiftPlane {
     __amdgpu_buffer_rsrc_t r;  // from 16 bytes below the first row to 64 past the last
     uint32_t pitch;            // bytes per row, a multiple of 16
@@ -132,9 +137,10 @@ __device__ __forceinline__ ShiftPlane shift_plane(void* row0, int n, uint32_t pi
 template <int LPR, int NR, int NP>
 __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int lane) {
     constexpr int RPA = 64 / LPR;  // rows per access
-    // per row and plane: the load offset of slot 0, the slots, the seam slot's selectors
+    // per row and plane: the load offset of slot 0, the slots, the seam's slot with its selectors
     int at[NP], cnt[NP];
-    uint32_t sel[NP][4];
+    uint32_t sel[NP][4], seam_off[NP], seam_up[NP];
+    v4u seam_v[NP];
 #pragma unroll
     for (int x = 0; x < NP; ++x) {
         const int px = p[x].px;
@@ -150,7 +156,20 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
             // a moved byte of dword i is byte px (right: 4 - px) further on in dwords i, i + 1
             sel[x][i] = 0x03020100u + (right ? 0x04040404u - (move & low) : move & ~low);
         }
+        seam_off[x] = cnt[x] > 0 ? (uint32_t)(at[x] + (right ? 16 * (cnt[x] - 1) : 0)) : kBufDrop;
+        seam_v[x] = __builtin_amdgcn_raw_buffer_load_b128(p[x].r, (int)seam_off[x], 0, 0);
+        seam_up[x] = __builtin_amdgcn_raw_buffer_load_b32(p[x].r, (int)(cnt[x] > 0 ? seam_off[x] + 16u : kBufDrop), 0, 0);
     }
+    auto store_seams = [&]() {
+#pragma unroll
+        for (int x = 0; x < NP; ++x) {
+            const uint32_t y[5] = {seam_v[x][0], seam_v[x][1], seam_v[x][2], seam_v[x][3], seam_up[x]};
+            v4u out;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = __builtin_amdgcn_perm(y[i + 1], y[i], sel[x][i]);
+            buf_st128(p[x].r, out, seam_off[x] + (right ? 4u : 0u));
+        }
+    };
     const int sub = lane / LPR, f0 = lane % LPR;
     auto row_of = [&](int v, int i) {  // row i's value, in the lanes that work on it
         if constexpr (LPR == 64) return __builtin_amdgcn_readlane(v, i);
@@ -160,8 +179,6 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
     struct Slot {
         v4u v;
         uint32_t vo;
-        int kf;  // the seam's slot
-        int li;  // the row, in sel
         int sd;
     };
     auto load = [&](Slot (&b)[NR][NP], int i, int fb) {  // rows i .. i + NR * RPA - 1, from slot fb of each
@@ -178,9 +195,7 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
                 const uint32_t off = (uint32_t)(base + 16 * f);
                 Slot& q = b[a][x];
                 q.v = __builtin_amdgcn_raw_buffer_load_b128(p[x].r, (int)(f <= c && c > 0 ? off : kBufDrop), 0, 0);
-                q.vo = f < c && f0 < LPR - 1 ? off + (sd ? 4u : 0u) : kBufDrop;
-                q.kf = (sd ? c - 1 : 0) - fb;
-                q.li = li;
+                q.vo = f < c && f != (sd ? c - 1 : 0) && f0 < LPR - 1 ? off + (sd ? 4u : 0u) : kBufDrop;
                 q.sd = sd;
                 if constexpr (LPR == 64) most = max(most, c);
             }
@@ -198,10 +213,7 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
                 const uint32_t all = 0x03020100u + (uint32_t)(q.sd ? 4 - p[x].px : p[x].px) * 0x01010101u;
                 v4u out;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t own = (uint32_t)row_of((int)sel[x][i], q.li);
-                    out[i] = __builtin_amdgcn_perm(y[i + 1], y[i], f0 == q.kf ? own : all);
-                }
+                for (int i = 0; i < 4; ++i) out[i] = __builtin_amdgcn_perm(y[i + 1], y[i], all);
                 buf_st128(p[x].r, out, q.vo);
             }
     };
@@ -213,15 +225,18 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
     };
     Slot A[NR][NP], B[NR][NP];
     step(load(A, i, fb));
+    bool mb = i < n;
+    step(load(B, i, fb));
+    store_seams();
     for (;;) {
-        const bool mb = i < n;
-        step(load(B, i, fb));
         store(A);
         if (!mb) break;
         const bool ma = i < n;
         step(load(A, i, fb));
         store(B);
         if (!ma) break;
+        mb = i < n;
+        step(load(B, i, fb));
     }
 }
 
@@ -229,7 +244,7 @@ __device__ __forceinline__ void shift_rows_lpr(const ShiftPlane (&p)[NP], int n,
 template <int NR, int NP>
 __device__ __forceinline__ void shift_rows(const ShiftPlane (&p)[NP], int n, int w, int s, int o, bool right, int most,
                                            int lane) {
-    if (most <= 208) shift_rows_lpr<16, NR / 2, NP>(p, n, w, s, o, right, lane);
+    if (most <= 208) shift_rows_lpr<16, 2, NP>(p, n, w, s, o, right, lane);
     else shift_rows_lpr<64, NR, NP>(p, n, w, s, o, right, lane);
 }
 
