@@ -404,9 +404,9 @@ sc_status sc_carve_noalloc(uint8_t* img, int H, int W, int C, int target_w, int 
 
 namespace {
 // Workspace of sc_insert_seams: the carve's own workspace, a scratch image the carve writes, the
-// seams in removal coordinates and in original columns, and the per-row Fenwick trees.
+// seams in removal coordinates and in original columns.
 struct InsertLayout {
-    size_t carve, scratch, cur, orig, tree, total;
+    size_t carve, scratch, cur, orig, total;
 };
 
 InsertLayout insert_layout(int H, int W, int C, int pitch, int k) {
@@ -420,8 +420,6 @@ InsertLayout insert_layout(int H, int W, int C, int pitch, int k) {
     off = sc::align_up(off + (size_t)std::max(k, 1) * H * 4, sc::kAlign);
     L.orig = off;
     off = sc::align_up(off + (size_t)std::max(k, 1) * H * 4, sc::kAlign);
-    L.tree = off;
-    off = sc::align_up(off + (size_t)(W + 1) * H * 4, sc::kAlign);
     L.total = off;
     return L;
 }
@@ -457,7 +455,7 @@ sc_status sc_insert_seams(const uint8_t* img, int H, int W, int C, int pitch, in
                      stream, img, tune);
         if (s != SC_OK) return s;
         hipError_t e = sc::launch_seam_origins(reinterpret_cast<const int32_t*>(base + L.cur), k, H, W,
-                                               reinterpret_cast<int32_t*>(base + L.tree), orig, st);
+                                               nullptr, orig, st);
         if (e != hipSuccess) return hip_fail(e, "seam origins launch");
     }
     hipError_t e = sc::launch_insert_seams(img, H, W, C, pitch, k, orig, out, out_pitch, st);

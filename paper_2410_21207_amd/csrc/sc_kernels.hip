@@ -308,34 +308,35 @@ __global__ void slot_write_kernel(Img* table, int slot, Img d) { table[slot] = d
 // ----------------------------------------------------------------------------------------------
 // Seam insertion (image enlargement).
 //
-// Original columns of seams recorded during removal: one thread per row keeps a Fenwick tree over
-// the row's columns still present (1 each) and finds seam j's column as the (s+1)-th present one,
-// then takes it out.  tree: (W + 1) * H int32, entry i of row r at tree[i * H + r] (neighbouring
-// threads touch neighbouring words).
-__global__ void seam_origins_kernel(const int32_t* __restrict__ seams, int k, int H, int W, int32_t* __restrict__ tree,
-                                    int32_t* __restrict__ orig) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+// Original columns of seams recorded during removal.  Seam j's column x is one of the row without
+// seams 0 .. j-1; putting them back, last first, moves it by one wherever x is not left of seam i:
+// x += (x >= s_i).  One wave per row, seam 64 b + l in lane l: a block's 64 columns are read once and
+// handed out by v_readlane, so a pair of seams costs three instructions for 64 lanes.
+// What bounds it: those instructions, k * k / 128 triples per row.  (A Fenwick tree per row, a thread
+// each, waits for 2 log W memory accesses one behind the other for every seam: 0.76 ms for 201 seams of
+// 1080 rows, and 1920 x 1080 widened by 480 took 26.5 ms with it and takes 25.0 ms so.)
+__global__ __launch_bounds__(256) void seam_origins_kernel(const int32_t* __restrict__ seams, int k, int H, int W,
+                                                           int32_t* __restrict__ orig) {
+    const int lane = threadIdx.x & 63;
+    const int r = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (r >= H) return;
-    int32_t* T = tree + r;
-    const size_t st = (size_t)H;
-    for (int i = 1; i <= W; ++i) *gp(T + i * st) = i & -i;
-    int top = 1;
-    while ((top << 1) <= W) top <<= 1;
-    for (int j = 0; j < k; ++j) {
-        int rem = min(max(*gp(seams + (size_t)j * H + r), 0), W - 1 - j) + 1;
-        int pos = 0;  // the largest index whose prefix count is below rem
-        for (int step = top; step > 0; step >>= 1) {
-            const int nx = pos + step;
-            if (nx <= W) {
-                const int v = *gp(T + nx * st);
-                if (v < rem) {
-                    pos = nx;
-                    rem -= v;
-                }
-            }
+    auto column = [&](int b) {
+        const int j = 64 * b + lane;
+        return j < k ? min(max(*gp(seams + (size_t)j * H + r), 0), W - 1 - j) : 0;
+    };
+    for (int b = 0; 64 * b < k; ++b) {
+        int y = column(b), x = y;
+        static_for<63>([&](auto I) {
+            constexpr int i = 62 - decltype(I)::value;
+            x += lane > i && x >= __builtin_amdgcn_readlane(y, i);
+        });
+        y = b > 0 ? column(b - 1) : 0;
+        for (int q = b - 1; q >= 0; --q) {
+            const int next = q > 0 ? column(q - 1) : 0;
+            static_for<64>([&](auto I) { x += x >= __builtin_amdgcn_readlane(y, 63 - decltype(I)::value); });
+            y = next;
         }
-        *gp(orig + (size_t)j * H + r) = pos;  // 0-based column of the (s+1)-th present one
-        for (int i = pos + 1; i <= W; i += i & -i) *gp(T + i * st) -= 1;
+        if (64 * b + lane < k) *gp(orig + (size_t)(64 * b + lane) * H + r) = x;
     }
 }
 
@@ -409,9 +410,8 @@ hipError_t launch_slot_write(Img* table, int slot, const Img& d, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_seam_origins(const int32_t* seams, int k, int H, int W, int32_t* tree, int32_t* orig,
-                               hipStream_t st) {
-    hipLaunchKernelGGL(seam_origins_kernel, dim3((H + 63) / 64), dim3(64), 0, st, seams, k, H, W, tree, orig);
+hipError_t launch_seam_origins(const int32_t* seams, int k, int H, int W, int32_t*, int32_t* orig, hipStream_t st) {
+    hipLaunchKernelGGL(seam_origins_kernel, dim3((H + 3) / 4), dim3(256), 0, st, seams, k, H, W, orig);
     return hipGetLastError();
 }
 

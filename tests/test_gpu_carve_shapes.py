@@ -121,3 +121,12 @@ def test_object_shapes(H, W, C):
     assert info["k"] == o_info["k"] and info["left"] == o_info["left"]
     assert np.array_equal(host(seams), o_seams) and np.array_equal(host(costs), o_costs)
     assert np.array_equal(host(out), o_out)
+
+
+@pytest.mark.parametrize("k", [1, 63, 64, 65, 128, 130, 299])
+def test_insert_blocks_of_seams(k):
+    """Original columns are found in blocks of 64 seams."""
+    img = np.random.default_rng(k).integers(0, 4, size=(7, 300, 1)).astype(np.uint8)
+    o_out, o_seams = oracle.insert_seams(img, k)
+    out, seams = api.insert_seams(dev(img), k)
+    assert np.array_equal(host(seams), o_seams) and np.array_equal(host(out), o_out)
