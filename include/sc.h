@@ -261,7 +261,7 @@ sc_status sc_carve_batch(const sc_job* jobs, int n, const sc_tune* tune, void* w
  * outside the row is clamped to it (so a border pixel costs its difference to
  * the pixel that becomes the border).  Ties, backtrack, removal and the seam
  * loop are those of sc_carve; the costs are recomputed from the current pixels
- * for every seam.  A team of at most 32 workgroups on one XCD carves one image;
+ * for every seam.  A team of at most 16 workgroups on one XCD carves one image;
  * its size follows from the image's (an estimate of a seam's time).
  *
  * sc_carve_forward: arguments as sc_carve (no tune); seams_out/costs_out

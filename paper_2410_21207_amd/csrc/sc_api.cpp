@@ -46,8 +46,8 @@ static_assert(sizeof(sc::Ctl) == 128, "ctl size");
 static_assert(sc::kWsImgOffset + sizeof(sc::Img) <= sc::kWsHeadBytes, "a single image's descriptor fits the header");
 
 constexpr int kMaxCostBound = 8388000;  // H*510*C: the column cost must fit 23 bits
-constexpr int kMaxTeamSingle = 16;      // largest team sc_carve and sc_dp_seam choose themselves
-constexpr int kMaxTeamForward = 32;     // and sc_carve_forward
+constexpr int kMaxTeamSingle = 16;      // largest team a single image gets without a tuned one
+static_assert(sc::kObjMaxTeam >= kMaxTeamSingle, "the object kernel's grid holds every team");
 constexpr int kDefaultTeamBatch = 16;   // largest team for one image of a batch
 
 sc_status check_image(int H, int W, int C, int pitch) {
@@ -123,13 +123,14 @@ double seam_us(int H, int w, int G, int nw) {
 
 constexpr int kTeamSizes[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
-// The team of a single image: the smallest that seam_us puts within 3 % of the fastest one.  At most
-// 16 by default: four streams (the hardware queues of a process) then find room for a whole team each among the
-// 64 workgroups of an XCD, whatever order their workgroups arrive in.
-int single_team(int H, int w, int nw, int most = kMaxTeamSingle) {
+// The team of a single image: the smallest that seam_us puts within 3 % of the fastest one.  At most 16
+// (forward energy at 1920 x 1080: 67.0 us per seam, 66.4 with 32): four streams (the hardware queues
+// of a process) then find room for a whole team each among the 64 workgroups of an XCD, whatever
+// order their workgroups arrive in.
+int single_team(int H, int w, int nw) {
     double best = 1e30;
     for (int g : kTeamSizes)
-        if (g <= most) best = std::min(best, seam_us(H, w, g, nw));
+        if (g <= kMaxTeamSingle) best = std::min(best, seam_us(H, w, g, nw));
     for (int g : kTeamSizes)
         if (seam_us(H, w, g, nw) <= 1.03 * best) return g;
     return 1;
@@ -893,7 +894,7 @@ extern "C" sc_status sc_carve_forward(uint8_t* img, int H, int W, int C, int tar
     char* base = static_cast<char*>(ws);
     sc::Ctl* ctl = reinterpret_cast<sc::Ctl*>(base + sizeof(WsHead));
     const size_t off_img = ctl_region(1);
-    const int G = single_team(H, W - (W - target_w) / 2, sc::kFwdThreads / 64, kMaxTeamForward);
+    const int G = single_team(H, W - (W - target_w) / 2, sc::kFwdThreads / 64);
     const sc::Img d = make_fwd_img(src, img, H, W, C, pitch, target_w, seams_out, costs_out,
                                    base + off_img + sc::align_up(sizeof(sc::Img), sc::kAlign), ctl, G);
     // header (magic, one image) and the descriptor, which the kernels read from the workspace
@@ -1202,7 +1203,7 @@ extern "C" sc_status sc_remove_object(const uint8_t* img, const uint8_t* mask, i
         d.c.bar = &tc->bar;
         d.c.status = &tc->status;
         d.c.minside = 1;
-        d.c.G = single_team(h, w0, sc::kObjThreads / 64, sc::kObjMaxTeam);
+        d.c.G = single_team(h, w0, sc::kObjThreads / 64);
     }
     sc::ObjImg* desc = reinterpret_cast<sc::ObjImg*>(base + L.desc);
     e = hipMemcpyAsync(desc, &d, sizeof(d), hipMemcpyHostToDevice, st);
