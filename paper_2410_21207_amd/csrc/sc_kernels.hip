@@ -7,33 +7,50 @@
 
 namespace sc {
 
-// ----------------------------------------------------------------------------------------------
-// e1 energy at one pixel of the current image (width w), indices clamped to the image.
-template <bool COH = false>
-__device__ __forceinline__ uint32_t energy_at(const uint8_t* img, long long pitch, int H, int w, int C, int y,
-                                              int x) {
-    const int xl = x > 0 ? x - 1 : 0, xr = x + 1 < w ? x + 1 : w - 1;
-    const int yu = y > 0 ? y - 1 : 0, yd = y + 1 < H ? y + 1 : H - 1;
-    const uint8_t* r = img + (long long)y * pitch;
-    const uint8_t* ru = img + (long long)yu * pitch;
-    const uint8_t* rd = img + (long long)yd * pitch;
-    uint32_t s = 0;
-    for (int c = 0; c < C; ++c) {
-        const int dx = (int)ld<COH>(r + xr * C + c) - (int)ld<COH>(r + xl * C + c);
-        const int dy = (int)ld<COH>(rd + x * C + c) - (int)ld<COH>(ru + x * C + c);
-        s += (uint32_t)(dx < 0 ? -dx : dx) + (uint32_t)(dy < 0 ? -dy : dy);
+// Standalone energy map (int32, dense): a thread takes 4 pixels of kEnergyRows rows from whole dwords
+// (SrcRow) and keeps the rows above and below in registers.  What bounds it: its loads' latency.  (A
+// byte load per channel and neighbour: 8 passes of energy, seam and removal at 1920 x 1080 took 886 us
+// with it and take 846 us so.)
+constexpr int kEnergyRows = 4;
+template <int C>
+__device__ void energy_rows(const uint8_t* img, int H, int W, long long pitch, int32_t* out, int y0, int x0) {
+    typedef uint32_t v4u_row __attribute__((ext_vector_type(4), aligned(4)));  // a row starts at any dword
+    SrcRow<C> row[kEnergyRows + 2];
+#pragma unroll
+    for (int i = 0; i < kEnergyRows + 2; ++i) row[i].load(img, pitch, W, min(max(y0 + i - 1, 0), H - 1), x0);
+    if (x0 >= W) return;
+#pragma unroll
+    for (int i = 0; i < kEnergyRows; ++i) {
+        if (y0 + i >= H) break;
+        const SrcRow<C>&up = row[i], &cur = row[i + 1], &dn = row[i + 2];
+        uint32_t e[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t l = x0 + p > 0 ? cur.px(p - 1) : cur.px(p);
+            const uint32_t r = x0 + p + 1 < W ? cur.px(p + 1) : cur.px(p);
+            e[p] = __builtin_amdgcn_sad_u8(up.px(p), dn.px(p), __builtin_amdgcn_sad_u8(l, r, 0u));
+        }
+        int32_t* o = out + (long long)(y0 + i) * W + x0;
+        if (x0 + 3 < W) {
+            *gp(reinterpret_cast<v4u_row*>(o)) = v4u_row{e[0], e[1], e[2], e[3]};
+        } else {
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                if (x0 + p < W) *gp(o + p) = (int32_t)e[p];
+        }
     }
-    return s;
 }
 
-// Standalone energy map (int32, dense).
-__global__ void energy_i32_kernel(const uint8_t* __restrict__ img, int H, int W, int C, long long pitch,
-                                  int32_t* __restrict__ out) {
-    const int y = blockIdx.y;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < W; x += gridDim.x * blockDim.x)
-        *gp(out + (long long)y * W + x) = (int32_t)energy_at(img, pitch, H, W, C, y, x);
+__global__ __launch_bounds__(256) void energy_i32_kernel(const uint8_t* __restrict__ img, int H, int W, int C,
+                                                         long long pitch, int32_t* __restrict__ out) {
+    const int y0 = blockIdx.y * kEnergyRows, x0 = 4 * (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    switch (C) {
+        case 1: energy_rows<1>(img, H, W, pitch, out, y0, x0); break;
+        case 2: energy_rows<2>(img, H, W, pitch, out, y0, x0); break;
+        case 3: energy_rows<3>(img, H, W, pitch, out, y0, x0); break;
+        default: energy_rows<4>(img, H, W, pitch, out, y0, x0); break;
+    }
 }
-
 
 // A single-image workspace starts with a header: magic, image count, then the descriptor itself
 // (read by the step-wise carve kernel), then the image's Ctl block.
@@ -424,7 +441,7 @@ hipError_t launch_insert_seams(const uint8_t* img, int H, int W, int C, long lon
 }
 
 hipError_t launch_energy_i32(const uint8_t* img, int H, int W, int C, long long pitch, int32_t* out, hipStream_t st) {
-    dim3 grid((W + 255) / 256, H);
+    dim3 grid((W + 1023) / 1024, (H + kEnergyRows - 1) / kEnergyRows);
     hipLaunchKernelGGL(energy_i32_kernel, grid, dim3(256), 0, st, img, H, W, C, pitch, out);
     return hipGetLastError();
 }

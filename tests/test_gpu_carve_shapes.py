@@ -130,3 +130,14 @@ def test_insert_blocks_of_seams(k):
     o_out, o_seams = oracle.insert_seams(img, k)
     out, seams = api.insert_seams(dev(img), k)
     assert np.array_equal(host(seams), o_seams) and np.array_equal(host(out), o_out)
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+@pytest.mark.parametrize("H,W", [(1, 1), (2, 3), (4, 4), (5, 5), (9, 1023), (3, 1025), (8, 1028)])
+def test_energy_map_groups(H, W, C):
+    """The energy map in groups of 4 columns by 4 rows, of rows that start at any byte."""
+    img = np.random.default_rng(H * W + C).integers(0, 256, size=(H, W, C), dtype=np.uint8)
+    flat = torch.zeros(H * (W * C + 5) + 1, dtype=torch.uint8, device="cuda")
+    rows = torch.as_strided(flat, (H, W, C), (W * C + 5, C, 1), 1)
+    rows.copy_(dev(img))
+    assert np.array_equal(host(api.energy(rows)), oracle.energy(img))
