@@ -34,7 +34,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "carve_batch_c4_traffic.json")
 FWD_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fwt_carve_batch_traffic.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2410_21207_amd", "csrc", f)
                   for f in ("sc_kernels.hip", "sc_batch.hip", "sc_carver.h", "sc_forward.hip", "sc_object.hip", "sc_device.h",
-                            "sc_internal.h")]
+                            "sc_team.h", "sc_internal.h")]
 
 
 def log(*a):

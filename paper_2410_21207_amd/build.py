@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libseamcarve.so")
 SOURCES = [os.path.join(CSRC, n) for n in ("sc_kernels.hip", "sc_batch.hip", "sc_object.hip", "sc_forward.hip",
                                             "sc_api.cpp")]
-HEADERS = [os.path.join(CSRC, n) for n in ("sc_internal.h", "sc_device.h", "sc_carver.h")] + [
+HEADERS = [os.path.join(CSRC, n) for n in ("sc_internal.h", "sc_device.h", "sc_team.h", "sc_carver.h")] + [
     os.path.join(ROOT, "include", "sc.h")]
 ARCH = os.environ.get("SC_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

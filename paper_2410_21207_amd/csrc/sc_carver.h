@@ -30,6 +30,7 @@
 // 4.4, barrier and hops 7.7, walk 0.8, removal 10.3, barrier and new energies 4.2.
 #pragma once
 #include "sc_device.h"
+#include "sc_team.h"
 
 namespace sc {
 
@@ -1029,11 +1030,10 @@ struct Carver : Rows<block_rows(KR), KD> {
             }
             // a team's time budget: its first member decides before the seam's last barrier, every
             // member reads the decision after it
-            if (deadline && G > 1 && k + 1 < k_end && rank == 0 && threadIdx.x == 0)
-                __hip_atomic_store(&ctl->stop, wall_clock64() >= deadline ? 1u : 0u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            const bool timed = deadline && G > 1 && k + 1 < k_end;
+            if (timed && rank == 0 && threadIdx.x == 0 && wall_clock64() >= deadline) stop_after<DevMem>(&ctl->stop, k);
             if (!FWD && !team_sync<TEAM>(gd, epoch, G, &sm.flag)) return k;
-            if (deadline && G > 1 && k + 1 < k_end && __hip_atomic_load(&ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) k_end = k + 1;
+            if (timed && stops_after<DevMem>(&ctl->stop, k)) k_end = k + 1;
             if (timer) {
                 const unsigned long long tm3 = wall_clock64();
                 ctl->t_stage[0] += tm1 - tm0;
@@ -1110,13 +1110,9 @@ struct Carver : Rows<block_rows(KR), KD> {
         }
         __syncthreads();
         if (rank == 0 && threadIdx.x == 0) {
-            ctl->done = (unsigned)kd;
             if (MSK || kd == nseams) ctl->t_end = wall_clock64();
-            if (max_seams > 0) {  // every member ended this call at the same barrier count
-                ctl->ebase = epoch;
-                ctl->xmask = 0;
-                ctl->stop = 0;
-            }
+            if (max_seams > 0) leave_call(ctl, kd, epoch);  // every member ended this call at the same barrier count
+            else ctl->done = (unsigned)kd;
         }
     }
 };

@@ -48,6 +48,18 @@ __device__ __forceinline__ T ld(const T* p) {
         return *gp(p);
 }
 
+// Words that a team shares, for the steps of sc_team.h.
+struct DevMem {
+    template <class W>
+    static __device__ __forceinline__ W load(GAS W* p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    template <class W>
+    static __device__ __forceinline__ void store(GAS W* p, W v) {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
 // Raw buffer descriptors (gfx9 word 3).  A raw buffer access adds a wave-uniform byte offset
 // (scalar register) to a per-lane byte offset (vector register); only the per-lane part is
 // range checked, and an access whose per-lane offset is >= the descriptor's size is dropped

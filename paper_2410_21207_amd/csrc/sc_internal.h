@@ -42,8 +42,8 @@ struct Ctl {
     unsigned xmask;                     // XCDs the team's workgroups ran on (bit per XCD)
     unsigned done;                      // seams removed so far (step-wise carving)
     unsigned long long t_stage[3];      // device clock spent in: DP sweep; backtrack + removal; band update
-    // step-wise carving by a team (serving): the barrier count the previous calls left, and the
-    // stop decision of the team's first member at the end of a seam
+    // step-wise carving by a team (serving): the barrier count the previous calls left, and one more
+    // than the seam after which the team's first member ended a call by its time budget (stop_after)
     unsigned ebase;
     unsigned stop;
     unsigned left;  // object removal: masked pixels in the image
