@@ -36,6 +36,10 @@
  *     nullable.
  *   - Thread safety: calls are reentrant; calls that share a workspace must be
  *     ordered on one stream.
+ *   - Teams: where several workgroups carve an image they sit on one XCD.  When
+ *     other work holds that XCD's slots a team carves with those of its
+ *     workgroups that start in time (0.2 ms to 10 ms, by the seams to remove),
+ *     down to one; the results are the same.
  */
 #ifndef SEAMCARVE_SC_H
 #define SEAMCARVE_SC_H
@@ -369,9 +373,8 @@ sc_status sc_remove_object(const uint8_t* img, const uint8_t* mask, int H, int W
  *   sc_slots_step_teams  sc_slots_step_timed where slot s is carved by a team of team[s]
  *                  workgroups (host array of n_slots entries, 1 = one workgroup, at most 32);
  *                  table_slots is the table's size as passed to sc_slot_table_bytes (>= n_slots):
- *                  the teams sit on one XCD each and are resident together (a team that finds
- *                  no room in this step carves with one workgroup); the budget is the team's
- *                  first member's.  Results equal those of sc_slots_step_timed.  The call writes
+ *                  the teams sit on one XCD each (a team that finds no room in this step carves
+ *                  with one workgroup); the budget is the team's first member's.  Results equal those of sc_slots_step_timed.  The call writes
  *                  the step's block plan into the table (after the descriptors) with an
  *                  asynchronous host-to-device copy from pageable memory.
  */

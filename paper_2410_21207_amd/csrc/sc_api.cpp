@@ -123,10 +123,11 @@ double seam_us(int H, int w, int G, int nw) {
 
 constexpr int kTeamSizes[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 
-// The team of a single image: the smallest that seam_us puts within 3 % of the fastest one.  At most 16
-// (forward energy at 1920 x 1080: 67.0 us per seam, 66.4 with 32): four streams (the hardware queues
-// of a process) then find room for a whole team each among the 64 workgroups of an XCD, whatever
-// order their workgroups arrive in.
+// The team of a single image: the smallest that seam_us puts within 3 % of the fastest one, at most 16
+// (forward energy at 1920 x 1080: 67.0 us per seam, 66.4 with 32; 3840 x 2160 and its transpose: 121 ms,
+// 101 with 32).  Single images all go to one XCD unless the caller names another, and it holds 64 workgroups: four streams
+// find room for a whole team of 16 each.  A team that does not find it carves with the workgroups that
+// came (join_team).
 int single_team(int H, int w, int nw) {
     double best = 1e30;
     for (int g : kTeamSizes)
@@ -760,9 +761,9 @@ extern "C" sc_status sc_slots_step_teams(const void* table, int table_slots, int
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return hip_fail(e, "device query");
-    // Teams first in the grid, each on one XCD, all of them resident at once (their members wait
-    // for each other); a team that finds no room carves with one workgroup.  Then one block per
-    // remaining slot (those need no company and may wait for a free slot of the device).
+    // Teams first in the grid, each on one XCD, with room for all of them at once (a team goes without
+    // the members that come late); a team that finds no room carves with one workgroup.  Then one
+    // block per remaining slot (those need no company and may wait for a free slot of the device).
     const int per_xcd = std::max(1, sc::carve_blocks_per_cu(v) * ncu / 8 * 3 / 4);
     std::vector<int> order;
     for (int s = 0; s < n_slots; ++s)
@@ -780,13 +781,13 @@ extern "C" sc_status sc_slots_step_teams(const void* table, int table_slots, int
         for (int r = 0; r < G; ++r) {
             const size_t b = (size_t)x + 8 * (size_t)(used[x] + r);
             if (plan.size() <= b) plan.resize(b + 1, make_int4(-1, 0, 0, 0));
-            plan[b] = make_int4(s, r, G, 0);
+            plan[b] = make_int4(s, r | G << 16, 0, 0);
         }
         used[x] += G;
         single[s] = 0;
     }
     for (int s = 0; s < n_slots; ++s)
-        if (single[s]) plan.push_back(make_int4(s, 0, 1, 0));
+        if (single[s]) plan.push_back(make_int4(s, 1 << 16, 0, 0));
     if (plan.size() > slot_plan_capacity(table_slots)) return fail(SC_EUNSUPPORTED, "step plan too large");
     hipStream_t st = (hipStream_t)stream;
     char* base = static_cast<char*>(const_cast<void*>(table));

@@ -16,28 +16,32 @@ __global__ __launch_bounds__(NT, 4) void carve_batch_kernel(const Img* __restric
     const int2 tr = teams[me.x];
     for (int i = 0; i < tr.y; ++i) {
         const CAS Img* gd = (const CAS Img*)(imgs + team_imgs[tr.x + i]);
-        CV::carve_image(gd, me.y, gd->G, sm, 0);
+        CV::carve_image(gd, me.y, gd->G, team_word(gd), sm, 0);
         __syncthreads();
     }
 }
 
 // Step-wise carve (serving): each image of the slot table advances by at most max_seams seams and
 // reports how many seams it has removed in total (-1 on a device error, -2 for an empty slot).
-// Without a plan block b carves slot b alone; with one, block b is member plan[b].y of the team of
-// plan[b].z workgroups that carves slot plan[b].x (-1: no work), the members of a team on one XCD.
+// Without a plan block b carves slot b alone; with one, block b is member plan[b].y & 0xFFFF of the team
+// of plan[b].y >> 16 workgroups that carves slot plan[b].x (-1: no work), the members of a team on one
+// XCD, 8 blocks apart.  The plan comes anew with every step, and with it, in the second half of the
+// entry of a team's member 0, the word by which the team forms.
 // The table is a device array of descriptors written by slot_write_kernel.
 template <int CPL, int KR, int NT>
 __global__ __launch_bounds__(NT, 4) void carve_steps_kernel(const Img* __restrict__ table, int n, int max_seams,
                                                             unsigned long long budget_ticks,
-                                                            int* __restrict__ progress, const int4* __restrict__ plan) {
+                                                            int* __restrict__ progress, int4* plan) {
     using CV = Carver<CPL, KR, NT>;
     __shared__ typename CV::Smem sm;
     int slot = (int)blockIdx.x, rank = 0, G = 1;
+    GAS unsigned long long* join = nullptr;
     if (plan) {
-        const int4 p = plan[blockIdx.x];
-        slot = p.x;
-        rank = p.y;
-        G = p.z;
+        slot = __builtin_amdgcn_readfirstlane(plan[blockIdx.x].x);
+        const int place = __builtin_amdgcn_readfirstlane(plan[blockIdx.x].y);
+        rank = place & 0xFFFF;
+        G = place >> 16;
+        join = gp(reinterpret_cast<unsigned long long*>(plan + blockIdx.x - 8 * rank) + 1);
     }
     if (slot < 0 || slot >= n) return;
     const CAS Img* gd = (const CAS Img*)(table + slot);
@@ -47,9 +51,9 @@ __global__ __launch_bounds__(NT, 4) void carve_steps_kernel(const Img* __restric
     }
     // a time budget (device wall clock ticks) ends the image's share after the seam that crosses
     // it, so a step's workgroups stay busy for about the same time
-    CV::carve_image(gd, rank, G, sm, max_seams, budget_ticks ? wall_clock64() + budget_ticks : 0ull);
+    CV::carve_image(gd, rank, G, join, sm, max_seams, budget_ticks ? wall_clock64() + budget_ticks : 0ull);
     __syncthreads();
-    if (rank == 0 && threadIdx.x == 0 && progress) {
+    if (CV::first_member(sm, G) && progress) {
         const GAS Ctl* ctl = gp(reinterpret_cast<const Ctl*>(gd->amin));
         progress[slot] = (ctl->status & (kStatusTimeout | kStatusPlacement)) ? -1 : (int)ctl->done;
     }
@@ -74,7 +78,7 @@ hipError_t launch_carve_steps(const Img* table, int n, int v, int max_seams, uns
 #define X(id, c, k, t)                                                                                        \
     case id:                                                                                                  \
         hipLaunchKernelGGL((carve_steps_kernel<c, k, t>), dim3(nb), dim3(t), 0, st, table, n, max_seams, budget_ticks, \
-                           progress, plan);                                                                        \
+                           progress, const_cast<int4*>(plan));                                                                        \
         break;
         SC_VARIANTS(X)
 #undef X

@@ -122,6 +122,11 @@ struct Wait {
     }
 };
 
+// The word by which an image's team forms; the image's first pass of every launch clears it.
+__device__ __forceinline__ GAS unsigned long long* team_word(const CAS Img* gd) {
+    return &gp(reinterpret_cast<Ctl*>(gd->amin))->join;
+}
+
 // Tag of a row's seam column (16 bits, columns below 65535), in the upper half of its word: never 0.
 __device__ __forceinline__ uint32_t seam_word(int k) { return ((uint32_t)k + 1u) << 16; }
 
@@ -511,6 +516,7 @@ struct Carver : Rows<block_rows(KR), KD> {
         unsigned long long red[NW];
         int flag;
         int stop;                      // step mode: the time budget is spent
+        Member me;                     // this workgroup's place in its team
     };
 
     // ---- the middle (a4): the cheapest pair of T's and B's last rows, leftmost lower column, then
@@ -1077,13 +1083,30 @@ struct Carver : Rows<block_rows(KR), KD> {
         return k_end;
     }
 
-    // Carve one image, or (max_seams > 0) continue it by at most max_seams seams.
+    // Carve one image, or (max_seams > 0) continue it by at most max_seams seams.  rank, G: this
+    // workgroup's place in the team that the launch means; join: the word by which those that come form
+    // one (0 at the launch; used with G > 1 only).  sm.me keeps the place taken (first_member).
     template <bool MAP = false>
-    static __device__ __forceinline__ void carve_image(const CAS Img* gd, int rank, int G, Smem& sm, int max_seams,
-                                                       unsigned long long deadline = 0) {
+    static __device__ __forceinline__ void carve_image(const CAS Img* gd, int rank, int G, GAS unsigned long long* join, Smem& sm,
+                                                       int max_seams, unsigned long long deadline = 0) {
         const Img d = fetch(gd);
         GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.amin));
         const int nseams = d.mode ? 1 : d.W - d.target_w;
+        if (G > 1) {  // (first: a workgroup that comes late must not read what its team is changing)
+            if (threadIdx.x == 0)
+                sm.me = join_team<DevMem, DevClock>(join, (int)xcc_id(), G, team_patience(max_seams > 0 ? min(nseams, max_seams) : nseams));
+            __syncthreads();
+            rank = __builtin_amdgcn_readfirstlane(sm.me.rank);
+            G = __builtin_amdgcn_readfirstlane(sm.me.size);
+            if (rank < 0) return;
+            // a team spread over several XCDs would not see each other's stores through sc1 loads, so
+            // such an image is flagged instead of carved
+            if (__builtin_amdgcn_readfirstlane((int)sm.me.apart)) {
+                if (rank == 0 && threadIdx.x == 0)
+                    __hip_atomic_fetch_or(gp(d.status), kStatusPlacement, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+        }
         const int k0 = max_seams > 0 ? (int)ctl->done : 0;
         const int k1 = max_seams > 0 ? min(nseams, k0 + max_seams) : nseams;
         if (k0 >= k1) return;
@@ -1091,29 +1114,19 @@ struct Carver : Rows<block_rows(KR), KD> {
         // a call that continues a carve (step mode) starts from the barrier count the previous
         // calls left behind, so a team's barrier counter never has to be reset between launches
         unsigned epoch = max_seams > 0 ? __hip_atomic_load(&ctl->ebase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-        int kd = k0;  // seams removed in total when this call ends
-        if (G > 1) {
-            // every member records its XCD; a team spread over several XCDs would not see each
-            // other's stores through sc1 loads, so such an image is flagged instead of carved
-            if (threadIdx.x == 0) __hip_atomic_fetch_or(&ctl->xmask, 1u << (xcc_id() & 31), __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-            if (!team_sync<true>(gd, epoch, G, &sm.flag)) return;
-            const unsigned m = __hip_atomic_load(&ctl->xmask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__popc(m) != 1) {
-                if (threadIdx.x == 0)
-                    __hip_atomic_fetch_or(gp(d.status), kStatusPlacement, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return;
-            }
-            kd = carve_seams<true, MAP>(gd, rank, G, sm, k0, k1, epoch, deadline);
-        } else {
-            kd = carve_seams<false, MAP>(gd, rank, G, sm, k0, k1, epoch, deadline);
-        }
+        const int kd = G > 1 ? carve_seams<true, MAP>(gd, rank, G, sm, k0, k1, epoch, deadline)
+                             : carve_seams<false, MAP>(gd, 0, 1, sm, k0, k1, epoch, deadline);  // seams removed in total
         __syncthreads();
         if (rank == 0 && threadIdx.x == 0) {
             if (MSK || kd == nseams) ctl->t_end = wall_clock64();
             if (max_seams > 0) leave_call(ctl, kd, epoch);  // every member ended this call at the same barrier count
             else ctl->done = (unsigned)kd;
         }
+    }
+
+    // After carve_image with the same G: whether this thread speaks for the team.
+    static __device__ __forceinline__ bool first_member(const Smem& sm, int G) {
+        return threadIdx.x == 0 && (G == 1 || sm.me.rank == 0);
     }
 };
 

@@ -58,6 +58,18 @@ struct DevMem {
     static __device__ __forceinline__ void store(GAS W* p, W v) {
         __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    template <class W>
+    static __device__ __forceinline__ W add(GAS W* p, W v) {
+        return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    template <class W>
+    static __device__ __forceinline__ bool swap(GAS W* p, W& seen, W v) {
+        return __hip_atomic_compare_exchange_strong(p, &seen, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+struct DevClock {
+    static __device__ __forceinline__ unsigned long long now() { return wall_clock64(); }
+    static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(1); }
 };
 
 // Raw buffer descriptors (gfx9 word 3).  A raw buffer access adds a wave-uniform byte offset
@@ -408,7 +420,7 @@ __device__ __forceinline__ void reset_ctl(const Img& d) {
     c->bar = 0;
     c->status = 0;
     c->t_begin = c->t_end = 0;
-    c->xmask = 0;
+    c->join = 0;
     c->done = 0;
     c->t_stage[0] = c->t_stage[1] = c->t_stage[2] = 0;
     c->ebase = 0;

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kFwdThreads, 4) void fwt_carve_kernel(const Img* __
     if (me.x < 0) return;
     const CAS Img* pd = (const CAS Img*)(imgs + me.x);
     if (me.y >= pd->G) return;
-    FwdCarver::carve_image(pd, me.y, pd->G, sm, 0);
+    FwdCarver::carve_image(pd, me.y, pd->G, team_word(pd), sm, 0);
 }
 
 // Copy-in for the forward carve: every pixel of src (or img) as one dword of wk (channels in the

@@ -39,15 +39,15 @@ struct Ctl {
     unsigned bar;                       // team barrier counter
     unsigned status;                    // error bits (kStatus*)
     unsigned long long t_begin, t_end;  // device clock when the carve started / ended
-    unsigned xmask;                     // XCDs the team's workgroups ran on (bit per XCD)
-    unsigned done;                      // seams removed so far (step-wise carving)
     unsigned long long t_stage[3];      // device clock spent in: DP sweep; backtrack + removal; band update
+    unsigned long long join;            // the team as it forms (join_team)
+    unsigned done;                      // seams removed so far (step-wise carving)
     // step-wise carving by a team (serving): the barrier count the previous calls left, and one more
     // than the seam after which the team's first member ended a call by its time budget (stop_after)
     unsigned ebase;
     unsigned stop;
     unsigned left;  // object removal: masked pixels in the image
-    unsigned pad[13];
+    unsigned pad[12];
 };
 constexpr unsigned kStatusTimeout = 1u;    // a team barrier timed out
 constexpr unsigned kStatusPlacement = 2u;  // a team's workgroups were not on one XCD

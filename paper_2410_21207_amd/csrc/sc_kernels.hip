@@ -316,7 +316,7 @@ __global__ __launch_bounds__(NT, 4) void carve_single_kernel(Img d, int xcd) {
     // round-robin by block index, so they share XCD `xcd`'s L2; the other blocks exit at once.
     if ((int)(blockIdx.x & 7) != xcd) return;
     const CAS Img* gd = (const CAS Img*)__builtin_amdgcn_kernarg_segment_ptr();  // d, the first argument
-    CV::template carve_image<true>(gd, blockIdx.x >> 3, d.G, sm, 0);
+    CV::template carve_image<true>(gd, blockIdx.x >> 3, d.G, team_word(gd), sm, 0);
 }
 
 // Slot management: write (or clear) one descriptor of the slot table.

@@ -422,10 +422,10 @@ __global__ __launch_bounds__(kObjThreads, 4) void obj_team_kernel(const ObjImg* 
     __shared__ MaskedCarver::Smem sm;
     const ObjImg* o = imgs + blockIdx.y;
     const CAS Img* gd = (const CAS Img*)&o->c;
-    const int rank = blockIdx.x >> 3, G = gd->G;
-    if ((blockIdx.x & 7) || rank >= G) return;
-    MaskedCarver::carve_image(gd, rank, G, sm, 0);
-    if (rank == 0 && threadIdx.x == 0) {
+    const int G = gd->G;
+    if ((blockIdx.x & 7) || (int)(blockIdx.x >> 3) >= G) return;
+    MaskedCarver::carve_image(gd, blockIdx.x >> 3, G, team_word(gd), sm, 0);
+    if (MaskedCarver::first_member(sm, G)) {
         const GAS Ctl* c = gp(reinterpret_cast<const Ctl*>(gd->amin));
         GAS ObjCtl* r = gp(o->ctl);
         r->k = __hip_atomic_load(&c->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : (int)c->done;

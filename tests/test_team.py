@@ -25,3 +25,11 @@ def _run(tmp_path, name, *flags):
 
 def test_every_member_reads_the_same_end_of_a_timed_call(tmp_path):
     assert "all members agreed" in _run(tmp_path, "step_stop")
+
+
+def test_a_team_is_whoever_has_come(tmp_path):
+    assert "all teams formed" in _run(tmp_path, "join")
+
+
+def test_a_team_is_whoever_has_come_under_a_thread_sanitizer(tmp_path):
+    assert "all teams formed" in _run(tmp_path, "join", "-fsanitize=thread")
