@@ -145,7 +145,8 @@ constexpr size_t kFwdSlack = 256;
 // Forward-energy carve by teams of workgroups on one XCD (sc_forward.hip).  A working pixel is one
 // dword; Img::e and ep are that plane.  blk: block -> (image, member), or nullptr for one image
 // whose members are blocks xcd, xcd + 8, ...  A batch holds at most kFwdBatchUnits units of
-// kFwdUnitCols columns (an image of up to kFwdUnitFirst columns is one).
+// kFwdUnitCols columns (an image of up to kFwdUnitFirst columns is one): a limit of the call, which
+// refuses what it always refused; the kernel and the planner take any number of images.
 constexpr int kFwdThreads = 512;
 constexpr int kFwdKR = 64;  // rows per sweep phase, four columns per lane
 constexpr int kFwdBatchUnits = 512;
