@@ -106,19 +106,21 @@ int resolve_variant(const sc_tune* t) {
 // both ends (by strips of 128 columns, or of 448 where those are more than the waves), the walk
 // back over blocks of rows, the removal and the band of new energies.  Fitted to 25 sizes from 64 x 64 to
 // 2100 x 2100 with six team sizes each on an idle MI355X; the team it ranks first is within 6 % of
-// the fastest there.  Forward energy takes up to a third more or less and ranks the teams the same way.
+// the fastest there, and within 10 % for flat images of 1 to 33 rows and up to 8000 columns.  Forward
+// energy takes up to a third more or less and ranks the teams the same way.
 double seam_us(int H, int w, int G, int nw) {
     const int tw = G * nw;
     const auto strips = [](int cols, int win, int step) { return cols <= win ? 1 : (cols - win + step - 1) / step + 1; };
-    const double rows = H / 2 + 16;
-    const int n4 = 2 * strips(w, 256, 128), n8 = 2 * strips(w, 504, 448);
+    const bool flat = H <= sc::kFlatRows;  // swept as one block
+    const double rows = flat ? sc::kFlatRows : H / 2 + 16;
+    const int n4 = (flat ? 1 : 2) * strips(w, 256, 128), n8 = (flat ? 1 : 2) * strips(w, 504, 448);
     const double sweep = n4 <= tw || w <= 504
                              ? rows * (0.047 + (n4 > 2 ? 0.0085 * std::max(0.0, (double)n4 / G - 2) : 0.0))
                              : rows * (0.045 + 0.0175 * n8 / G);
     const int each = (H + tw - 1) / tw, blocks = 2 * ((H + 63) / 64);
     const double back = 4.5 + 4.8 * ((blocks + tw - 1) / tw - 1);
     const double remove = 2.5 + each * (0.085 + (w <= 138 ? 0.2 : 0.45 + std::max(0, w - 600) * 0.00037));
-    return sweep + back + remove + (G > 1 ? 5.5 + 0.0012 * H + 0.002 * w : std::min(3.5, 0.006 * w));
+    return sweep + back + remove + (G > 1 ? 5.5 + 0.0012 * H + 0.002 * std::min(w, 2100) : std::min(3.5, 0.006 * w));
 }
 
 constexpr int kTeamSizes[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};

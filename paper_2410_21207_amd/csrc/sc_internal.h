@@ -88,10 +88,13 @@ constexpr int kMaxRows = 16448;  // rows of the tallest image (one channel; the 
 // Rows of a backtrack block of a variant with kr-row phases: whole blocks make up a phase, and a
 // block's ancestor offset fits 7 bits.
 __host__ __device__ constexpr int block_rows(int kr) { return kr % 32 == 0 ? 32 : kr / 2; }
-// The cost sweep runs down over rows [0, split_row) and up over the rest; with the direction map
-// (mode 2: the parent of every cell) it runs down over all of them.  A multiple of 4 or H.
+// The cost sweep runs down over rows [0, split_row) and up over the rest.  It runs down over all of
+// them with the direction map (mode 2: the parent of every cell), and in an image of one block, of which
+// either half would be swept as a whole block too (one workgroup: 8 x 8000 takes 32.5 us per seam with two
+// halves and 23.6 with one, 16 x 700 16.4 and 12.6).  A multiple of 4 or H.
+constexpr int kFlatRows = 32;
 __host__ __device__ constexpr int split_row(int H, int mode) {
-    const int m = mode == 2 ? H : ((H + 1) / 2 + 3) & ~3;
+    const int m = mode == 2 || H <= kFlatRows ? H : ((H + 1) / 2 + 3) & ~3;
     return m < H ? m : H;
 }
 // Blocks of both halves: the rows of published keys.
