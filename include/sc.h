@@ -115,7 +115,8 @@ sc_status sc_transpose_u8(const uint8_t* src, int H, int W, int C, int src_pitch
 /* Launch shape of the persistent carve kernel; NULL selects the built-in choice. */
 typedef struct {
     int team;    /* workgroups working together on one image (0 = default: by the image's
-                    size, at most 16; teams run on one XCD); in a batch the largest team */
+                    size, at most 16; teams run on one XCD).  In a batch the largest team
+                    (0 = 16); the image that takes longest may have twice that, at most 32 */
     int variant; /* kernel variant id (see sc_variant_count); -1 = default */
     int flags;   /* SC_TUNE_* bits */
 } sc_tune;
@@ -222,7 +223,7 @@ typedef struct {
     int nblocks;  /* workgroups of the carve launch */
     int variant;  /* kernel variant */
     int max_rows; /* tallest image */
-    int team;       /* largest team of workgroups for one image */
+    int team;       /* largest team of workgroups for one image (the longest may have twice that) */
     int teams_used; /* images carved by a team of more than one workgroup */
     size_t off_imgs, off_blk, off_teams, off_team_imgs; /* plan arrays inside ws */
 } sc_batch_info;

@@ -88,7 +88,6 @@ sc::Img make_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long lon
     d.wk = reinterpret_cast<uint8_t*>(base + L.wk);
     d.wp = L.wp;
     d.minside = 1;
-    d.amin = &ctl->amin;
     d.bar = &ctl->bar;
     d.status = &ctl->status;
     d.ep = L.ep;
@@ -906,7 +905,6 @@ sc::Img make_fwd_img(const uint8_t* src, uint8_t* img, int H, int W, int C, long
     d.ep = L.wp / 2;
     d.minside = 1;
     d.P = L.P;
-    d.amin = &ctl->amin;
     d.bar = &ctl->bar;
     d.status = &ctl->status;
     d.G = G;
@@ -1237,7 +1235,6 @@ extern "C" sc_status sc_remove_object(const uint8_t* img, const uint8_t* mask, i
         d.c.ro = reinterpret_cast<int32_t*>(base + L.ro);
         d.c.wk = wk;
         d.c.wp = L.wp;
-        d.c.amin = &tc->amin;
         d.c.bar = &tc->bar;
         d.c.status = &tc->status;
         d.c.minside = 1;

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(NT, 4) void carve_steps_kernel(const Img* __restric
     CV::carve_image(gd, rank, G, join, sm, max_seams, budget_ticks ? wall_clock64() + budget_ticks : 0ull);
     __syncthreads();
     if (CV::first_member(sm, G) && progress) {
-        const GAS Ctl* ctl = gp(reinterpret_cast<const Ctl*>(gd->amin));
+        const GAS Ctl* ctl = gp(reinterpret_cast<const Ctl*>(gd->bar));
         progress[slot] = (ctl->status & (kStatusTimeout | kStatusPlacement)) ? -1 : (int)ctl->done;
     }
 }

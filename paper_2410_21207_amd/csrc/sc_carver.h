@@ -24,10 +24,12 @@
 //
 // Three kinds of image share the engine (Kind below): energies, forward energy and masked energies.
 //
-// What bounds it (1920 x 1080 by 32 workgroups on MI355X, us per seam, in all 57, 122 before the sweep
-// from both ends): sweep 28 (issue: a wave starts an instruction every 5.3 cycles, 14 of them per
-// row, and waits about a microsecond for its neighbours at each of nine phases), middle 2.5, trace
-// 4.4, barrier and hops 7.7, walk 0.8, removal 10.3, barrier and new energies 4.2.
+// What bounds it (1920 x 1080 by 32 workgroups on MI355X, us per seam, in all 53, 122 before the sweep
+// from both ends): sweep and middle 28 (issue: a wave starts an instruction every 5.3 cycles, 14 of them
+// per row, and waits about a microsecond for its neighbours at each of nine phases), backtrack and
+// removal 20 (when they took 23: trace 4.4, barrier and hops 7.7, walk 0.8, removal 10.3), barrier and
+// new energies 4.  The workspace's address is worth 5 %: the same carve takes 51.5 to 54 at offsets of 0 to
+// 100 MB, the removal and the energies 3 of them.
 #pragma once
 #include "sc_device.h"
 #include "sc_team.h"
@@ -124,7 +126,7 @@ struct Wait {
 
 // The word by which an image's team forms; the image's first pass of every launch clears it.
 __device__ __forceinline__ GAS unsigned long long* team_word(const CAS Img* gd) {
-    return &gp(reinterpret_cast<Ctl*>(gd->amin))->join;
+    return &gp(reinterpret_cast<Ctl*>(gd->bar))->join;
 }
 
 // Tag of a row's seam column (16 bits, columns below 65535), in the upper half of its word: never 0.
@@ -835,7 +837,6 @@ struct Carver : Rows<block_rows(KR), KD> {
                 uint32_t* cw = sm.cw[hh];
                 int p = hh ? b[1] : b[0], j = hh ? c[1] : c[0];
                 const int low = p - (hh ? nblk[1] : nblk[0]) + 1;
-                bool run = true;
                 if (lane == 0) sm.jend[hh * BMAX + p] = j;
                 if constexpr (!TEAM) {
                     // the round's offsets are in LDS: block p's window j is wave (p0 - p) * nw + j of this half
@@ -851,11 +852,9 @@ struct Carver : Rows<block_rows(KR), KD> {
                         if (lane == 0) sm.jend[hh * BMAX + p] = j;
                     }
                     if (p == 0 && p >= low && j >= lo && j < hi) p = -1;
-                    run = false;
                 }
-                while (run) {
-                    const int j0 = j, p0 = p, m = min(TEAM ? Carver::CH : 8, p - max(low, 1) + 1);
-                    constexpr int CH = TEAM ? Carver::CH : 8;  // (a lone workgroup's round has few blocks)
+                for (bool run = TEAM; run;) {
+                    const int j0 = j, p0 = p, m = min(CH, p - max(low, 1) + 1);
                     v4u v[CH];
                     // byte window [o, o + 1024) of every block's row, from a multiple of 16 at or below
                     // j0 - 512; what lies before the array is dropped
@@ -863,8 +862,7 @@ struct Carver : Rows<block_rows(KR), KD> {
 #pragma unroll
                     for (int i = 0; i < CH; ++i) {
                         const int bo = (ckb + p0 - i) * d.xw + w0 + 16 * lane;
-                        v[i] = __builtin_amdgcn_raw_buffer_load_b128(ranc, (int)(i < m && bo >= 0 ? (uint32_t)bo : kBufDrop), 0,
-                                                                     TEAM ? 16 : 0);
+                        v[i] = __builtin_amdgcn_raw_buffer_load_b128(ranc, (int)(i < m && bo >= 0 ? (uint32_t)bo : kBufDrop), 0, 16);
                     }
 #pragma unroll
                     for (int i = 0; i < CH; ++i) *reinterpret_cast<v4u*>(cw + i * 256 + 4 * lane) = v[i];
@@ -967,7 +965,7 @@ struct Carver : Rows<block_rows(KR), KD> {
         const int H = gd->H, W = gd->W, mode = gd->mode;
         const int rpw = (H + TW - 1) / TW;
         const int ra = min(H, tw * rpw), rb = min(H, ra + rpw);  // rows this wave owns
-        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(gd->amin));
+        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(gd->bar));
         const bool timer = rank == 0 && threadIdx.x == 0;  // one clock reader per image
         // The stage clocks run in LDS: in registers they would be alive through the stages they measure.
         // (512 thumbnails up to 250 x 250: 2.61 ms with them there, 2.50 so.)
@@ -1109,7 +1107,7 @@ struct Carver : Rows<block_rows(KR), KD> {
     static __device__ __forceinline__ void carve_image(const CAS Img* gd, int rank, int G, GAS unsigned long long* join, Smem& sm,
                                                        int max_seams, unsigned long long deadline = 0) {
         const Img d = fetch(gd);
-        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.amin));
+        GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.bar));
         const int nseams = d.mode ? 1 : d.W - d.target_w;
         if (G > 1) {  // (first: a workgroup that comes late must not read what its team is changing)
             if (threadIdx.x == 0)

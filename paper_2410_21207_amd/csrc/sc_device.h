@@ -36,18 +36,6 @@ __device__ __forceinline__ T fetch(const CAS T* p) {
     return *p;
 }
 
-// Load of data that another workgroup of the same team may have written since this CU last read
-// it.  A relaxed device-scope atomic load is a plain load with the sc1 cache bit: it skips the
-// CU's L1 and reads the XCD's L2, where the other workgroup's stores have landed (a team always
-// runs on one XCD).  Single-workgroup carves use ordinary loads.
-template <bool COH, class T>
-__device__ __forceinline__ T ld(const T* p) {
-    if constexpr (COH)
-        return __hip_atomic_load(gp(const_cast<T*>(p)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-        return *gp(p);
-}
-
 // Words that a team shares, for the steps of sc_team.h.
 struct DevMem {
     template <class W>
@@ -85,9 +73,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, kBufWord3);
 }
 
-// A dword at a lane's byte offset into a buffer; COH sets the sc1 bit (the load reads the XCD's L2,
-// like ld<true>).  Being a plain load, it leaves the compiler's memory-counter waits for later
-// loads exact, where an atomic load in flight makes it wait for every outstanding access.
+// A dword at a lane's byte offset into a buffer.  COH, for data that another workgroup of the same team
+// may have written since this compute unit last read it, sets the sc1 bit: the load skips the unit's L1 and
+// reads the XCD's L2, where the other workgroup's stores have landed (a team always runs on one XCD).
+// It is a plain load and leaves the compiler's memory-counter waits for later loads exact, where an
+// atomic load in flight makes it wait for every outstanding access.
 template <bool COH>
 __device__ __forceinline__ uint32_t buf_ld32(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, 0, COH ? 16 : 0);
@@ -314,7 +304,7 @@ __device__ __forceinline__ void copy_bytes_wave(uint8_t* dst, const uint8_t* src
 }
 
 // ----------------------------------------------------------------------------------------------
-// Single-workgroup DP helpers (forward energy, object removal).
+// Helpers of the single-workgroup DP (object removal on tall frames).
 
 // v_min3_u32: the smallest of three tagged keys (ties go to the smallest tag, i.e. the leftmost).
 __device__ __forceinline__ uint32_t min3u(uint32_t a, uint32_t b, uint32_t c) {
@@ -377,7 +367,7 @@ struct PixRow {
 // Team barrier.  One workgroup: a workgroup barrier.  A team of G workgroups on one XCD: each
 // thread waits for its own stores to reach the L2 (vmcnt), then one thread per workgroup bumps
 // the image's counter with a device-scope atomic and polls it with device-scope loads until all
-// G have arrived; readers then fetch shared data with sc1 loads (see ld<true>).  The wait is
+// G have arrived; readers then fetch shared data with sc1 loads (see buf_ld32).  The wait is
 // bounded: after ~10 s it flags the image and every member gives up on it.
 template <bool TEAM>
 __device__ __forceinline__ bool team_sync(const CAS Img* gd, unsigned& epoch, int G, int* flag) {
@@ -415,8 +405,7 @@ __device__ __forceinline__ bool team_sync(const CAS Img* gd, unsigned& epoch, in
 
 // Reset the control words of one image (every carve launch starts from them).
 __device__ __forceinline__ void reset_ctl(const Img& d) {
-    GAS Ctl* c = gp(reinterpret_cast<Ctl*>(d.amin));
-    c->amin = ~0ull;
+    GAS Ctl* c = gp(reinterpret_cast<Ctl*>(d.bar));
     c->bar = 0;
     c->status = 0;
     c->t_begin = c->t_end = 0;

@@ -21,13 +21,12 @@ struct Img {
     uint32_t* xq;  // published DP keys: P rows of `xw` uint32, the last row of every block
     int32_t* seam; // current seam, H
     int32_t* ro;   // per row: physical column of the row's first pixel (min-side removal), H
-    uint8_t* wk;   // working copy of the image, H rows of `wp` bytes (64-byte aligned rows)
-    unsigned long long* amin;  // packed (cost << 32 | column) argmin of the current seam
-    unsigned* bar;             // team barrier counter
-    unsigned* status;          // error bits
+    uint8_t* wk;   // working copy of the image, H rows of `wp` bytes, a multiple of 16
+    unsigned* bar;             // the control words (Ctl); their first is the team barrier counter
+    unsigned* status;          // of them the error bits
     int ep, xw, P;             // pitches; rows of published keys
     int wp;                    // bytes per row of wk, at least 16 more than its pixels
-    int G;                     // team size (workgroups) carving this image
+    int G;                     // workgroups that are to carve this image (those that come do)
     int mode;                  // 0 = carve, 1 = one seam only, no removal (sc_dp_seam), 2 = the same
                                // and the direction of every cell as a byte in img (H x W)
     int minside;               // 1 = remove a seam pixel by moving the shorter side of its row
@@ -35,7 +34,6 @@ struct Img {
 
 // Control words of one image (zeroed by the energy pass of every launch).
 struct Ctl {
-    unsigned long long amin;            // packed (cost << 32 | column) argmin of the current seam
     unsigned bar;                       // team barrier counter
     unsigned status;                    // error bits (kStatus*)
     unsigned long long t_begin, t_end;  // device clock when the carve started / ended
@@ -47,7 +45,7 @@ struct Ctl {
     unsigned ebase;
     unsigned stop;
     unsigned left;  // object removal: masked pixels in the image
-    unsigned pad[12];
+    unsigned pad[14];
 };
 constexpr unsigned kStatusTimeout = 1u;    // a team barrier timed out
 constexpr unsigned kStatusPlacement = 2u;  // a team's workgroups were not on one XCD
@@ -114,7 +112,7 @@ __host__ __device__ constexpr bool masked_by_teams(int H, int C) {
     return (unsigned long long)(split_row(H, 0) + 1) * masked_bias(H, C) < (1ull << 31);
 }
 
-// Launchers (sc_kernels.hip).  Return hipSuccess or the launch error.
+// Launchers.  Return hipSuccess or the launch error.
 hipError_t launch_energy_i32(const uint8_t* img, int H, int W, int C, long long pitch, int32_t* out,
                              hipStream_t st);
 hipError_t launch_prepare_single(const Img& d, hipStream_t st);          // energy plane (+copy, ctl zero)

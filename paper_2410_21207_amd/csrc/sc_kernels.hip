@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void energy_i32_kernel(const uint8_t* __restri
 // A single-image workspace starts with a header: magic, image count, then the descriptor itself
 // (read by the step-wise carve kernel), then the image's Ctl block.
 __device__ __forceinline__ void write_single_header(const Img& d) {
-    char* h = reinterpret_cast<char*>(d.amin) - kWsHeadBytes;
+    char* h = reinterpret_cast<char*>(d.bar) - kWsHeadBytes;
     reinterpret_cast<uint32_t*>(h)[0] = kWsMagic;
     reinterpret_cast<uint32_t*>(h)[1] = 1u;
     *reinterpret_cast<Img*>(h + kWsImgOffset) = d;
@@ -73,8 +73,8 @@ __device__ __forceinline__ void write_single_header(const Img& d) {
 // source row is read once per tile, as the aligned dwords covering the thread's 4 pixels and one
 // pixel on each side, realigned to the row start with v_alignbyte (rows may start anywhere); the
 // rows above and below stay in registers as the tile moves down.  The energy goes out as one
-// 8-byte store of 4 uint16 per thread, the pixels as C dword stores into the 64-byte aligned rows
-// of wk.
+// 8-byte store of 4 uint16 per thread, the pixels as C dword stores into the rows of
+// wk, which start at multiples of 16 bytes.
 constexpr int kTileRows = 32;
 constexpr int kTileCols = 1024;  // 256 threads x 4 pixels
 
@@ -180,96 +180,59 @@ __global__ void prepare_from_i32_kernel(Img d, const int32_t* __restrict__ e) {
 }
 
 // ----------------------------------------------------------------------------------------------
-// In-place left shift of row segments by one pixel, one wave.  Segment a: dst bytes [a_lo, a_hi)
-// get src bytes shifted by sh_a (1..4); segment b likewise (sh_b).  The work is cut into 16-byte
-// slots aligned to absolute addresses; a pass gives each lane U slots of the concatenated slot
-// list and issues every load of the pass before any store.  A slot's store writes only inside the
-// slot, and the bytes it needs beyond its end belong to the next slot of the same segment, which
-// is loaded in the same pass or a later one -- so the in-place update is hazard free.
-struct Seg {
-    uint8_t* base;  // 16-byte aligned (wave-uniform)
-    int lo, hi;     // the segment is [base + lo, base + hi)
-    int sh;         // shift in bytes, 1..4
-    int n;          // 16-byte slots covering it
-};
-
-__device__ __forceinline__ Seg make_seg(uint8_t* lo_p, uint8_t* hi_p, int sh) {
-    Seg g;
-    const int off = (int)((uintptr_t)lo_p & 15);
-    g.base = lo_p - off;
-    g.lo = off;
-    g.hi = hi_p > lo_p ? off + (int)(hi_p - lo_p) : off;
-    g.sh = sh;
-    g.n = g.hi > g.lo ? ((g.hi - 1) >> 4) + 1 : 0;
-    return g;
-}
-
-template <int U, bool COH>
-__device__ __forceinline__ void seg_load(const Seg& g, int fb, int lane, uint32_t (&D)[U][5]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int f = fb + u * 64 + lane;
-#pragma unroll
-        for (int i = 0; i < 5; ++i) D[u][i] = 0;
-        if (f < g.n) {
-            const uint32_t so = (uint32_t)f << 4;  // slot offset from the uniform base
-            const uint64_t* q = reinterpret_cast<const uint64_t*>(g.base + so);
-            const uint64_t v0 = ld<COH>(q), v1 = ld<COH>(q + 1);
-            D[u][0] = (uint32_t)v0; D[u][1] = (uint32_t)(v0 >> 32);
-            D[u][2] = (uint32_t)v1; D[u][3] = (uint32_t)(v1 >> 32);
-            if ((int)so + 16 - g.sh < g.hi) D[u][4] = ld<COH>(reinterpret_cast<const uint32_t*>(g.base + so + 16));
-        }
-    }
-}
-
+// In-place left shift of a row segment by one pixel, one wave: the bytes of [lo, hi) take the values sh
+// (1..4) bytes to their right.  The work is cut into 16-byte slots aligned to absolute addresses; a pass
+// gives each lane U slots and issues every load of the pass before any store.  A slot's store writes
+// only inside the slot, and the bytes it needs beyond its end belong to the next slot, loaded in the
+// same pass or a later one, so the in-place update is hazard free.
 template <int U>
-__device__ __forceinline__ void seg_store(const Seg& g, int fb, int lane, const uint32_t (&D)[U][5]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int f = fb + u * 64 + lane;
-        if (f >= g.n) continue;
-        const int so = f << 4;
-        uint8_t* sp = g.base + so;
-        uint32_t o[4];
-        if (g.sh == 4) {
-            o[0] = D[u][1]; o[1] = D[u][2]; o[2] = D[u][3]; o[3] = D[u][4];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(D[u][i + 1], D[u][i], (uint32_t)g.sh);
-        }
-        if (so >= g.lo && so + 16 <= g.hi) {
-            *gp(reinterpret_cast<u32x4*>(sp)) = u32x4{o[0], o[1], o[2], o[3]};
-        } else {
-            // a slot at a segment edge: store only the bytes inside the segment, one predicated
-            // byte store per position (static offsets and register indices)
-            const int k0 = so > g.lo ? 0 : g.lo - so;
-            const int k1 = so + 16 < g.hi ? 16 : g.hi - so;
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-                if (k >= k0 && k < k1) *gp(sp + k) = (uint8_t)(o[k >> 2] >> ((k & 3) * 8));
-        }
-    }
-}
-
-// In-place left shift of up to two row segments by one pixel, one wave.  Segment a: the bytes
-// of [a_lo, a_hi) take the values sh_a bytes to their right; segment b likewise.  The work is
-// cut into 16-byte slots aligned to absolute addresses; a pass gives each lane U slots of each
-// segment and issues every load of the pass before any store.  A slot's store writes only inside
-// the slot, and the bytes it needs beyond its end belong to the next slot of the same segment,
-// loaded in the same pass or a later one -- so the in-place update is hazard free.
-template <int U, bool COH>
-__device__ __forceinline__ void shift_segments_wave(uint8_t* a_lo_p, uint8_t* a_hi_p, int sh_a, uint8_t* b_lo_p,
-                                                    uint8_t* b_hi_p, int sh_b, int lane) {
-    const Seg A = make_seg(a_lo_p, a_hi_p, sh_a);
-    const Seg B = make_seg(b_lo_p, b_hi_p, sh_b);
-    const int n = max(A.n, B.n);
+__device__ __forceinline__ void shift_segment_wave(uint8_t* lo_p, uint8_t* hi_p, int sh, int lane) {
+    const int lo = (int)((uintptr_t)lo_p & 15);
+    uint8_t* const base = lo_p - lo;  // 16-byte aligned (wave-uniform)
+    const int hi = hi_p > lo_p ? lo + (int)(hi_p - lo_p) : lo;
+    const int n = hi > lo ? ((hi - 1) >> 4) + 1 : 0;  // slots covering the segment
 #pragma unroll 1
     for (int fb = 0; fb < n; fb += 64 * U) {
-        uint32_t DA[U][5], DB[U][5];
-        seg_load<U, COH>(A, fb, lane, DA);
-        seg_load<U, COH>(B, fb, lane, DB);
-        seg_store<U>(A, fb, lane, DA);
-        seg_store<U>(B, fb, lane, DB);
+        uint32_t D[U][5];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = fb + u * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) D[u][i] = 0;
+            if (f < n) {
+                const uint32_t so = (uint32_t)f << 4;  // slot offset from the uniform base
+                const uint64_t* q = reinterpret_cast<const uint64_t*>(base + so);
+                const uint64_t v0 = *gp(q), v1 = *gp(q + 1);
+                D[u][0] = (uint32_t)v0; D[u][1] = (uint32_t)(v0 >> 32);
+                D[u][2] = (uint32_t)v1; D[u][3] = (uint32_t)(v1 >> 32);
+                if ((int)so + 16 - sh < hi) D[u][4] = *gp(reinterpret_cast<const uint32_t*>(base + so + 16));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = fb + u * 64 + lane;
+            if (f >= n) continue;
+            const int so = f << 4;
+            uint8_t* sp = base + so;
+            uint32_t o[4];
+            if (sh == 4) {
+                o[0] = D[u][1]; o[1] = D[u][2]; o[2] = D[u][3]; o[3] = D[u][4];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_alignbyte(D[u][i + 1], D[u][i], (uint32_t)sh);
+            }
+            if (so >= lo && so + 16 <= hi) {
+                *gp(reinterpret_cast<u32x4*>(sp)) = u32x4{o[0], o[1], o[2], o[3]};
+            } else {
+                // a slot at the segment's edge: store only the bytes inside the segment, one predicated
+                // byte store per position (static offsets and register indices)
+                const int k0 = so > lo ? 0 : lo - so;
+                const int k1 = so + 16 < hi ? 16 : hi - so;
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (k >= k0 && k < k1) *gp(sp + k) = (uint8_t)(o[k >> 2] >> ((k & 3) * 8));
+            }
+        }
     }
 }
 
@@ -283,7 +246,7 @@ __global__ void remove_seam_kernel(uint8_t* __restrict__ img, int H, int W, int 
         const int s = *gp(seam + y);
         if (s < 0 || s >= W) continue;
         uint8_t* row = img + (long long)y * pitch;
-        shift_segments_wave<4, false>(row + (long long)s * C, row + (long long)(W - 1) * C, C, row, row, 1, lane);
+        shift_segment_wave<4>(row + (long long)s * C, row + (long long)(W - 1) * C, C, lane);
     }
 }
 

@@ -16,7 +16,7 @@
 // backtrack keeps cost and ancestor offset in two words (10 instructions per column and row, where one
 // word takes five).  The seam's cost says how many masked pixels it takes, and the carve ends when none is left.  What bounds it
 // is the plain carve's chain of rows; 1080p with a mask of 401 x 201 and the size restored:
-// 198 ms by one workgroup (below), 27 ms by a team of 16.
+// 198 ms by one workgroup (below), 24 ms by a team of 16.
 //
 // Taller frames: one 1024-thread workgroup carves one image (thread t owns columns [CPL*t, CPL*t +
 // CPL)), with (q, E) as one 64-bit key (q in the high word; E << 9 | ancestor offset in the low word,
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256) void obj_weights_kernel(const ObjImg* __restri
 #pragma unroll
     for (int x = 32; x > 0; x >>= 1) cnt += __shfl_xor(cnt, x);
     if ((threadIdx.x & 63) == 0 && cnt)
-        __hip_atomic_fetch_add(&gp(reinterpret_cast<Ctl*>(d.amin))->left, (unsigned)cnt, __ATOMIC_RELAXED,
+        __hip_atomic_fetch_add(&gp(reinterpret_cast<Ctl*>(d.bar))->left, (unsigned)cnt, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kObjThreads, 4) void obj_team_kernel(const ObjImg* 
     if ((blockIdx.x & 7) || (int)(blockIdx.x >> 3) >= G) return;
     MaskedCarver::carve_image(gd, blockIdx.x >> 3, G, team_word(gd), sm, 0);
     if (MaskedCarver::first_member(sm, G)) {
-        const GAS Ctl* c = gp(reinterpret_cast<const Ctl*>(gd->amin));
+        const GAS Ctl* c = gp(reinterpret_cast<const Ctl*>(gd->bar));
         GAS ObjCtl* r = gp(o->ctl);
         r->k = __hip_atomic_load(&c->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? -1 : (int)c->done;
         r->left = (int)__hip_atomic_load(&c->left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
