@@ -1086,9 +1086,18 @@ struct Carver : Rows<block_rows(KR), KD> {
                     if constexpr (FWD) {  // the low C bytes of each pixel's dword
                         const uint32_t* src = reinterpret_cast<const uint32_t*>(d.wk + (long long)(rc + i) * d.wp) + o;
                         uint8_t* dst = d.img + (long long)(rc + i) * d.pitch;
-                        for (int x = lane; x < d.target_w; x += 64) {
-                            const uint32_t px = *gp(src + x);
-                            for (int c = 0; c < d.C; ++c) *gp(dst + (long long)x * d.C + c) = (uint8_t)(px >> (8 * c));
+                        // (eight loads in flight; one by one they are most of a carve of a single seam: 16447 x 8192
+                        // 14.9 ms, 5.7 so)
+                        for (int x0 = 0; x0 < d.target_w; x0 += 512) {
+                            uint32_t px[8];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) px[u] = *gp(src + min(x0 + 64 * u + lane, d.target_w - 1));
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) {
+                                const int x = x0 + 64 * u + lane;
+                                if (x >= d.target_w) continue;
+                                for (int c = 0; c < d.C; ++c) *gp(dst + (long long)x * d.C + c) = (uint8_t)(px[u] >> (8 * c));
+                            }
                         }
                         continue;
                     }
