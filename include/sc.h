@@ -38,7 +38,7 @@
  *     ordered on one stream.
  *   - Teams: where several workgroups carve an image they sit on one XCD.  When
  *     other work holds that XCD's slots a team carves with those of its
- *     workgroups that start in time (0.2 ms to 10 ms, by the seams to remove),
+ *     workgroups that start in time (0.2 ms to 50 ms, by the seams to remove),
  *     down to one; the results are the same.
  */
 #ifndef SEAMCARVE_SC_H

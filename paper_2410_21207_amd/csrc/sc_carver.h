@@ -1121,8 +1121,12 @@ struct Carver : Rows<block_rows(KR), KD> {
         GAS Ctl* ctl = gp(reinterpret_cast<Ctl*>(d.bar));
         const int nseams = d.mode ? 1 : d.W - d.target_w;
         if (G > 1) {  // (first: a workgroup that comes late must not read what its team is changing)
-            if (threadIdx.x == 0)
-                sm.me = join_team<DevMem, DevClock>(join, (int)xcc_id(), G, team_patience(max_seams > 0 ? min(nseams, max_seams) : nseams));
+            if (threadIdx.x == 0) {
+                const unsigned long long now = wall_clock64();
+                sm.me = join_team<DevMem, DevClock>(join, (int)xcc_id(), G,
+                                                    team_patience(max_seams > 0 ? min(nseams, max_seams) : nseams,
+                                                                  deadline > now ? deadline - now : 0ull));
+            }
             __syncthreads();
             rank = __builtin_amdgcn_readfirstlane(sm.me.rank);
             G = __builtin_amdgcn_readfirstlane(sm.me.size);

@@ -53,11 +53,15 @@ TEAM_FN Member join_team(Word* word, int xcd, int G, unsigned long long patience
     const int size = (int)(w >> kTeamClosed);
     return {rank, size & 63, (size & 64) != 0};
 }
-// Ticks of the 100 MHz clock that a team of `seams` seams waits for its missing workgroups: 0.2 ms,
-// many times what a dispatch takes, and 20 us per seam, less than a whole team saves on most (a seam of
-// 1003 x 701 takes 38 us by 16 workgroups and 110 by one), at most 10 ms.
-TEAM_FN unsigned long long team_patience(int seams) {
-    return seams < 490 ? 20000ull + 2000ull * (unsigned)seams : 1000000ull;
+// Ticks of the 100 MHz clock that a team of `seams` seams waits for its missing workgroups: 0.2 ms, many
+// times what a dispatch takes, and about as long as the whole team then takes for its seams, 50 us each
+// (1003 x 701 takes 38 us by 16 workgroups and 110 by one), at most 50 ms; a quarter of the time
+// budget where there is one.  A wait in vain so at most doubles the time, and what a team that went without its
+// members loses is more: 256 images launched with a 25 ms carve that held slots of their XCD took 269 ms
+// with 20 us per seam and a cap of 10 ms, which closed the longest image's team early, and take 177 to 197 (175 alone).
+TEAM_FN unsigned long long team_patience(int seams, unsigned long long budget) {
+    const unsigned long long p = seams < 996 ? 20000ull + 5000ull * (unsigned)seams : 5000000ull;
+    return budget && budget / 4 < p ? budget / 4 : p;
 }
 
 // The end of a call by its time budget (step-wise carving).  The team's first member decides before

@@ -106,7 +106,8 @@ int main() {
         for (auto& x : slots) x.join();
         for (int t = 0; t < T; ++t) expect(done[t].load() == 1, "a team that did not end once");
     }
-    expect(sc::team_patience(1) >= 20000 && sc::team_patience(100000) <= 1000000, "patience out of range");
+    expect(sc::team_patience(1, 0) >= 20000 && sc::team_patience(1 << 30, 0) <= 5000000 && sc::team_patience(900, 2000) == 500,
+           "patience out of range");
     if (!bad) std::printf("all teams formed\n");
     return bad != 0;
 }
